@@ -27,7 +27,8 @@ FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",
 # FP8 first layer 5 % and FastMemb's first layer 7 % faster, bitwise the same
 # outputs, every other kernel unchanged).
 FILE_FLAGS = {"probe.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-              "conv_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+              "conv_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+              "conv_split.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def sources():

@@ -102,6 +102,7 @@ struct VariantInfo {
   int rowq = 0;         // 1: row-quad K order (k_slot); 0: flattened
   int groups = 0;       // 1: a work item is a tile of four phases whose max filters share
                         // fragments (spaced layers whose max filter has half their spacing)
+  int split = 0;        // FP32 operands as f16 hi + lo pairs (conv_split); 2: max-out row order
 };
 
 // K order of the implicit-GEMM convs over one channel block. K slot c is read
@@ -149,6 +150,15 @@ __host__ __device__ inline KSlot k_slot(int c, int ks, int nchb, bool rowq) {
   return k;
 }
 
+// Output channel of MFMA row r (0..15) of n-block nb of a split conv. Natural
+// order, except that the max-out kinds interleave each pair of n-blocks, so that
+// a lane's rows 4g .. 4g + 3 of both are 8 consecutive channels (4 stored ones,
+// 16 bytes).
+__host__ __device__ constexpr int split_chan(int nb, int r, int nnb, bool maxout) {
+  if (!maxout || (nb | 1) >= nnb) return nb * 16 + r;
+  return 32 * (nb >> 1) + 8 * (r >> 2) + (nb & 1) * 4 + (r & 3);
+}
+
 struct FirstInfo {
   int prec_out, cout, ks;
   int maxout;  // 1: bias + max-out over channel pairs (stores cout / 2 channels); 0: bias + ReLU
@@ -159,7 +169,10 @@ struct FirstInfo {
   const char* name;
 };
 
-// Registries implemented in conv_kernels.hip.
+// Registries implemented in conv_kernels.hip and (split FP32 convs, which come
+// first in conv_variant's index range) conv_split.hip.
+int split_variant_count();
+const VariantInfo* split_variant(int i);
 int conv_variant_count();
 const VariantInfo* conv_variant(int i);
 int first_variant_count();

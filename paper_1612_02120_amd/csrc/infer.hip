@@ -935,7 +935,8 @@ extern "C" int cnn_autotune(cnn_net* h, int64_t H, int64_t W, const char* cache_
     for (int c : L.candidates) {
       // only candidates with the default's accumulation order (K layout and channel block)
       if (!L.first && (conv_variant(c)->rr != conv_variant(def)->rr || conv_variant(c)->cb != conv_variant(def)->cb ||
-                       conv_variant(c)->fused != conv_variant(def)->fused))
+                       conv_variant(c)->fused != conv_variant(def)->fused ||
+                       conv_variant(c)->split != conv_variant(def)->split))
         continue;
       select_variant(L, c);
       rc = run_one_layer(net, l, layer_in(l), bufs[nl + 1], d, st);  // warm-up, also the checked output
@@ -1106,7 +1107,8 @@ extern "C" int cnn_autotune_batch(cnn_net* h, const cnn_tile* tiles, int32_t n, 
         // only candidates with the default's accumulation order
         if (!L.first && (conv_variant(cand)->rr != conv_variant(defaults[l])->rr ||
                          conv_variant(cand)->cb != conv_variant(defaults[l])->cb ||
-                         conv_variant(cand)->fused != conv_variant(defaults[l])->fused))
+                         conv_variant(cand)->fused != conv_variant(defaults[l])->fused ||
+                         conv_variant(cand)->split != conv_variant(defaults[l])->split))
           continue;
         std::vector<int> trial = best;
         trial[l] = cand;

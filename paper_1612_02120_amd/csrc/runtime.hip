@@ -107,6 +107,38 @@ static std::vector<int> find_conv_variants(int prec, int cin, int cout, int ks, 
   return v;
 }
 
+// Upload one candidate's packed weights, and (with the first candidate) the
+// per-channel data that all candidates of the layer share.
+static int upload_conv(ExecLayer& L, const VariantInfo* v, const std::vector<uint8_t>& pk, const double* b,
+                       const std::vector<float>& osc, const double* hw, double hb, double next_scale) {
+  const int cout = v->cout;
+  const std::vector<float> bias(b, b + cout);
+  hipError_t e;
+  void* wdev = nullptr;
+  if ((e = hipMalloc(&wdev, pk.size())) != hipSuccess) return hip_fail(e, "hipMalloc(weights)");
+  L.wpacks.push_back(wdev);
+  if ((e = hipMemcpy(wdev, pk.data(), pk.size(), hipMemcpyHostToDevice)) != hipSuccess)
+    return hip_fail(e, "hipMemcpy(weights)");
+  if (L.bias) return CNN_OK;  // per-channel data shared by all candidates is already set
+  if ((e = hipMalloc(&L.bias, cout * sizeof(float))) != hipSuccess) return hip_fail(e, "hipMalloc(bias)");
+  if ((e = hipMemcpy(L.bias, bias.data(), cout * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
+    return hip_fail(e, "hipMemcpy(bias)");
+  if (v->prec == FP8) {
+    if ((e = hipMalloc(&L.oscale, cout * sizeof(float))) != hipSuccess) return hip_fail(e, "hipMalloc(scale)");
+    if ((e = hipMemcpy(L.oscale, osc.data(), cout * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
+      return hip_fail(e, "hipMemcpy(scale)");
+  }
+  if (v->head) {
+    std::vector<float> h(hw, hw + cout);
+    if ((e = hipMalloc(&L.head_w, cout * sizeof(float))) != hipSuccess) return hip_fail(e, "hipMalloc(head)");
+    if ((e = hipMemcpy(L.head_w, h.data(), cout * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
+      return hip_fail(e, "hipMemcpy(head)");
+    L.head_b = (float)hb;
+  }
+  L.out_inv_scale = next_scale > 0 ? (float)(1.0 / next_scale) : 1.0f;
+  return CNN_OK;
+}
+
 static int pack_conv(ExecLayer& L, int variant, const double* w, const double* b, const double* hw, double hb,
                      double in_scale, double next_scale) {
   const VariantInfo* v = conv_variant(variant);
@@ -178,31 +210,167 @@ static int pack_conv(ExecLayer& L, int variant, const double* w, const double* b
             }
           }
         }
-  std::vector<float> bias(b, b + cout);
-  hipError_t e;
-  void* wdev = nullptr;
-  if ((e = hipMalloc(&wdev, bytes)) != hipSuccess) return hip_fail(e, "hipMalloc(weights)");
-  L.wpacks.push_back(wdev);
-  if ((e = hipMemcpy(wdev, pk.data(), bytes, hipMemcpyHostToDevice)) != hipSuccess)
-    return hip_fail(e, "hipMemcpy(weights)");
-  if (L.bias) return CNN_OK;  // per-channel data shared by all candidates is already set
-  if ((e = hipMalloc(&L.bias, cout * sizeof(float))) != hipSuccess) return hip_fail(e, "hipMalloc(bias)");
-  if ((e = hipMemcpy(L.bias, bias.data(), cout * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
-    return hip_fail(e, "hipMemcpy(bias)");
-  if (v->prec == FP8) {
-    if ((e = hipMalloc(&L.oscale, cout * sizeof(float))) != hipSuccess) return hip_fail(e, "hipMalloc(scale)");
-    if ((e = hipMemcpy(L.oscale, osc.data(), cout * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
-      return hip_fail(e, "hipMemcpy(scale)");
+  return upload_conv(L, v, pk, b, osc, hw, hb, next_scale);
+}
+
+// ------------------------------------------------------------------ split FP32 convs
+
+// Range of every stored activation channel of a layer, over all images.
+struct Bounds {
+  std::vector<double> lo, hi;
+};
+
+// Bounds of a conv's stored output from its input's: interval arithmetic over
+// the taps, then the activation (max filters and subsamples keep a channel's
+// range). Exact up to the rounding of FP32 sums, which split_scales' factor of
+// two covers.
+static Bounds conv_bounds(const cnn_layer& l, const double* w, const double* b, const Bounds& in) {
+  Bounds o;
+  const size_t taps = (size_t)l.k * l.k;
+  for (int co = 0; co < l.cout; ++co) {
+    double lo = b[co], hi = b[co];
+    for (int ci = 0; ci < l.cin; ++ci) {
+      const double* p = w + ((size_t)co * l.cin + ci) * taps;
+      double pos = 0, neg = 0;
+      for (size_t t = 0; t < taps; ++t) (p[t] > 0 ? pos : neg) += p[t];
+      hi += pos * in.hi[ci] + neg * in.lo[ci];
+      lo += pos * in.lo[ci] + neg * in.hi[ci];
+    }
+    if (l.act == CNN_ACT_RELU) {
+      lo = std::max(lo, 0.0);
+      hi = std::max(hi, 0.0);
+    }
+    if (l.act == CNN_ACT_MAXOUT && (co & 1)) {
+      o.lo.back() = std::max(o.lo.back(), lo);
+      o.hi.back() = std::max(o.hi.back(), hi);
+    } else {
+      o.lo.push_back(lo);
+      o.hi.push_back(hi);
+    }
   }
-  if (v->head) {
-    std::vector<float> h(hw, hw + cout);
-    if ((e = hipMalloc(&L.head_w, cout * sizeof(float))) != hipSuccess) return hip_fail(e, "hipMalloc(head)");
-    if ((e = hipMemcpy(L.head_w, h.data(), cout * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
-      return hip_fail(e, "hipMemcpy(head)");
-    L.head_b = (float)hb;
+  return o;
+}
+
+// Power-of-two scales of a split conv (conv_split): iscale brings the bound of
+// each input channel to (2^14, 2^15], a factor of two below f16's largest
+// value, and rexp each output channel's largest weight (taken against the
+// scaled inputs) to the same range. Powers of two are exact, so the scales
+// change no product; a product's error is then relative to the largest value
+// its channel can take and its row's largest weight. False (keep the FP32
+// kernels) where a bound or weight is not finite or a scale leaves FP32's
+// normal exponents.
+static bool split_scales(int cin, int cout, int ks, const double* w, const Bounds& in, std::vector<int>& iexp,
+                         std::vector<int>& rexp) {
+  if ((int)in.lo.size() != cin) return false;
+  const size_t taps = (size_t)ks * ks;
+  iexp.assign(cin, 0);
+  rexp.assign(cout, 0);
+  for (int ci = 0; ci < cin; ++ci) {
+    const double m = std::max(std::fabs(in.lo[ci]), std::fabs(in.hi[ci]));
+    if (!std::isfinite(in.lo[ci]) || !std::isfinite(in.hi[ci])) return false;
+    if (m > 0) iexp[ci] = 14 - std::ilogb(m);
+    if (std::abs(iexp[ci]) > 100) return false;
   }
-  L.out_inv_scale = next_scale > 0 ? (float)(1.0 / next_scale) : 1.0f;
-  return CNN_OK;
+  for (int co = 0; co < cout; ++co) {
+    double m = 0;
+    for (int ci = 0; ci < cin; ++ci)
+      for (size_t t = 0; t < taps; ++t) {
+        const double a = std::fabs((double)(float)w[((size_t)co * cin + ci) * taps + t]);
+        if (!std::isfinite(a)) return false;
+        m = std::max(m, std::ldexp(a, -iexp[ci]));
+      }
+    if (m > 0) rexp[co] = 14 - std::ilogb(m);
+    if (std::abs(rexp[co]) > 100) return false;
+  }
+  return true;
+}
+
+// Nearest f16 code of x (ties to even, |x| below 2^16) and, in val, its value.
+static uint16_t f16_code(float x, float& val) {
+  uint32_t u;
+  std::memcpy(&u, &x, 4);
+  const uint32_t sign = u & 0x80000000u, m = u & 0x7fffffffu;
+  uint32_t h;
+  if (m >= 0x38800000u) {  // 2^-14 and above: drop 13 mantissa bits, rounding
+    h = (m + 0xfffu + ((m >> 13) & 1u)) >> 13;
+    const uint32_t back = (h << 13) | sign;
+    std::memcpy(&val, &back, 4);
+    h -= 112u << 10;
+  } else {  // subnormal: a multiple of 2^-24
+    const float a = std::fabs(x);
+    h = (uint32_t)std::nearbyint(a * 16777216.0f);
+    val = std::copysign((float)h * (1.0f / 16777216.0f), x);
+  }
+  return (uint16_t)(h | (sign >> 16));
+}
+
+// Scaled and split weights of one layer (split_scales' scales), for every split
+// candidate of the layer.
+struct SplitWeights {
+  bool ok = false;
+  std::vector<uint16_t> hi, lo;       // [co][tap][ci]
+  std::vector<float> iscale, oscale;  // 2^iexp per input channel, 2^-rexp per output channel
+};
+
+static SplitWeights split_weights(const cnn_layer& l, const double* w, const Bounds& in) {
+  SplitWeights s;
+  std::vector<int> iexp, rexp;
+  s.ok = split_scales(l.cin, l.cout, l.k, w, in, iexp, rexp);
+  if (!s.ok) return s;
+  const int taps = l.k * l.k;
+  s.hi.resize((size_t)l.cout * taps * l.cin);
+  s.lo.resize(s.hi.size());
+  for (int ci = 0; ci < l.cin; ++ci) s.iscale.push_back(std::ldexp(1.0f, iexp[ci]));
+  for (int co = 0; co < l.cout; ++co) {
+    s.oscale.push_back(std::ldexp(1.0f, -rexp[co]));
+    for (int ci = 0; ci < l.cin; ++ci) {
+      const double sc = std::ldexp(1.0, rexp[co] - iexp[ci]);
+      for (int t = 0; t < taps; ++t) {
+        // exact: a power of two times an FP32 value (what underflows FP32 here is below 2^-100 of its row)
+        const float x = (float)((double)(float)w[((size_t)co * l.cin + ci) * taps + t] * sc);
+        const size_t at = ((size_t)co * taps + t) * l.cin + ci;
+        float hv, lv;
+        s.hi[at] = f16_code(x, hv);
+        s.lo[at] = f16_code(x - hv, lv);
+      }
+    }
+  }
+  return s;
+}
+
+// Weights of a split conv: fragments [channel block][group-step][n-block][hi,
+// lo][lane][8 f16], lane (n16, g) holding channel split_chan of row n16 for the
+// 8 input channels of slot 4 s + g; then float iscale[cin], oscale[cout].
+static int pack_split(ExecLayer& L, int variant, const SplitWeights& sw, const double* b, const double* hw, double hb) {
+  const VariantInfo* v = conv_variant(variant);
+  const int cin = v->cin, cout = v->cout, ks = v->ks, cb = v->cb, ncb = cin / cb, nb = cout / 16;
+  const size_t frags = (size_t)ncb * v->ngs * nb * 2 * 1024;
+  std::vector<uint8_t> pk(frags + (size_t)(cin + cout) * 4, 0);
+  for (int c0 = 0; c0 < ncb; ++c0)
+    for (int s = 0; s < v->ngs; ++s)
+      for (int g = 0; g < 4; ++g) {
+        const KSlot k = k_slot(4 * s + g, ks, cb / 8, false);
+        if (!k.live) continue;
+        for (int q = 0; q < nb; ++q)
+          for (int r = 0; r < 16; ++r) {
+            const int co = split_chan(q, r, nb, v->split == 2);
+            const size_t at = ((size_t)co * ks * ks + k.i * ks + k.j) * cin + c0 * cb + k.cg * 8;
+            uint8_t* dst = pk.data() + (((size_t)(c0 * v->ngs + s) * nb + q) * 2 * 64 + g * 16 + r) * 16;
+            std::memcpy(dst, &sw.hi[at], 16);
+            std::memcpy(dst + 1024, &sw.lo[at], 16);
+          }
+      }
+  std::memcpy(pk.data() + frags, sw.iscale.data(), (size_t)cin * 4);
+  std::memcpy(pk.data() + frags + (size_t)cin * 4, sw.oscale.data(), (size_t)cout * 4);
+  return upload_conv(L, v, pk, b, {}, hw, hb, 0.0);
+}
+
+// Drop a layer's split candidates unless its scales exist (split_scales).
+static void keep_split(ExecLayer& L, bool ok) {
+  if (ok) return;
+  L.candidates.erase(std::remove_if(L.candidates.begin(), L.candidates.end(),
+                                    [](int v) { return conv_variant(v)->split != 0; }),
+                     L.candidates.end());
 }
 
 // First-layer weights as per-lane MFMA B fragments (see conv_first):
@@ -420,6 +588,9 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
   }
   const double* wp = weights;
   int sp = 1;  // spacing of the current layer's input
+  // ranges of the current layer's input channels (V / 255 lies in [0, 1]); real-valued maps have none
+  Bounds act;
+  if (!maps) act = Bounds{{0.0}, {1.0}};
   for (size_t c = 0; c < conv_at.size(); ++c) {
     const cnn_layer& l = Lr[conv_at[c]];
     const int64_t nwl = (int64_t)l.cout * l.cin * l.k * l.k;
@@ -431,6 +602,9 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
     E.cin = l.cin;
     E.spaced = 1;
     int rc = CNN_OK;
+    SplitWeights split;
+    if (prec == CNN_PREC_FP32) split = split_weights(l, w, act);
+    if (!act.lo.empty()) act = conv_bounds(l, w, b, act);
     if (c == 0 && maps) {
       // a spaced conv straight on the caller's NHWC float maps: no max filter, spacing 1
       E.cout = l.cout;
@@ -443,6 +617,7 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
       E.candidates.erase(std::remove_if(E.candidates.begin(), E.candidates.end(),
                                         [](int v) { return conv_variant(v)->groups != 0; }),
                          E.candidates.end());  // no max filter: no phase groups
+      keep_split(E, false);  // its input has no bound
       if (E.candidates.empty()) return unsupported("no kernel for a first conv " + std::to_string(l.cin) + " -> " +
                                                    std::to_string(l.cout));
       for (int v : E.candidates)
@@ -520,11 +695,14 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
           E.candidates.erase(std::remove_if(E.candidates.begin(), E.candidates.end(),
                                             [](int v) { return conv_variant(v)->groups != 0; }),
                              E.candidates.end());
+        keep_split(E, split.ok);
         if (E.candidates.empty())
           return unsupported("no MFMA kernel for conv " + std::to_string(c) + " (" + std::to_string(l.cin) + " -> " +
                              std::to_string(l.cout) + ")");
         for (int v : E.candidates)
-          if (rc == CNN_OK) rc = pack_conv(E, v, w, b, nullptr, 0.0, 1.0, 0.0);
+          if (rc == CNN_OK)
+            rc = conv_variant(v)->split ? pack_split(E, v, split, b, nullptr, 0.0)
+                                        : pack_conv(E, v, w, b, nullptr, 0.0, 1.0, 0.0);
       }
     }
     E.variant = E.candidates[0];
@@ -696,6 +874,7 @@ extern "C" int cnn_create(const double* weights, int64_t n_weights, const cnn_la
   int pending_pool = 0;
   int conv_i = 0;
   int rc = CNN_OK;
+  Bounds act{{0.0}, {1.0}};  // ranges of the current layer's input channels (V / 255)
   // next FP8 input scale of the conv following layer i
   auto next_conv_scale = [&](int i) -> double {
     for (int k = i + 1; k < nl; ++k)
@@ -720,6 +899,9 @@ extern "C" int cnn_create(const double* weights, int64_t n_weights, const cnn_la
     const double* b = wp + nwl;
     wp += nwl + l.cout;
     if (i == nl - 1) break;  // head: fused into the previous conv
+    SplitWeights split;
+    if (prec == CNN_PREC_FP32) split = split_weights(l, w, act);
+    act = conv_bounds(l, w, b, act);
     ExecLayer E;
     E.cin = l.cin;
     E.cout = l.cout;
@@ -757,6 +939,7 @@ extern "C" int cnn_create(const double* weights, int64_t n_weights, const cnn_la
         }
         E.candidates.swap(keep);
       }
+      keep_split(E, split.ok);
       if (E.candidates.empty()) {
         rc = fail(CNN_EUNSUPPORTED, "cnn_create: no MFMA kernel for conv " + std::to_string(i));
         break;
@@ -774,7 +957,9 @@ extern "C" int cnn_create(const double* weights, int64_t n_weights, const cnn_la
         hb = wp[hd.cin];
       }
       for (int c : E.candidates) {
-        if (rc == CNN_OK) rc = pack_conv(E, c, w, b, hw, hb, in_scale, fuse_head ? 0.0 : nxt);
+        if (rc == CNN_OK)
+          rc = conv_variant(c)->split ? pack_split(E, c, split, b, hw, hb)
+                                      : pack_conv(E, c, w, b, hw, hb, in_scale, fuse_head ? 0.0 : nxt);
       }
       if (rc == CNN_OK) select_variant(E, E.variant);
     }
