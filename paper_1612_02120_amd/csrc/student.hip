@@ -29,6 +29,10 @@ namespace emcnn {
 constexpr int S_C = 8;  // student channels
 constexpr int S_NP = 801;
 constexpr int OFF_W1 = 0, OFF_B1 = 200, OFF_W2 = 208, OFF_B2 = 784, OFF_WH = 792, OFF_BH = 800;
+// Working weights again, in the orders the training kernels read them: eight
+// consecutive floats (one scalar load) per tap and channel.
+//   OFF_W1T [tap][co], OFF_W2T [tap][ci][co], OFF_W2U [tap][co][ci]
+constexpr int OFF_W1T = 808, OFF_W2T = OFF_W1T + 200, OFF_W2U = OFF_W2T + 576, S_NWW = OFF_W2U + 576;
 
 __device__ __forceinline__ float s_relu(float v) { return v > 0.0f ? v : 0.0f; }
 __device__ __forceinline__ float s_bf16(float v) { return (float)(__bf16)v; }
@@ -258,184 +262,498 @@ __global__ __launch_bounds__(256) void student_mfma(const uint8_t* in, int64_t i
 
 // ------------------------------------------------------------------ training kernels
 
-// h1[b][y][x][c] over (P-4)^2 positions (post-ReLU; bf16-valued in BF16 mode)
-__global__ void st_conv1(const uint8_t* __restrict__ patches, int B, int P, const float* __restrict__ ww,
-                         float* __restrict__ h1, int bf16) {
-  const int P1 = P - 4;
-  const int64_t n = (int64_t)B * P1 * P1;
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
-    const int b = (int)(p / ((int64_t)P1 * P1));
-    const int rem = (int)(p % ((int64_t)P1 * P1));
-    const int y = rem / P1, x = rem % P1;
-    const uint8_t* s = patches + (int64_t)b * P * P + (int64_t)y * P + x;
-    float a[S_C];
+// Forward, loss and the activation gradients of one FY x FX tile of h1
+// positions of one patch: h1, h2, dz, dh2 and dh1 in one kernel. Writes, per
+// position and FP32 (bf16-valued in BF16 mode where noted):
+//   h1[b][y][x][c]  over (P-4)^2 positions, post-ReLU (bf16-valued)
+//   h2              over (P-6)^2 positions, post-ReLU
+//   dz              (sigmoid(z) - t) / N
+//   dh2             dz wh [h2 > 0] (bf16-valued)
+//   dh1             sum over co, i, j of W2[co][ci][i][j] dh2[co][y-i][x-j],
+//                   masked by h1 > 0 (bf16-valued)
+// and one FP64 partial of sum(softplus(z) - t z) per block (fixed-order tree).
+// dh1 of a tile needs dh2 two rows and columns before it, which the block
+// recomputes (18 x 34 of h2, 20 x 36 of h1 for 16 x 32): 1.3x the multiply-adds
+// of the layers run one after another, but one launch instead of three, and no
+// layer waits for another's maps. The kernel is bound by the FP32 vector rate;
+// a thread computes up to three positions at once, so that the eight weights of
+// a tap and channel (two broadcast LDS reads) serve 24 FMAs. 32 us at 16 x 128^2 (10 us of them FMAs
+// at the vector rate, 4 us stores; 16 x 16 and 8 x 32 tiles 33 and 35 us, 512
+// threads 37 us). Every value is the same
+// chain of FMAs in the same order as when each layer was a kernel of its own.
+constexpr int FY = 16, FX = 32, FT = 256;  // tile, threads
+__global__ __launch_bounds__(FT) void st_forward(const uint8_t* __restrict__ patches, int P, int tiles_y, int tiles_x,
+                                                  const float* __restrict__ ww, const float* __restrict__ teacher,
+                                                  float* __restrict__ h1, float* __restrict__ h2,
+                                                  float* __restrict__ dz, float* __restrict__ dh2,
+                                                  float* __restrict__ dh1, double* __restrict__ loss_part,
+                                                  double invN, int bf16) {
+  constexpr int XR = FY + 8, XC = FX + 8;  // input tile, from (y0 - 2, x0 - 2)
+  constexpr int HR = FY + 4, HC = FX + 4;  // h1, from (y0 - 2, x0 - 2)
+  constexpr int DR = FY + 2, DC = FX + 2;  // h2 and dh2, from (y0 - 2, x0 - 2)
+  constexpr int N1 = (HR * HC + FT - 1) / FT, N2 = (DR * DC + FT - 1) / FT, N3 = FY * FX / FT;
+  __shared__ float xin[XR * XC];
+  __shared__ float s1[S_C][HR * HC];
+  __shared__ float sd[S_C][DR * DC];
+  __shared__ double red[FT];
+  __shared__ __attribute__((aligned(16))) float wl[S_NWW - OFF_W1T];  // W1T, W2T, W2U
+  const int tid = threadIdx.x;
+  const int P1 = P - 4, P2 = P - 6;
+  const int tiles = tiles_y * tiles_x;
+  const int64_t b = blockIdx.x / tiles;
+  const int rt = (int)(blockIdx.x % tiles);
+  const int y0 = (rt / tiles_x) * FY, x0 = (rt % tiles_x) * FX;
+  const uint8_t* src = patches + b * P * P;
+  // every load of the block's inputs in flight before the first is used: input
+  // tile, weights, and the targets of this thread's h2 positions
+  constexpr int NX = (XR * XC + FT - 1) / FT, NW = ((S_NWW - OFF_W1T) / 4 + FT - 1) / FT;
+  static_assert((S_NWW - OFF_W1T) % 4 == 0 && OFF_W1T % 4 == 0, "weights copied in 16-byte chunks");
+  unsigned char xb[NX];
+  f4 wb[NW];
+  float tv[N2];
 #pragma unroll
-    for (int co = 0; co < S_C; ++co) a[co] = ww[OFF_B1 + co];
+  for (int k = 0; k < NX; ++k) {
+    const int t = min(tid + k * FT, XR * XC - 1);
+    const int y = min(max(y0 - 2 + t / XC, 0), P - 1), x = min(max(x0 - 2 + t % XC, 0), P - 1);
+    xb[k] = src[(int64_t)y * P + x];
+  }
 #pragma unroll
+  for (int k = 0; k < NW; ++k)
+    wb[k] = reinterpret_cast<const f4*>(ww + OFF_W1T)[min(tid + k * FT, (S_NWW - OFF_W1T) / 4 - 1)];
+#pragma unroll
+  for (int k = 0; k < N2; ++k) {
+    const int t = min(tid + k * FT, DR * DC - 1);
+    const int y = min(max(y0 - 2 + t / DC, 0), P2 - 1), x = min(max(x0 - 2 + t % DC, 0), P2 - 1);
+    tv[k] = teacher[(b * P2 + y) * P2 + x];
+  }
+#pragma unroll
+  for (int k = 0; k < NX; ++k)
+    if (tid + k * FT < XR * XC) xin[tid + k * FT] = (float)xb[k];
+#pragma unroll
+  for (int k = 0; k < NW; ++k)
+    if (tid + k * FT < (S_NWW - OFF_W1T) / 4) reinterpret_cast<f4*>(wl)[tid + k * FT] = wb[k];
+  __syncthreads();
+  {
+    float a[N1][S_C];
+    int xp[N1];
+#pragma unroll
+    for (int k = 0; k < N1; ++k) {
+      const int t = min(tid + k * FT, HR * HC - 1);
+      xp[k] = (t / HC) * XC + t % HC;
+#pragma unroll
+      for (int co = 0; co < S_C; ++co) a[k][co] = ww[OFF_B1 + co];
+    }
+    // rows rolled: unrolled, the 200 weights overflow the scalar registers
+#pragma unroll 1
     for (int i = 0; i < 5; ++i)
 #pragma unroll
       for (int j = 0; j < 5; ++j) {
-        const float xv = (float)s[i * P + j];
+        const f4* wv = reinterpret_cast<const f4*>(wl + (i * 5 + j) * 8);
+        const f4 wa = wv[0], wb = wv[1];
 #pragma unroll
-        for (int co = 0; co < S_C; ++co) a[co] = fmaf(ww[OFF_W1 + co * 25 + i * 5 + j], xv, a[co]);
+        for (int k = 0; k < N1; ++k) {
+          const float xv = xin[xp[k] + i * XC + j];
+#pragma unroll
+          for (int co = 0; co < S_C; ++co) a[k][co] = fmaf(co < 4 ? wa[co & 3] : wb[co & 3], xv, a[k][co]);
+        }
       }
 #pragma unroll
-    for (int co = 0; co < S_C; ++co) {
-      float v = s_relu(a[co]);
-      h1[p * S_C + co] = bf16 ? s_bf16(v) : v;
+    for (int k = 0; k < N1; ++k) {
+      const int t = tid + k * FT;
+      if (t >= HR * HC) break;
+      const int r = t / HC, c = t % HC, y = y0 - 2 + r, x = x0 - 2 + c;
+      f4 v[2];
+#pragma unroll
+      for (int co = 0; co < S_C; ++co) {
+        const float q = s_relu(a[k][co]);
+        v[co >> 2][co & 3] = bf16 ? s_bf16(q) : q;
+        s1[co][t] = v[co >> 2][co & 3];
+      }
+      if (r >= 2 && c >= 2 && r < 2 + FY && c < 2 + FX && y < P1 && x < P1) {  // this tile's own positions
+        f4* o = reinterpret_cast<f4*>(h1 + ((b * P1 + y) * P1 + x) * S_C);
+        o[0] = v[0];
+        o[1] = v[1];
+      }
     }
   }
-}
-
-// conv2 + head + BCE: h2 (FP32), dz = (sigmoid(z) - t)/N, dh2 = dz wh [h2 > 0]
-// (bf16-valued in BF16 mode), and one FP64 partial of sum(softplus(z) - t z)
-// per block (fixed-order tree inside the block).
-__global__ __launch_bounds__(256) void st_conv2_loss(const float* __restrict__ h1, int B, int P,
-                                                      const float* __restrict__ ww, const float* __restrict__ teacher,
-                                                      float* __restrict__ h2, float* __restrict__ dz,
-                                                      float* __restrict__ dh2, double* __restrict__ loss_part,
-                                                      double invN, int bf16) {
-  __shared__ double red[256];
-  const int P1 = P - 4, P2 = P - 6;
-  const int64_t n = (int64_t)B * P2 * P2;
-  const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  __syncthreads();
   double term = 0.0;
-  if (p < n) {
-    const int b = (int)(p / ((int64_t)P2 * P2));
-    const int rem = (int)(p % ((int64_t)P2 * P2));
-    const int y = rem / P2, x = rem % P2;
-    float a[S_C];
+  {
+    float a[N2][S_C];
+    int hp[N2];
 #pragma unroll
-    for (int co = 0; co < S_C; ++co) a[co] = ww[OFF_B2 + co];
-    const float* hb = h1 + ((int64_t)b * P1 * P1) * S_C;
+    for (int k = 0; k < N2; ++k) {
+      const int t = min(tid + k * FT, DR * DC - 1);
+      hp[k] = (t / DC) * HC + t % DC;
 #pragma unroll
+      for (int co = 0; co < S_C; ++co) a[k][co] = ww[OFF_B2 + co];
+    }
+#pragma unroll 1
     for (int i = 0; i < 3; ++i)
 #pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const float* hp = hb + ((int64_t)(y + i) * P1 + x + j) * S_C;
+      for (int j = 0; j < 3; ++j)
 #pragma unroll
         for (int ci = 0; ci < S_C; ++ci) {
-          const float hv = hp[ci];
+          const f4* wv = reinterpret_cast<const f4*>(wl + OFF_W2T - OFF_W1T + ((i * 3 + j) * 8 + ci) * 8);
+          const f4 wa = wv[0], wb = wv[1];
 #pragma unroll
-          for (int co = 0; co < S_C; ++co) a[co] = fmaf(ww[OFF_W2 + (co * 8 + ci) * 9 + i * 3 + j], hv, a[co]);
-        }
-      }
-    float zl = ww[OFF_BH];
+          for (int k = 0; k < N2; ++k) {
+            const float hv = s1[ci][hp[k] + i * HC + j];
 #pragma unroll
-    for (int co = 0; co < S_C; ++co) {
-      a[co] = s_relu(a[co]);
-      h2[p * S_C + co] = a[co];
-      zl = fmaf(ww[OFF_WH + co], a[co], zl);
-    }
-    const float t = teacher[p];
-    const float g = (s_sigmoid(zl) - t) * (float)invN;
-    dz[p] = g;
-#pragma unroll
-    for (int co = 0; co < S_C; ++co) {
-      float d = a[co] > 0.0f ? g * ww[OFF_WH + co] : 0.0f;
-      dh2[p * S_C + co] = bf16 ? s_bf16(d) : d;
-    }
-    const double zd = (double)zl;
-    term = fmax(zd, 0.0) + log1p(exp(-fabs(zd))) - (double)t * zd;
-  }
-  red[threadIdx.x] = term;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) loss_part[blockIdx.x] = red[0];
-}
-
-// dh1 = sum_{co,i,j} W2[co][ci][i][j] dh2[co][y-i][x-j], masked by h1 > 0
-__global__ void st_dh1(const float* __restrict__ dh2, const float* __restrict__ h1, int B, int P,
-                       const float* __restrict__ ww, float* __restrict__ dh1, int bf16) {
-  const int P1 = P - 4, P2 = P - 6;
-  const int64_t n = (int64_t)B * P1 * P1;
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
-    const int b = (int)(p / ((int64_t)P1 * P1));
-    const int rem = (int)(p % ((int64_t)P1 * P1));
-    const int y = rem / P1, x = rem % P1;
-    float a[S_C];
-#pragma unroll
-    for (int ci = 0; ci < S_C; ++ci) a[ci] = 0.f;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const int yy = y - i, xx = x - j;
-        if (yy < 0 || xx < 0 || yy >= P2 || xx >= P2) continue;
-        const float* d = dh2 + (((int64_t)b * P2 + yy) * P2 + xx) * S_C;
-#pragma unroll
-        for (int co = 0; co < S_C; ++co) {
-          const float dv = d[co];
-#pragma unroll
-          for (int ci = 0; ci < S_C; ++ci) a[ci] = fmaf(ww[OFF_W2 + (co * 8 + ci) * 9 + i * 3 + j], dv, a[ci]);
-        }
-      }
-#pragma unroll
-    for (int ci = 0; ci < S_C; ++ci) {
-      float v = h1[p * S_C + ci] > 0.0f ? a[ci] : 0.0f;
-      dh1[p * S_C + ci] = bf16 ? s_bf16(v) : v;
-    }
-  }
-}
-
-// Partial weight gradients over a chunk of positions: one thread per
-// parameter of the layer, positions in ascending order, FP32 accumulation.
-// layer 0: dY = dh1 (P-4)^2 x 8, X = uint8 patch / 255 (5x5, 1 channel)
-// layer 1: dY = dh2 (P-6)^2 x 8, X = h1 (3x3, 8 channels)
-// layer 2: dY = dz  (P-6)^2 x 1, X = h2 (1x1, 8 channels)
-template <int LAYER>
-__global__ __launch_bounds__(1024) void st_wgrad(const float* __restrict__ dY, const void* __restrict__ X, int B, int P,
-                                                 int chunk, float* __restrict__ part) {
-  constexpr int K = LAYER == 0 ? 5 : LAYER == 1 ? 3 : 1;
-  constexpr int CI = LAYER == 0 ? 1 : 8;
-  constexpr int CO = LAYER == 2 ? 1 : 8;
-  constexpr int NW = CO * CI * K * K;
-  constexpr int NE = NW + CO;
-  constexpr int U = 32;  // positions whose loads are issued together
-  const int Ho = LAYER == 0 ? P - 4 : P - 6;
-  const int Hi = Ho + K - 1;
-  const int64_t n = (int64_t)B * Ho * Ho;
-  const int64_t p0 = (int64_t)blockIdx.x * chunk;
-  const int64_t p1 = min(n, p0 + chunk);
-  for (int e = threadIdx.x; e < NE; e += blockDim.x) {
-    // element e: weight (co, ci, i, j), or the bias of co (then ci = i = j = 0
-    // and the input is not read)
-    const bool wt = e < NW;
-    const int co = wt ? e / (CI * K * K) : e - NW, r = wt ? e % (CI * K * K) : 0;
-    const int ci = r / (K * K), i = (r % (K * K)) / K, j = r % K;
-    // position p0 as (b, y, x), advanced one position at a time below (no
-    // division per position); the sum runs over p = p0 .. p1 - 1 in order
-    int b = (int)(p0 / ((int64_t)Ho * Ho));
-    const int rem = (int)(p0 % ((int64_t)Ho * Ho));
-    int y = rem / Ho, x = rem % Ho;
-    float acc = 0.f;
-    for (int64_t pb = p0; pb < p1; pb += U) {
-      float dv[U], xv[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const bool live = pb + u < p1;
-        const int64_t pp = live ? pb + u : p0;
-        dv[u] = dY[pp * CO + co];
-        const int64_t xi = ((int64_t)b * Hi + y + i) * Hi + x + j;
-        if constexpr (LAYER == 0) xv[u] = (float)reinterpret_cast<const uint8_t*>(X)[live ? xi : 0] * (1.0f / 255.0f);
-        else xv[u] = reinterpret_cast<const float*>(X)[(live ? xi : 0) * CI + ci];
-        if (++x == Ho) {
-          x = 0;
-          if (++y == Ho) {
-            y = 0;
-            ++b;
+            for (int co = 0; co < S_C; ++co) a[k][co] = fmaf(co < 4 ? wa[co & 3] : wb[co & 3], hv, a[k][co]);
           }
         }
+#pragma unroll
+    for (int k = 0; k < N2; ++k) {
+      const int t = tid + k * FT;
+      if (t >= DR * DC) break;
+      const int r = t / DC, c = t % DC, y = y0 - 2 + r, x = x0 - 2 + c;
+      float d[S_C];
+#pragma unroll
+      for (int co = 0; co < S_C; ++co) d[co] = 0.f;
+      if (y >= 0 && x >= 0 && y < P2 && x < P2) {
+        float zl = ww[OFF_BH];
+#pragma unroll
+        for (int co = 0; co < S_C; ++co) {
+          a[k][co] = s_relu(a[k][co]);
+          zl = fmaf(ww[OFF_WH + co], a[k][co], zl);
+        }
+        const int64_t p = (b * P2 + y) * P2 + x;
+        const float g = (s_sigmoid(zl) - tv[k]) * (float)invN;
+#pragma unroll
+        for (int co = 0; co < S_C; ++co) {
+          const float q = a[k][co] > 0.0f ? g * ww[OFF_WH + co] : 0.0f;
+          d[co] = bf16 ? s_bf16(q) : q;
+        }
+        if (r >= 2 && c >= 2) {  // this tile's own positions
+          dz[p] = g;
+          f4* o2 = reinterpret_cast<f4*>(h2 + p * S_C);
+          o2[0] = f4{a[k][0], a[k][1], a[k][2], a[k][3]};
+          o2[1] = f4{a[k][4], a[k][5], a[k][6], a[k][7]};
+          f4* od = reinterpret_cast<f4*>(dh2 + p * S_C);
+          od[0] = f4{d[0], d[1], d[2], d[3]};
+          od[1] = f4{d[4], d[5], d[6], d[7]};
+          const double zd = (double)zl;
+          term += fmax(zd, 0.0) + log1p(exp(-fabs(zd))) - (double)tv[k] * zd;
+        }
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (pb + u < p1) acc = wt ? fmaf(dv[u], xv[u], acc) : acc + dv[u];
+      for (int co = 0; co < S_C; ++co) sd[co][t] = d[co];
+    }
+  }
+  red[tid] = term;
+  __syncthreads();
+  {
+    float a[N3][S_C];
+#pragma unroll
+    for (int k = 0; k < N3; ++k)
+#pragma unroll
+      for (int ci = 0; ci < S_C; ++ci) a[k][ci] = 0.f;
+#pragma unroll 1
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int k = 0; k < N3; ++k) {
+          const int r = (tid + k * FT) / FX, c = tid % FX;
+          const int yy = y0 + r - i, xx = x0 + c - j;
+          if (yy < 0 || xx < 0 || yy >= P2 || xx >= P2) continue;
+          const int dp = (r + 2 - i) * DC + c + 2 - j;
+#pragma unroll
+          for (int co = 0; co < S_C; ++co) {
+            const f4* wv = reinterpret_cast<const f4*>(wl + OFF_W2U - OFF_W1T + ((i * 3 + j) * 8 + co) * 8);
+            const f4 wa = wv[0], wb = wv[1];
+            const float dv = sd[co][dp];
+#pragma unroll
+            for (int ci = 0; ci < S_C; ++ci) a[k][ci] = fmaf(ci < 4 ? wa[ci & 3] : wb[ci & 3], dv, a[k][ci]);
+          }
+        }
+#pragma unroll
+    for (int k = 0; k < N3; ++k) {
+      const int r = (tid + k * FT) / FX, c = tid % FX, y = y0 + r, x = x0 + c;
+      if (y < P1 && x < P1) {
+        f4 v[2];
+#pragma unroll
+        for (int ci = 0; ci < S_C; ++ci) {
+          const float q = s1[ci][(r + 2) * HC + c + 2] > 0.0f ? a[k][ci] : 0.0f;
+          v[ci >> 2][ci & 3] = bf16 ? s_bf16(q) : q;
+        }
+        f4* o = reinterpret_cast<f4*>(dh1 + ((b * P1 + y) * P1 + x) * S_C);
+        o[0] = v[0];
+        o[1] = v[1];
       }
     }
-    part[(int64_t)blockIdx.x * NE + e] = acc;
+  }
+  for (int s = FT / 2; s > 0; s >>= 1) {
+    if (tid < s) red[tid] += red[tid + s];
+    __syncthreads();
+  }
+  if (tid == 0) loss_part[blockIdx.x] = red[0];
+}
+
+// Partial weight gradients over a chunk of 2048 positions, in FP32: element
+// (co, ci, i, j) sums dY[p][co] X[p + (i, j)][ci] over the chunk's positions in
+// ascending order (one FMA chain per element, so the result does not depend on
+// how the work is laid out), the bias elements sum dY.
+//   layer 0: dY = dh1 (P-4)^2 x 8, X = uint8 patch / 255 (5x5, 1 channel)
+//   layer 1: dY = dh2 (P-6)^2 x 8, X = h1 (3x3, 8 channels)
+//   layer 2: dY = dz  (P-6)^2 x 1, X = h2 (1x1, 8 channels)
+// One launch for all layers: the first blocks take layer 1's chunks together
+// with layer 2's (the same positions), the rest layer 0's.
+//
+// A chain of 2048 dependent FMAs per element bounds a chunk from below, so what
+// counts is how few other instructions each position costs. Rows of a chunk are
+// laid out one after another at the input's row pitch, channel planes apart: a
+// position's K taps of a filter row are then consecutive columns, and dY is zero
+// in the K - 1 columns past a row's outputs (an FMA with 0 leaves a finite chain
+// as it is). A thread holds three taps of one filter row of one (co, ci): per
+// eight columns two 16-byte LDS reads of dY, two of X, and 24 FMAs whose X slides
+// through registers; the biases read an X of ones. Four producer waves stage the
+// next 256 columns meanwhile. Loading dY and X from global memory for every
+// element and position instead (two loads per FMA) left the texture addresser as
+// the bound: 0.26 - 0.40 ms per layer at 16 x 128^2, against 25 us for all three.
+constexpr int WQ = 256;          // columns staged at a time
+constexpr int WPITCH = WQ + 4;   // plane pitch in floats: 8 planes' 16-byte reads fall in distinct banks
+constexpr int kChunk = 2048;     // positions per chunk
+struct WgradArgs {
+  const float *dh1, *h1, *dh2, *h2, *dz;
+  const uint8_t* patches;
+  float* part[3];
+  int64_t n1, n2;
+  int P, nc1;  // nc1: chunks of layers 1 and 2
+};
+
+// A stage. Entry e of a dY plane is column q0 + e; entry e of an X plane is the
+// last of the three taps there, the two columns before it being carried along:
+//   layer 1: x[8 i + ci] = h1 at (row i, column q0 + e + 2), x[24 + c] = h2,
+//            d[co] = dh2, d[8] = dz
+//   layer 0: x[i], x[5 + i] = patch / 255 at (row i, columns q0 + e + 2, + 4)
+//            for taps 0..2 and 2..4, d[co] = dh1
+struct WgBuf {
+  float x[32][WPITCH];
+  float d[9][WPITCH];
+};
+
+// Layout of a chunk in columns: output rows of Ho positions at a pitch of Hi.
+struct WgChunk {
+  unsigned row0;  // first output row, over all patches (batch P^2 <= 2^31: 32 bits)
+  int x0;         // first position's column
+  int nq;         // columns of the chunk
+  __device__ WgChunk(int64_t p0, int64_t p1, int Ho, int Hi) {
+    row0 = (unsigned)p0 / (unsigned)Ho;
+    x0 = (int)((unsigned)p0 % (unsigned)Ho);
+    const unsigned last = (unsigned)(p1 - 1), row1 = last / (unsigned)Ho;
+    nq = (int)(row1 - row0) * Hi + (int)(last % (unsigned)Ho) - x0 + 1;
+  }
+};
+
+__global__ __launch_bounds__(512) void st_wgrad(WgradArgs a) {
+  __shared__ __attribute__((aligned(16))) WgBuf buf[2];
+  __shared__ __attribute__((aligned(16))) float ones[WPITCH];
+  __shared__ int odd[2][4];  // per stage and producer wave: it staged an h1 that is not finite
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int P = a.P, P1 = P - 4, P2 = P - 6;
+  const bool l1 = (int)blockIdx.x < a.nc1;  // uniform: layers 1 and 2, or layer 0
+  const int chunk = l1 ? blockIdx.x : blockIdx.x - a.nc1;
+  const int Ho = l1 ? P2 : P1, Hi = l1 ? P1 : P;
+  const int64_t p0 = (int64_t)chunk * kChunk, p1 = min(l1 ? a.n2 : a.n1, p0 + kChunk);
+  const WgChunk w(p0, p1, Ho, Hi);
+  const int nst = (w.nq + WQ - 1) / WQ;
+  const unsigned rows = (unsigned)(l1 ? a.n2 : a.n1) / (unsigned)Ho;  // output rows over all patches
+  // output row and input column of chunk column q (past the chunk's end: read, never used)
+  auto at = [&](int q, unsigned& row, int& col) __attribute__((always_inline)) {
+    const unsigned v = (unsigned)(q + w.x0);
+    row = min(w.row0 + v / (unsigned)Hi, rows - 1);
+    col = (int)(v % (unsigned)Hi);
+  };
+  // X at (row, col): filter rows i are P1 (P) pixels apart
+  auto x1_at = [&](unsigned row, int col) __attribute__((always_inline)) {
+    const int64_t b = row / (unsigned)P2, y = row % (unsigned)P2;
+    return gin(a.h1) + ((b * P1 + y) * P1 + col) * (S_C * 4);
+  };
+  auto x0_at = [&](unsigned row, int col) __attribute__((always_inline)) {
+    const int64_t b = row / (unsigned)P1, y = row % (unsigned)P1;
+    return gin(a.patches) + (b * P + y) * P + col;
+  };
+
+  if (wave >= 4) {
+    // ---------------- producer waves: one column per thread; the next stage's
+    // loads are in flight while this stage is computed
+    const int pt = tid - 256;
+    ones[pt] = 1.0f;
+    if (pt < WPITCH - 256) ones[256 + pt] = 1.0f;
+    f4 v[3][2], dv[2], hv[2];
+    float zv = 0.f;
+    unsigned char b5[2][5];
+    bool live = false;
+    auto load = [&](int k) __attribute__((always_inline)) {
+      const int q = k * WQ + pt;
+      unsigned row, rx;
+      int col, cx;
+      at(q, row, col);
+      at(q + 2, rx, cx);
+      live = col < Ho && q < w.nq;
+      const int64_t p = (int64_t)row * Ho + min(col, Ho - 1);
+      if (l1) {
+        const gbyte* s = x1_at(rx, cx);
+        const gbyte* dsrc = gin(a.dh2) + p * (S_C * 4);
+        const gbyte* hsrc = gin(a.h2) + p * (S_C * 4);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) v[i][h] = ld<f4>(s + (int64_t)i * P1 * (S_C * 4) + h * 16);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          dv[h] = ld<f4>(dsrc + h * 16);
+          hv[h] = ld<f4>(hsrc + h * 16);
+        }
+        zv = ld<float>(gin(a.dz) + p * 4);
+      } else {
+        unsigned r4;
+        int c4;
+        at(q + 4, r4, c4);
+        const gbyte* s2 = x0_at(rx, cx);
+        const gbyte* s4 = x0_at(r4, c4);
+        const gbyte* dsrc = gin(a.dh1) + p * (S_C * 4);
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+          b5[0][i] = ld<unsigned char>(s2 + (int64_t)i * P);
+          b5[1][i] = ld<unsigned char>(s4 + (int64_t)i * P);
+        }
+        dv[0] = ld<f4>(dsrc);
+        dv[1] = ld<f4>(dsrc + 16);
+      }
+    };
+    load(0);
+    for (int k = 0; k < nst; ++k) {
+      WgBuf& o = buf[k & 1];
+      if (l1) {
+        bool fin = true;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+          for (int c = 0; c < S_C; ++c) {
+            const float xv = v[i][c >> 2][c & 3];
+            o.x[8 * i + c][pt] = xv;
+            fin = fin && isfinite(xv);
+          }
+#pragma unroll
+        for (int c = 0; c < S_C; ++c) o.x[24 + c][pt] = live ? hv[c >> 2][c & 3] : 0.f;
+        o.d[8][pt] = live ? zv : 0.f;
+        const uint64_t bad = __ballot(!fin);
+        if (lane == 0) odd[k & 1][wave - 4] = bad != 0;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+          o.x[i][pt] = (float)b5[0][i] * (1.0f / 255.0f);
+          o.x[5 + i][pt] = (float)b5[1][i] * (1.0f / 255.0f);
+        }
+        if (lane == 0) odd[k & 1][wave - 4] = 0;
+      }
+#pragma unroll
+      for (int c = 0; c < S_C; ++c) o.d[c][pt] = live ? dv[c >> 2][c & 3] : 0.f;
+      if (k + 1 < nst) load(k + 1);
+      __syncthreads();  // stage k ready; the compute waves are done with stage k - 1
+    }
+    return;
+  }
+
+  // ---------------- compute waves: the planes of this lane's elements, and X at
+  // the two columns before the first entry
+  //   layer 1: waves 0..2: filter row i = wave, lane (co, ci); wave 3: lanes
+  //            0..7 layer 2's weights, 8 its bias, 16..23 layer 1's biases, all
+  //            in the chain of the last tap
+  //   layer 0: waves 0, 1: taps 0..2 and 2..4 of filter row i = lane / 8 for
+  //            channel co = lane % 8; lanes 40..47 of wave 1 the biases
+  const int lo = lane & 7, hi8 = lane >> 3;
+  const bool one = l1 ? wave == 3 && lane >= 8 : wave == 1 && lane >= 40;  // X of ones
+  const int xpl = l1 ? (wave < 3 ? 8 * wave + lo : 24 + lo) : (wave & 1) * 5 + min(hi8, 4);
+  const int dpl = l1 ? (wave < 3 ? hi8 : lane < 16 ? 8 : lo) : lo;
+  float c0 = 1.f, c1 = 1.f;
+  {
+    const int q = l1 ? 0 : 2 * (wave & 1);
+    unsigned row;
+    int cc;
+    if (l1 && wave < 3) {
+      at(q, row, cc);
+      c0 = ld<float>(x1_at(row, cc) + (int64_t)wave * P1 * (S_C * 4) + lo * 4);
+      at(q + 1, row, cc);
+      c1 = ld<float>(x1_at(row, cc) + (int64_t)wave * P1 * (S_C * 4) + lo * 4);
+    } else if (!l1) {
+      at(q, row, cc);
+      c0 = (float)ld<unsigned char>(x0_at(row, cc) + (int64_t)min(hi8, 4) * P) * (1.0f / 255.0f);
+      at(q + 1, row, cc);
+      c1 = (float)ld<unsigned char>(x0_at(row, cc) + (int64_t)min(hi8, 4) * P) * (1.0f / 255.0f);
+    }
+  }
+  float acc[3] = {0.f, 0.f, 0.f};
+  for (int k = 0; k < nst; ++k) {
+    __syncthreads();
+    if (!l1 && wave > 1) continue;
+    const WgBuf& o = buf[k & 1];
+    const float* pd = o.d[dpl];
+    const float* px = one ? ones : o.x[xpl];
+    const int n = min(WQ, w.nq - k * WQ);
+    const int* od = odd[k & 1];
+    if (od[0] | od[1] | od[2] | od[3]) {
+      // an h1 of this stage is not finite (0 times it is NaN): only positions, one by one
+      for (int q = 0; q < n; ++q) {
+        const float x = px[q], d = pd[q];
+        if ((k * WQ + q + w.x0) % Hi < Ho) {
+          acc[0] = fmaf(d, c0, acc[0]);
+          acc[1] = fmaf(d, c1, acc[1]);
+          acc[2] = fmaf(d, x, acc[2]);
+        }
+        c0 = c1;
+        c1 = x;
+      }
+      if (n < WQ) break;
+      continue;
+    }
+#pragma unroll 1
+    for (int q = 0; q < n; q += 32) {  // entries past n: dY is zero
+      f4 d[8], x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        d[e] = *reinterpret_cast<const f4*>(pd + q + 4 * e);
+        x[e] = *reinterpret_cast<const f4*>(px + q + 4 * e);
+      }
+#pragma unroll
+      for (int e = 0; e < 32; ++e) {
+        const float xv = x[e >> 2][e & 3], dv = d[e >> 2][e & 3];
+        acc[0] = fmaf(dv, c0, acc[0]);
+        acc[1] = fmaf(dv, c1, acc[1]);
+        acc[2] = fmaf(dv, xv, acc[2]);
+        c0 = c1;
+        c1 = xv;
+      }
+    }
+  }
+  if (l1) {
+    float* q1 = a.part[1] + (int64_t)chunk * (S_C * 72 + S_C);
+    float* q2 = a.part[2] + (int64_t)chunk * 9;
+    if (wave < 3) {
+#pragma unroll
+      for (int j = 0; j < 3; ++j) q1[(hi8 * 8 + lo) * 9 + wave * 3 + j] = acc[j];
+    } else if (lane < 9) {
+      q2[lane] = acc[2];
+    } else if (lane >= 16 && lane < 24) {
+      q1[S_C * 72 + lo] = acc[2];
+    }
+  } else {
+    float* q0 = a.part[0] + (int64_t)chunk * 208;
+    if (lane < 40) {
+      if (wave == 0) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) q0[lo * 25 + hi8 * 5 + j] = acc[j];
+      } else if (wave == 1) {
+#pragma unroll
+        for (int j = 1; j < 3; ++j) q0[lo * 25 + hi8 * 5 + 2 + j] = acc[j];
+      }
+    } else if (wave == 1 && lane < 48) {
+      q0[200 + lo] = acc[2];
+    }
   }
 }
 
@@ -458,18 +776,42 @@ struct ReduceArgs {
   float c1, c2;  // 1 - b1^t, 1 - b2^t
 };
 
-__device__ __forceinline__ void refresh_working(float* ww, const float* master, int e, int bf16) {
-  float w = master[e];
+__device__ __forceinline__ void refresh_working(float* ww, float w, int e, int bf16) {
   if (e < OFF_B1) w = w * (1.0f / 255.0f);  // the kernels read raw uint8 input
   if (bf16 && (e < OFF_B1 || (e >= OFF_W2 && e < OFF_B2))) w = s_bf16(w);
   ww[e] = w;
+  if (e < OFF_B1) {
+    ww[OFF_W1T + (e % 25) * 8 + e / 25] = w;
+  } else if (e >= OFF_W2 && e < OFF_B2) {
+    const int r = e - OFF_W2, co = r / 72, ci = (r / 9) % 8, tap = r % 9;
+    ww[OFF_W2T + (tap * 8 + ci) * 8 + co] = w;
+    ww[OFF_W2U + (tap * 8 + co) * 8 + ci] = w;
+  }
+}
+
+// FP64 sum over the block's 1024 threads in a fixed order: butterflies inside
+// each wave, then over the 16 waves' sums. Every thread receives it.
+__device__ __forceinline__ double block_sum(double v, double* lds16) {
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) v += __shfl_xor(v, s);
+  if ((threadIdx.x & 63) == 0) lds16[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double t = 0.0;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) t += lds16[k];
+  return t;
 }
 
 // One block of 1024 threads: fixed-order reduction of the chunk partials into
-// the gradient, FP64 sums of the loss and of g^2, and the Adam update.
+// the gradient, FP64 sums of the loss and of g^2, and the Adam update. One block
+// on one CU: its time is latency, so every load is issued ahead of the sums.
 __global__ __launch_bounds__(1024) void st_reduce_adam(ReduceArgs a) {
-  __shared__ double red[1024];
+  __shared__ double red[2][16];
   const int e = threadIdx.x;
+  const int ec = min(e, S_NP - 1);
+  const float w0 = a.master[ec], m0 = a.m[ec], v0 = a.v[ec];
+  double l = 0.0;
+  for (int i = e; i < a.nloss; i += 1024) l += a.loss_part[i];
   float g = 0.f;
   if (e < S_NP) {
     int layer, local, ne;
@@ -486,44 +828,39 @@ __global__ __launch_bounds__(1024) void st_reduce_adam(ReduceArgs a) {
       local = e - OFF_WH;
       ne = S_NP - OFF_WH;
     }
-    for (int c = 0; c < a.nchunk[layer]; ++c) g += a.part[layer][(int64_t)c * ne + local];
+    // chunk after chunk, 64 loads in flight
+    const float* src = a.part[layer] + local;
+    const int nch = a.nchunk[layer];
+    for (int c = 0; c < nch; c += 64) {
+      float v[64];
+#pragma unroll
+      for (int k = 0; k < 64; ++k) v[k] = src[(int64_t)min(c + k, nch - 1) * ne];
+#pragma unroll
+      for (int k = 0; k < 64; ++k) g = c + k < nch ? g + v[k] : g;
+    }
     if (a.grad_out) a.grad_out[e] = g;
   }
-  red[e] = (double)g * (double)g;
-  __syncthreads();
-  for (int s = 512; s > 0; s >>= 1) {
-    if (e < s) red[e] += red[e + s];
-    __syncthreads();
-  }
-  const double g2 = red[0];
-  __syncthreads();
-  // loss: fixed-order sum of the per-block FP64 partials
-  double l = 0.0;
-  for (int i = e; i < a.nloss; i += 1024) l += a.loss_part[i];
-  red[e] = l;
-  __syncthreads();
-  for (int s = 512; s > 0; s >>= 1) {
-    if (e < s) red[e] += red[e + s];
-    __syncthreads();
-  }
-  if (e == 0) {
-    if (a.loss_out) *a.loss_out = red[0] * a.invN;
-    if (a.gnorm_out) *a.gnorm_out = sqrt(g2);
-  }
   if (e < S_NP && a.do_update) {
-    const float m = a.b1 * a.m[e] + (1.0f - a.b1) * g;
-    const float v = a.b2 * a.v[e] + (1.0f - a.b2) * g * g;
+    const float m = fmaf(g, 1.0f - a.b1, a.b1 * m0);
+    const float v = fmaf(a.b2, v0, (1.0f - a.b2) * g * g);
     a.m[e] = m;
     a.v[e] = v;
     const float mh = m / a.c1, vh = v / a.c2;
-    a.master[e] = a.master[e] - a.lr * mh / (sqrtf(vh) + a.eps);
-    refresh_working(a.ww, a.master, e, a.bf16);
+    const float w = w0 - a.lr * mh / (sqrtf(vh) + a.eps);
+    a.master[e] = w;
+    refresh_working(a.ww, w, e, a.bf16);
+  }
+  const double g2 = block_sum((double)g * (double)g, red[0]);
+  const double ls = block_sum(l, red[1]);
+  if (e == 0) {
+    if (a.loss_out) *a.loss_out = ls * a.invN;
+    if (a.gnorm_out) *a.gnorm_out = sqrt(g2);
   }
 }
 
 __global__ void st_refresh(float* ww, const float* master, int bf16) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < S_NP) refresh_working(ww, master, e, bf16);
+  if (e < S_NP) refresh_working(ww, master[e], e, bf16);
 }
 
 // ------------------------------------------------------------------ fallback decisions
@@ -652,9 +989,9 @@ static int grad_impl(Student* s, const uint8_t* patches, const float* teacher, i
                      double* loss_out, double* gnorm_out, const cnn_adam* hp, hipStream_t st) {
   const int P1 = P - 4, P2 = P - 6;
   const int64_t n1 = (int64_t)B * P1 * P1, n2 = (int64_t)B * P2 * P2;
-  const int chunk = 2048;
-  const int nc0 = (int)((n1 + chunk - 1) / chunk), nc1 = (int)((n2 + chunk - 1) / chunk), nc2 = nc1;
-  const int nloss = (int)((n2 + 255) / 256);
+  const int nc0 = (int)((n1 + kChunk - 1) / kChunk), nc1 = (int)((n2 + kChunk - 1) / kChunk), nc2 = nc1;
+  const int tiles_y = (P1 + FY - 1) / FY, tiles_x = (P1 + FX - 1) / FX;
+  const int nloss = B * tiles_y * tiles_x;  // one loss partial per forward block
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t sz_h1 = al(n1 * S_C * 4), sz_h2 = al(n2 * S_C * 4), sz_dz = al(n2 * 4);
   const size_t sz_p0 = al((size_t)nc0 * 208 * 4), sz_p1 = al((size_t)nc1 * 584 * 4), sz_p2 = al((size_t)nc2 * 9 * 4);
@@ -682,14 +1019,23 @@ static int grad_impl(Student* s, const uint8_t* patches, const float* teacher, i
   double* lp = reinterpret_cast<double*>(w);
   const int bf = s->prec == CNN_PREC_BF16;
   const double invN = 1.0 / (double)n2;
-  auto blocks = [](int64_t n) { return (int)std::min<int64_t>((n + 255) / 256, 65535); };
-  hipLaunchKernelGGL(st_conv1, dim3(blocks(n1)), dim3(256), 0, st, patches, B, P, s->ww, h1, bf);
-  hipLaunchKernelGGL(st_conv2_loss, dim3(nloss), dim3(256), 0, st, h1, B, P, s->ww, teacher, h2, dz, dh2, lp, invN, bf);
-  hipLaunchKernelGGL(st_dh1, dim3(blocks(n1)), dim3(256), 0, st, dh2, h1, B, P, s->ww, dh1, bf);
-  // one thread per gradient element of a chunk (8 x 25 + 8, 8 x 72 + 8, 8 + 1)
-  hipLaunchKernelGGL(st_wgrad<0>, dim3(nc0), dim3(256), 0, st, dh1, (const void*)patches, B, P, chunk, p0);
-  hipLaunchKernelGGL(st_wgrad<1>, dim3(nc1), dim3(640), 0, st, dh2, (const void*)h1, B, P, chunk, p1);
-  hipLaunchKernelGGL(st_wgrad<2>, dim3(nc2), dim3(64), 0, st, dz, (const void*)h2, B, P, chunk, p2);
+  hipLaunchKernelGGL(st_forward, dim3(nloss), dim3(FT), 0, st, patches, P, tiles_y, tiles_x, s->ww, teacher, h1, h2, dz,
+                     dh2, dh1, lp, invN, bf);
+  WgradArgs wa;
+  wa.dh1 = dh1;
+  wa.h1 = h1;
+  wa.dh2 = dh2;
+  wa.h2 = h2;
+  wa.dz = dz;
+  wa.patches = patches;
+  wa.part[0] = p0;
+  wa.part[1] = p1;
+  wa.part[2] = p2;
+  wa.n1 = n1;
+  wa.n2 = n2;
+  wa.P = P;
+  wa.nc1 = nc1;
+  hipLaunchKernelGGL(st_wgrad, dim3(nc1 + nc0), dim3(512), 0, st, wa);
   ReduceArgs a;
   std::memset(&a, 0, sizeof(a));
   a.part[0] = p0;
@@ -742,13 +1088,15 @@ extern "C" int student_create(const double* w_init, int64_t n, int32_t precision
   std::vector<float> w(S_NP);
   for (int i = 0; i < S_NP; ++i) w[i] = (float)w_init[i];
   hipError_t e;
-  if ((e = hipMalloc(&s->master, 4 * S_NP * sizeof(float))) != hipSuccess) {
+  // master, m, v, then the working weights at a multiple of 32 bytes
+  constexpr size_t ww_at = (3 * S_NP + 7) / 8 * 8;
+  if ((e = hipMalloc(&s->master, (ww_at + S_NWW) * sizeof(float))) != hipSuccess) {
     delete s;
     return fail(CNN_ENOMEM, "student_create: hipMalloc");
   }
   s->m = s->master + S_NP;
   s->v = s->m + S_NP;
-  s->ww = s->v + S_NP;
+  s->ww = s->master + ww_at;
   e = hipMemcpy(s->master, w.data(), S_NP * sizeof(float), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemset(s->m, 0, 2 * S_NP * sizeof(float));
   if (e == hipSuccess) {
@@ -1057,7 +1405,7 @@ extern "C" int student_gather(const cnn_patch_src* src, int32_t batch, int32_t p
     a.src[b].map_rs = Wm;
   }
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  const int gx = std::max(1, std::min(64, (patch * patch + 4095) / 4096));
+  const int gx = std::max(1, std::min(64, (patch * patch + 1023) / 1024));
   hipLaunchKernelGGL(st_gather, dim3(gx, batch), dim3(256), 0, st, a, patches_out, teacher_out);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "student_gather");
