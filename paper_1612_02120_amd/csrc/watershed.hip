@@ -13,8 +13,8 @@
 // component's tree. Roots are fixed points: component minima and non-seed
 // local minima.
 //   ws_init   one pass: a seed points to the first seed of its run along x
-//             (the run's least index; a ballot scan per row), any other
-//             voxel to next(v). The x-links of the seed graph are then made.
+//             (the run's least index), any other voxel to next(v). The x-links
+//             of the seed graph are then made.
 //   ws_union  one pass over the seeds: runs adjacent along y or z are united
 //             by a lock-free union-find (the structure of ECL-CC): find both
 //             roots, hook the larger root under the smaller with a
@@ -24,12 +24,24 @@
 //             where they do (the pair one column left, when both are seeds,
 //             joins the same two runs). A seed's parent index only
 //             decreases, so every component ends rooted at its least index.
-//   ws_label  every voxel finds its root (a component minimum or a local
-//             minimum), halving the path as it goes, and takes root + 1.
+//   ws_flat   every run's first seed finds its component's root r, halving the
+//             path as it goes, and takes ~r, which ends a walk.
+//   ws_label  every voxel follows its parents to a run's ~r (a seed in two
+//             steps, a non-seed after its descent) or to a local minimum r, and
+//             takes r + 1. Nothing changes the forest any more.
 // Path halving points a node at its grandparent, an ancestor in the same
 // tree, so concurrent finds stay valid; it never writes a root.
+//
+// Every kernel gives a row to a wave, four consecutive columns to a lane, as one
+// 16-byte access where rows and pointers allow it. On a 32 x 1012^2 membrane map
+// with seeds below 0.05 (44 % of the voxels): ws_init 90 us, ws_union 220-234, ws_flat
+// 55, ws_label 227; 1.57 ms in all when a row was a workgroup, one column a
+// thread, and ws_label halved paths from every voxel (ws_init 228, ws_union 392,
+// ws_label 944 us). ws_init moves 0.26 GB, the rate of a large copy; the other
+// passes are chains of dependent loads and, in ws_union, 1.4 M compare-and-swaps.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 
 #include "../../include/emcnn.h"
@@ -43,72 +55,129 @@ struct Vol3 {
   int64_t N;
 };
 
-__device__ __forceinline__ float wp(const float* p, int64_t v) { return ld<float>(gin(p) + v * 4); }
+// Parents while other threads may be changing them, read through the caches: an
+// older value is an ancestor all the same, and a root that has been hooked since
+// shows in the compare-and-swap, whose answer the walk goes on from. (Past the
+// caches, the root of a large component is one address that every find of every
+// CU waits for: ws_union 268 us there, 217-234 here, and 259 against 111-128 on a
+// volume of 2 M voxels in one component.)
 __device__ __forceinline__ int32_t wa(const int32_t* a, int64_t v) {
-  return __atomic_load_n(a + v, __ATOMIC_RELAXED);
+  return __hip_atomic_load(a + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Work split: one row (z, y) of W voxels per block iteration, x over the
-// threads in chunks of 256 columns; indices fit in 32 bits (Z H W < 2^31 - 1).
+typedef int32_t i4 __attribute__((ext_vector_type(4)));
+
+// Four values at v .. v + 3 of a row that holds n of them (the others read as 0).
+// VEC: rows and pointers are 16-byte aligned, so all four are there or none.
+template <bool VEC>
+__device__ __forceinline__ f4 row4(const float* p, int v, int n) {
+  if constexpr (VEC) {
+    return n > 0 ? ld<f4>(gin(p) + (int64_t)v * 4) : f4{0.f, 0.f, 0.f, 0.f};
+  } else {
+    f4 r;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r[k] = k < n ? ld<float>(gin(p) + ((int64_t)v + k) * 4) : 0.f;
+    return r;
+  }
+}
+
+// Bits k < n with q[k] < t.
+__device__ __forceinline__ unsigned below4(f4 q, int n, float t) {
+  unsigned m = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) m |= (k < n && q[k] < t) ? 1u << k : 0u;
+  return m;
+}
+
+// body(row) for the rows of this wave: groups of four rows, one per wave of a
+// workgroup, dealt out so that consecutive groups run on the same XCD (workgroup
+// b on XCD b % 8) and its L2 serves the rows that neighbours share.
+template <class Body>
+__device__ __forceinline__ void wave_rows(unsigned nrow, Body body) {
+  const unsigned per = ((nrow + 3) / 4 + 7) / 8;  // groups per XCD (nrow < 2^31)
+  for (unsigned k = blockIdx.x >> 3; k < per; k += gridDim.x >> 3) {
+    const unsigned row = ((blockIdx.x & 7) * per + k) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (row < nrow) body((int)row);
+  }
+}
+
+// Columns per step of a wave.
+constexpr int WC = 256;
+
+// The last non-seed column before this lane's columns x .. x + 3 (m: which of
+// them are seeds); carry: the last one before the wave's step, updated.
+__device__ __forceinline__ int break_before(unsigned m, int x, int lane, int& carry) {
+  // the last non-seed column of this lane's (columns past the row count as non-seeds)
+  const int last = m == 15u ? -1 : x + 31 - __builtin_clz(~m & 15u);
+  const uint64_t brk = __ballot(m != 15u);
+  const uint64_t before = brk & ((1ull << lane) - 1);
+  const int from = __shfl(last, before ? 63 - __builtin_clzll(before) : 0);
+  const int lb = before ? from : carry;
+  if (brk) carry = __shfl(last, 63 - __builtin_clzll(brk));
+  return lb;
+}
+
+template <bool VEC>
 __global__ __launch_bounds__(256) void ws_init(const float* __restrict__ p, Vol3 g, float t, int32_t* __restrict__ a) {
-  __shared__ int wbreak[4];  // per wave: its last non-seed column in the chunk, or -1
-  const int HW = g.H * g.W;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int row = blockIdx.x; row < g.Z * g.H; row += gridDim.x) {
+  const int HW = g.H * g.W, lane = threadIdx.x & 63;
+  wave_rows((unsigned)(g.Z * g.H), [&](int row) __attribute__((always_inline)) {
     const int z = row / g.H, y = row - z * g.H, base = row * g.W;
-    int carry = -1;  // the last non-seed column before the chunk
-    for (int x0 = 0; x0 < g.W; x0 += 256) {  // uniform over the block: every thread takes every chunk
-      const int x = x0 + threadIdx.x;
-      const int v = base + x;
-      const bool in = x < g.W;
-      const float pv = in ? wp(p, v) : 0.f;
-      const bool seed = in && pv < t;
-      // lb: the last non-seed column at or before x (columns past the row count as non-seeds)
-      const uint64_t brk = __ballot(!seed);
-      const uint64_t upto = brk & ((2ull << lane) - 1);  // lanes 0 .. lane (all 64 bits for lane 63)
-      const int wx = x0 + wv * 64 + 63;                   // the wave's last column
-      int lb = upto ? wx - __builtin_clzll(upto) : -1;
-      if (lane == 0) wbreak[wv] = brk ? wx - __builtin_clzll(brk) : -1;
-      __syncthreads();
-      if (lb < 0) {
-        lb = carry;
-        for (int k = 0; k < wv; ++k) lb = max(lb, wbreak[k]);
-      }
+    int carry = -1;  // the last non-seed column before the step
+    for (int x0 = 0; x0 < g.W; x0 += WC) {
+      const int x = x0 + 4 * lane, v = base + x, n = min(max(g.W - x, 0), 4);
+      const f4 q = row4<VEC>(p, v, n);
+      const f4 zm = row4<VEC>(p, z > 0 ? v - HW : v, n), zp = row4<VEC>(p, z < g.Z - 1 ? v + HW : v, n);
+      const f4 ym = row4<VEC>(p, y > 0 ? v - g.W : v, n), yp = row4<VEC>(p, y < g.H - 1 ? v + g.W : v, n);
+      float left = __shfl_up(q[3], 1), right = __shfl_down(q[0], 1);
+      if (lane == 0 && x > 0) left = ld<float>(gin(p) + ((int64_t)v - 1) * 4);
+      if (lane == 63 && x + 4 < g.W) right = ld<float>(gin(p) + ((int64_t)v + 4) * 4);
+      const unsigned m = below4(q, n, t);
+      int lb = break_before(m, x, lane, carry);
+      i4 out;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) carry = max(carry, wbreak[k]);
-      __syncthreads();  // wbreak is rewritten for the next chunk
-      if (!in) continue;
-      if (seed) {
-        a[v] = base + lb + 1;  // the run's first seed
-        continue;
-      }
-      int best = v;
-      float pb = pv;
-      // candidates in ascending index order: a later candidate wins only if strictly lower
-      const int cand[6] = {z > 0 ? v - HW : -1, y > 0 ? v - g.W : -1, x > 0 ? v - 1 : -1,
-                           x < g.W - 1 ? v + 1 : -1, y < g.H - 1 ? v + g.W : -1, z < g.Z - 1 ? v + HW : -1};
-#pragma unroll
-      for (int k = 0; k < 6; ++k) {
-        const int u = cand[k];
-        if (u < 0) continue;
-        const float pu = wp(p, u);
-        if (pu < pb || (pu == pb && u < best)) {
-          pb = pu;
-          best = u;
+      for (int k = 0; k < 4; ++k) {
+        if (m >> k & 1) {
+          out[k] = base + lb + 1;  // the run's first seed
+        } else {
+          lb = x + k;
+          int best = v + k;
+          float pb = q[k];
+          // candidates in ascending index order: a later one wins only if strictly lower
+          auto cand = [&](bool there, float pu, int u) __attribute__((always_inline)) {
+            const bool take = there && (pu < pb || (pu == pb && u < best));
+            pb = take ? pu : pb;
+            best = take ? u : best;
+          };
+          cand(z > 0, zm[k], v + k - HW);
+          cand(y > 0, ym[k], v + k - g.W);
+          cand(x + k > 0, k > 0 ? q[k > 0 ? k - 1 : 0] : left, v + k - 1);
+          cand(x + k < g.W - 1, k < 3 ? q[k < 3 ? k + 1 : 3] : right, v + k + 1);
+          cand(y < g.H - 1, yp[k], v + k + g.W);
+          cand(z < g.Z - 1, zp[k], v + k + HW);
+          out[k] = best;
         }
       }
-      a[v] = best;
+      if constexpr (VEC) {
+        if (n > 0) st<i4>(gout(a) + (int64_t)v * 4, out);
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (k < n) st<int32_t>(gout(a) + ((int64_t)v + k) * 4, out[k]);
+      }
     }
-  }
+  });
 }
 
 // Root of r with path halving (any node may be passed; roots are fixed points).
 __device__ __forceinline__ int32_t ws_find(int32_t* a, int32_t r) {
   int32_t par = wa(a, r);
   while (par != r) {
+    if (par < 0) return ~par;  // ws_flat has written the root here
     const int32_t gp = wa(a, par);
     if (gp == par) return par;
-    __atomic_store_n(a + r, gp, __ATOMIC_RELAXED);  // r is not a root: an ancestor is a valid parent
+    if (gp < 0) return ~gp;
+    // r is not a root: an ancestor is a valid parent
+    __hip_atomic_store(a + r, gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     r = gp;
     par = wa(a, r);
   }
@@ -121,35 +190,153 @@ __device__ __forceinline__ void ws_unite(int32_t* a, int32_t u, int32_t v) {
     const int32_t hi = ru > rv ? ru : rv, lo = ru < rv ? ru : rv;
     const int32_t old = atomicCAS(a + hi, hi, lo);
     if (old == hi) return;  // hooked while hi was still a root
-    // hi was hooked meanwhile: continue from the current roots
-    ru = ws_find(a, hi);
-    rv = ws_find(a, lo);
+    // hi had been hooked (under old < hi): continue from there
+    ru = ws_find(a, old);
+    rv = lo;
   }
 }
 
-__global__ __launch_bounds__(256) void ws_union(const float* __restrict__ p, Vol3 g, float t, int32_t* a) {
-  const int HW = g.H * g.W;
-  for (int row = blockIdx.x; row < g.Z * g.H; row += gridDim.x) {
-    const int z = row / g.H, y = row - z * g.H, base = row * g.W;
-    for (int x = threadIdx.x; x < g.W; x += 256) {
-      const int v = base + x;
-      if (!(wp(p, v) < t)) continue;
-      const bool left = x > 0 && wp(p, v - 1) < t;  // v is not its run's first seed
-      const int fwd[2] = {y < g.H - 1 ? v + g.W : -1, z < g.Z - 1 ? v + HW : -1};
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int u = fwd[k];
-        if (u < 0 || !(wp(p, u) < t)) continue;
-        if (left && wp(p, u - 1) < t) continue;  // the pair one column left joins the same two runs
-        ws_unite(a, v, u);
-      }
+// Bits of m whose left neighbour's bit is clear: the first columns of m's runs.
+// prev: the bit left of the wave's step (updated to its last one).
+__device__ __forceinline__ unsigned run_starts(unsigned m, int lane, unsigned& prev) {
+  unsigned left = (unsigned)__shfl_up((int)(m >> 3), 1);
+  if (lane == 0) left = prev;
+  prev = (unsigned)__shfl((int)(m >> 3), 63);
+  return m & ~((m << 1) | left);
+}
+
+// Finds are chains of dependent loads, and the columns that start one are sparse
+// (a few per wave and step): done where they are met, one lane in ten works while
+// the wave waits. So a wave queues them in LDS and works them off 64 at a time
+// (ws_flat 59 -> 55 us; ws_union, which waits for its atomics, the same).
+constexpr int WQCAP = 64 + 2 * WC;
+struct WaveQueue {
+  int* q;
+  int n = 0;  // uniform
+  int lane;
+  // queue e of the lanes with `there` (at most 64 at a time)
+  __device__ __forceinline__ void push(bool there, int e) {
+    const uint64_t b = __ballot(there);
+    if (there) q[n + __builtin_popcountll(b & ((1ull << lane) - 1))] = e;
+    n += __builtin_popcountll(b);
+  }
+  // work(e) on the last 64 entries while there are that many (all: on every entry)
+  template <class Work>
+  __device__ __forceinline__ void drain(bool all, Work work) {
+    while (n >= 64 || (all && n > 0)) {
+      const int k = min(n, 64);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const int e = lane < k ? q[n - k + lane] : 0;
+      if (lane < k) work(e);
+      n -= k;
+      __builtin_amdgcn_wave_barrier();
     }
   }
+};
+
+template <bool VEC>
+__global__ __launch_bounds__(256) void ws_union(const float* __restrict__ p, Vol3 g, float t, int32_t* a) {
+  __shared__ int queue[4][WQCAP];
+  const int HW = g.H * g.W, lane = threadIdx.x & 63;
+  WaveQueue wq{queue[threadIdx.x >> 6], 0, lane};
+  // entry v: unite v with the voxel below it; ~v: with the one in the next slice
+  auto work = [&](int e) __attribute__((always_inline)) {
+    const int v = e < 0 ? ~e : e;
+    ws_unite(a, v, e < 0 ? v + HW : v + g.W);
+  };
+  wave_rows((unsigned)(g.Z * g.H), [&](int row) __attribute__((always_inline)) {
+    const int z = row / g.H, y = row - z * g.H, base = row * g.W;
+    unsigned prevy = 0, prevz = 0;
+    for (int x0 = 0; x0 < g.W; x0 += WC) {
+      const int x = x0 + 4 * lane, v = base + x, n = min(max(g.W - x, 0), 4);
+      const unsigned m = below4(row4<VEC>(p, v, n), n, t);
+      const unsigned my = y < g.H - 1 ? below4(row4<VEC>(p, v + g.W, n), n, t) : 0u;
+      const unsigned mz = z < g.Z - 1 ? below4(row4<VEC>(p, v + HW, n), n, t) : 0u;
+      // first columns where the run of this row touches one of the next row / slice
+      const unsigned sy = run_starts(m & my, lane, prevy), sz = run_starts(m & mz, lane, prevz);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        wq.push(sy >> k & 1, v + k);
+        wq.push(sz >> k & 1, ~(v + k));
+      }
+      wq.drain(false, work);
+    }
+  });
+  wq.drain(true, work);
 }
 
-__global__ __launch_bounds__(256) void ws_label(Vol3 g, int32_t* a, int32_t* __restrict__ out) {
-  const int n = (int)g.N;
-  for (int v = blockIdx.x * 256 + threadIdx.x; v < n; v += gridDim.x * 256) out[v] = ws_find(a, v) + 1;
+template <bool VEC>
+__global__ __launch_bounds__(256) void ws_flat(const float* __restrict__ p, Vol3 g, float t, int32_t* a) {
+  __shared__ int queue[4][WQCAP];
+  const int lane = threadIdx.x & 63;
+  WaveQueue wq{queue[threadIdx.x >> 6], 0, lane};
+  auto work = [&](int v) __attribute__((always_inline)) {
+    const int32_t r = ws_find(a, v);
+    __hip_atomic_store(a + v, ~r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  wave_rows((unsigned)(g.Z * g.H), [&](int row) __attribute__((always_inline)) {
+    const int base = row * g.W;
+    unsigned prev = 0;
+    for (int x0 = 0; x0 < g.W; x0 += WC) {
+      const int x = x0 + 4 * lane, v = base + x, n = min(max(g.W - x, 0), 4);
+      const unsigned s = run_starts(below4(row4<VEC>(p, v, n), n, t), lane, prev);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) wq.push(s >> k & 1, v + k);
+      wq.drain(false, work);
+    }
+  });
+  wq.drain(true, work);
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(256) void ws_label(Vol3 g, const int32_t* __restrict__ a, int32_t* out) {
+  const gbyte* ab = gin(a);
+  const int64_t v = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (v >= g.N) return;
+  i4 r, par;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) r[k] = (int32_t)(VEC ? v + k : min(v + k, g.N - 1));
+  if constexpr (VEC) {
+    par = ld<i4>(ab + v * 4);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) par[k] = ld<int32_t>(ab + (int64_t)r[k] * 4);
+  }
+  // the four walks step together, so that their loads overlap
+  auto open = [&](int k) __attribute__((always_inline)) { return par[k] >= 0 && par[k] != r[k]; };
+  while (open(0) || open(1) || open(2) || open(3)) {
+    i4 nx;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) nx[k] = open(k) ? ld<int32_t>(ab + (int64_t)par[k] * 4) : par[k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      r[k] = open(k) ? par[k] : r[k];
+      par[k] = nx[k];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) r[k] = (par[k] < 0 ? ~par[k] : r[k]) + 1;
+  if constexpr (VEC) {
+    st<i4>(gout(out) + v * 4, r);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (v + k < g.N) st<int32_t>(gout(out) + (v + k) * 4, r[k]);
+  }
+}
+
+template <bool VEC>
+static hipError_t ws_run(const float* p, const Vol3& g, float t, int32_t* labels, int32_t* work, hipStream_t st) {
+  const int64_t groups = ((int64_t)g.Z * g.H + 3) / 4;  // of four rows
+  // multiples of 8 (wave_rows); the kernels with a queue run persistent waves, which keep theirs filled
+  const dim3 rows((unsigned)std::min<int64_t>((groups + 7) / 8 * 8, 1 << 20)), block(256);
+  const dim3 few(std::min(rows.x, 2048u));
+  hipLaunchKernelGGL(ws_init<VEC>, rows, block, 0, st, p, g, t, work);
+  hipLaunchKernelGGL(ws_union<VEC>, few, block, 0, st, p, g, t, work);
+  hipLaunchKernelGGL(ws_flat<VEC>, few, block, 0, st, p, g, t, work);
+  hipLaunchKernelGGL(ws_label<VEC>, dim3((unsigned)((g.N + 1023) / 1024)), block, 0, st, g, work, labels);
+  return hipGetLastError();
 }
 
 }  // namespace emcnn
@@ -166,14 +353,10 @@ extern "C" int watershed_3d(const float* prob, const int64_t dims[3], float seed
   if (seed_threshold != seed_threshold) return fail(CNN_EINVAL, "watershed_3d: NaN threshold");
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   Vol3 g{(int)Z, (int)H, (int)W, Z * H * W};
-  const int grid = (int)std::min<int64_t>((g.N + 255) / 256, 2048 * 8);
-  const int rows = (int)std::min<int64_t>(Z * H, 2048 * 8);  // row-per-block kernels
-  hipError_t e;
-  hipLaunchKernelGGL(ws_init, dim3(rows), dim3(256), 0, st, prob, g, seed_threshold, work);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "watershed_3d: init");
-  hipLaunchKernelGGL(ws_union, dim3(rows), dim3(256), 0, st, prob, g, seed_threshold, work);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "watershed_3d: union");
-  hipLaunchKernelGGL(ws_label, dim3(grid), dim3(256), 0, st, g, work, labels_out);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "watershed_3d: label");
+  // 16-byte accesses where every row starts at one
+  const bool vec = W % 4 == 0 && ((uintptr_t)prob | (uintptr_t)work | (uintptr_t)labels_out) % 16 == 0;
+  const hipError_t e = vec ? ws_run<true>(prob, g, seed_threshold, labels_out, work, st)
+                           : ws_run<false>(prob, g, seed_threshold, labels_out, work, st);
+  if (e != hipSuccess) return hip_fail(e, "watershed_3d");
   return CNN_OK;
 }

@@ -79,3 +79,18 @@ def test_watershed_on_net_b_map_full_size(emcnn):
     got = lab.cpu().numpy()
     print("net B map %s, t %.4f: %d basins" % (P.shape, t, len(np.unique(ref))))
     assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("W", [1, 3, 4, 252, 255, 256, 257, 508, 512])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_watershed_row_ends_and_alignment(emcnn, W, offset):
+    """Rows that end inside a lane's four columns or a wave's 256, and maps that do
+    not start at 16 bytes (read element by element), in one large component."""
+    rng = np.random.default_rng(W)
+    p = np.where(rng.uniform(0, 1, (3, 21, W)) < 0.7, 0.05, rng.uniform(0, 1, (3, 21, W))).astype(np.float32)
+    flat = torch.empty(p.size + offset, dtype=torch.float32, device="cuda")
+    view = flat[offset:].view(p.shape)
+    view.copy_(torch.from_numpy(p))
+    lab = emcnn.watershed_3d(view, 0.1)
+    torch.cuda.synchronize()
+    assert np.array_equal(lab.cpu().numpy(), oracle.watershed(p, 0.1))
