@@ -54,6 +54,20 @@ struct JobSet {
   LayerJob single;
 };
 
+// Range of one call's real-valued input maps, found on the device before the
+// layers run (nets on more than one input channel). The scales of split convs
+// (conv_split) assume maps in [-1, 1]; maps in [-2^k, 2^k] scale every bound by
+// at most 2^k, so the operands take 2^-k more and the sums 2^k. ok / bad gate the
+// split kernels and the FP32 ones that run instead where the maps are too large
+// (k > kMapsRangeMax) or not finite.
+struct MapsRange {
+  float down, up;  // 2^-k, 2^k
+  int32_t ok, bad;
+  uint32_t top;  // running maximum of the maps' magnitudes (float bits); 0 between calls
+  uint32_t pad_[3];
+};
+constexpr int kMapsRangeMax = 20;
+
 struct ConvParams {
   const void* wpack;     // packed B fragments (layout decided by the kernel variant)
   const float* bias;     // [cout]
@@ -66,6 +80,7 @@ struct ConvParams {
   const float* b1;       // [cin] first-layer bias
   float w1_inv_scale;    // FP8: first-layer output codes e4m3(v * w1_inv_scale)
   float pad_;
+  const MapsRange* range;  // split convs of nets on real-valued maps (nullptr: none)
 };
 
 struct FirstParams {

@@ -51,8 +51,12 @@ template <int CIN, int COUT, int KS, int KIND, int TY, int TX, int NCW, int NPW,
 struct CfgSplit {
   static constexpr int KSZ = KS, CB = CB_, SS = SS_;
   static constexpr int NMEM = KIND == SK_GROUP ? 4 : 1;
-  static_assert(CIN % CB == 0 && CB % 8 == 0, "whole 16-byte chunks of f16");
-  static constexpr int NCB = CIN / CB;
+  static_assert(CIN % 4 == 0 && CB % 8 == 0, "whole 16-byte chunks, stored and of f16");
+  // channels past CIN of the last block are zeros (12 input maps: 16 channels, a
+  // quarter of the products padding, still a third of the FP32 MFMA's time)
+  static constexpr int NCB = (CIN + CB - 1) / CB;
+  static constexpr int CINP = NCB * CB;
+  static constexpr int NCIN = CIN;
   static constexpr int NCHB = CB / 8;  // 16-byte chunks per pixel in each half
   static constexpr int NCHK = KS * KS * NCHB;
   static constexpr int NGS = (NCHK + 3) / 4;         // group-steps of a stage
@@ -80,7 +84,7 @@ struct CfgSplit {
   static_assert(NMEM == 1 || (TX == 16 && TY % WROWS == 0), "a consumer wave's rows lie in one member's tile");
   static constexpr int THREADS = (NCW + NPW) * 64;
   static_assert(THREADS <= 1024, "workgroup size limit");
-  static constexpr size_t PACKB = (size_t)NCB * NSL * SLB;  // fragments; then iscale[CIN], oscale[COUT]
+  static constexpr size_t PACKB = (size_t)NCB * NSL * SLB;  // fragments; then iscale[CINP], oscale[COUT]
 };
 
 // Four scaled FP32 values to f16 hi and lo halves (8 bytes each).
@@ -103,7 +107,7 @@ struct SplitStage {
   static_assert(!BLK || (C::LR % 2 == 0 && C::LC % 2 == 0), "2x2 staging blocks need even tile sides");
   static constexpr int NST = (BLK ? (C::LR / 2) * (C::LC / 2) : C::LR * C::LC) * NC4;
   static constexpr int NIT = (NST + NPT - 1) / NPT;
-  static constexpr int NL = KIND == SK_GROUP ? 9 : KIND == SK_PHASE ? 4 : BLK ? 9 : 1;
+  static constexpr int NL = KIND == SK_GROUP ? 9 : !POOL ? 1 : KIND == SK_PHASE ? 4 : 9;
   static constexpr int IPB = (NIT + C::NSL - 1) / C::NSL;  // items per thread and slice window
   static_assert(NPT % NC4 == 0, "a thread keeps its channel chunk");
   f4 q[IPB][NL];
@@ -119,6 +123,14 @@ struct SplitStage {
     if (t >= NST) return;
     const int cg = t % NC4, it = t / NC4;
     const gbyte* b = base + cg * 16;
+    if constexpr (C::CINP != C::NCIN) {
+      static_assert(C::NCB == 1 || C::CINP == C::NCIN, "padding in a single channel block");
+      if (cg * 4 >= C::NCIN) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) q[n][i] = f4{0.f, 0.f, 0.f, 0.f};
+        return;
+      }
+    }
     if constexpr (KIND == SK_GROUP) {
       const int R = y0 + it / C::LC, Cc = x0 + it % C::LC;
       const int64_t a0 = (int64_t)min(R, rA) * rowb, b0 = (int64_t)min(R, rB) * rowb;
@@ -134,7 +146,7 @@ struct SplitStage {
       q[n][6] = ld<f4>(b + a1 + c0);              // F00[R+1][C]
       q[n][7] = ld<f4>(b + o01 + a1 + d0);        // F01[R+1][C]
       q[n][8] = ld<f4>(b + a1 + c1);              // F00[R+1][C+1]
-    } else if constexpr (KIND == SK_PHASE) {
+    } else if constexpr (KIND == SK_PHASE && POOL) {
       const gbyte* p = b + (int64_t)min(y0 + it / C::LC, rA) * rowb + (int64_t)min(x0 + it % C::LC, cA) * elb;
       q[n][0] = ld<f4>(p);
       q[n][1] = ld<f4>(p + o01);
@@ -177,7 +189,7 @@ struct SplitStage {
       put(lds, C::LR * C::LC + it, cg, mx(mx(v[1], v[4]), m35), sc);
       put(lds, 2 * C::LR * C::LC + it, cg, mx(m23, mx(v[6], v[7])), sc);
       put(lds, 3 * C::LR * C::LC + it, cg, mx(m35, mx(v[7], v[8])), sc);
-    } else if constexpr (KIND == SK_PHASE) {
+    } else if constexpr (KIND == SK_PHASE && POOL) {
       put(lds, it, cg, mx(mx(v[0], v[1]), mx(v[2], v[3])), sc);
     } else if constexpr (BLK) {
       const int r = 2 * (it / (C::LC / 2)), c = 2 * (it % (C::LC / 2));
@@ -241,6 +253,7 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
     a.elb = ELB;
     const gbyte* isc = wglob + C::PACKB + (ptid % (C::CB / 4)) * 16;  // this thread's channel scales
     f4 sc;
+    const float down = prm.range ? ldf(&prm.range->down, 0) : 1.0f;
     int cb = 0;
     const gbyte* tile0 = nullptr;  // channel 0 of the tile's slice (spaced: of its fragment)
     auto new_tile = [&]() __attribute__((always_inline)) {
@@ -274,7 +287,7 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
     };
     auto new_stage = [&]() __attribute__((always_inline)) {
       a.base = tile0 + cb * (C::CB * 4);
-      sc = ld<f4>(isc + cb * (C::CB * 4));
+      sc = ld<f4>(isc + cb * (C::CB * 4)) * down;
     };
     // the next stage of the walk; false past the last
     auto advance = [&]() __attribute__((always_inline)) -> bool {
@@ -360,30 +373,62 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
     }
     const int off = g < 2 ? (g == 0 ? o[0] : o[1]) : (g == 2 ? o[2] : o[3]);
     const unsigned char* ap = abase + off;
-    h8v bh[C::NB], bl[C::NB];
+    auto mm = [&](f4& c, const h8v& x, const h8v& wv) __attribute__((always_inline)) {
+      if constexpr (TRANS) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(wv, x, c, 0, 0, 0);
+      else c = __builtin_amdgcn_mfma_f32_16x16x32_f16(x, wv, c, 0, 0, 0);
+    };
+    auto a_at = [&](int u) __attribute__((always_inline)) {
+      return ap + ((u / MCOLS) * C::LC + (u % MCOLS) * 16) * C::PSB;
+    };
+    // the operand with fewer fragments stays in registers, the other streams
+    if constexpr (C::NB <= C::MW) {
+      h8v bh[C::NB], bl[C::NB];
 #pragma unroll
-    for (int nb = 0; nb < C::NB; ++nb) {
-      bh[nb] = ld<h8v>(wl + (nb * 2) * 1024);
-      bl[nb] = ld<h8v>(wl + (nb * 2 + 1) * 1024);
-    }
+      for (int nb = 0; nb < C::NB; ++nb) {
+        bh[nb] = ld<h8v>(wl + (nb * 2) * 1024);
+        bl[nb] = ld<h8v>(wl + (nb * 2 + 1) * 1024);
+      }
 #pragma unroll
-    for (int u = 0; u < C::MW; ++u) {
-      const int mo = ((u / MCOLS) * C::LC + (u % MCOLS) * 16) * C::PSB;
-      const h8v ah = ld<h8v>(ap + mo), al = ld<h8v>(ap + C::HALF + mo);
-      auto mm = [&](f4& c, const h8v& x, const h8v& wv) __attribute__((always_inline)) {
-        if constexpr (TRANS) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(wv, x, c, 0, 0, 0);
-        else c = __builtin_amdgcn_mfma_f32_16x16x32_f16(x, wv, c, 0, 0, 0);
-      };
+      for (int u = 0; u < C::MW; ++u) {
+        const h8v ah = ld<h8v>(a_at(u)), al = ld<h8v>(a_at(u) + C::HALF);
 #pragma unroll
-      for (int nb = 0; nb < C::NB; ++nb) mm(acc[u][nb], al, bh[nb]);
+        for (int nb = 0; nb < C::NB; ++nb) mm(acc[u][nb], al, bh[nb]);
 #pragma unroll
-      for (int nb = 0; nb < C::NB; ++nb) mm(acc[u][nb], ah, bl[nb]);
+        for (int nb = 0; nb < C::NB; ++nb) mm(acc[u][nb], ah, bl[nb]);
 #pragma unroll
-      for (int nb = 0; nb < C::NB; ++nb) mm(acc[u][nb], ah, bh[nb]);
+        for (int nb = 0; nb < C::NB; ++nb) mm(acc[u][nb], ah, bh[nb]);
+      }
+    } else {
+      h8v ah[C::MW], al[C::MW];
+#pragma unroll
+      for (int u = 0; u < C::MW; ++u) {
+        ah[u] = ld<h8v>(a_at(u));
+        al[u] = ld<h8v>(a_at(u) + C::HALF);
+      }
+      // the next n-block's weights are loaded ahead of this one's MFMAs, and no
+      // earlier (the scheduler would hoist them until the registers spill)
+      h8v bh[2], bl[2];
+      bh[0] = ld<h8v>(wl);
+      bl[0] = ld<h8v>(wl + 1024);
+#pragma unroll
+      for (int nb = 0; nb < C::NB; ++nb) {
+        if (nb + 1 < C::NB) {
+          bh[(nb + 1) & 1] = ld<h8v>(wl + (nb * 2 + 2) * 1024);
+          bl[(nb + 1) & 1] = ld<h8v>(wl + (nb * 2 + 3) * 1024);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < C::MW; ++u) mm(acc[u][nb], al[u], bh[nb & 1]);
+#pragma unroll
+        for (int u = 0; u < C::MW; ++u) mm(acc[u][nb], ah[u], bl[nb & 1]);
+#pragma unroll
+        for (int u = 0; u < C::MW; ++u) mm(acc[u][nb], ah[u], bh[nb & 1]);
+      }
     }
   };
 
-  const gbyte* osc_p = wglob + C::PACKB + CIN * 4;
+  const gbyte* osc_p = wglob + C::PACKB + C::CINP * 4;
+  const float up = prm.range ? ldf(&prm.range->up, 0) : 1.0f;
   auto epilogue = [&]() __attribute__((always_inline)) {
     int zz, py, px, y0, x0;
     origin(zz, py, px, y0, x0);
@@ -393,7 +438,7 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
 #pragma unroll
       for (int nb = 0; nb < C::NB; ++nb) {
         bias[nb] = ldf(prm.bias, nb * 16 + n16);
-        osc[nb] = ld<float>(osc_p + (nb * 16 + n16) * 4);
+        osc[nb] = ld<float>(osc_p + (nb * 16 + n16) * 4) * up;
         hw[nb] = ldf(prm.head_w, nb * 16 + n16);
       }
       head_epilogue<C::MW, C::NB>(
@@ -404,13 +449,28 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
           },
           bias, osc, hw, prm.head_b, g, n16, gout(J.out), (int64_t)zz * J.out_zs, J.out_rs, J.hout, J.wout);
     } else {
-      f4 bs[C::NB], sc[C::NB];
+      // biases and scales of this lane's channels, all at once where the
+      // accumulators leave the registers for it (4 n-blocks: FastMemb's convs 7 %
+      // faster than with a load at each use), else where they are used
+      constexpr bool PRE = C::NB <= 4;
+      f4 bsv[PRE ? C::NB : 1], scv[PRE ? C::NB : 1];
+      auto chan4 = [&](int nb) __attribute__((always_inline)) { return split_chan(nb, 4 * g, C::NB, SPACED) * 4; };
+      if constexpr (PRE) {
 #pragma unroll
-      for (int nb = 0; nb < C::NB; ++nb) {
-        const int c = split_chan(nb, 4 * g, C::NB, SPACED);
-        bs[nb] = ld<f4>(gin(prm.bias) + c * 4);
-        sc[nb] = ld<f4>(osc_p + c * 4);
+        for (int nb = 0; nb < C::NB; ++nb) {
+          bsv[nb] = ld<f4>(gin(prm.bias) + chan4(nb));
+          scv[nb] = ld<f4>(osc_p + chan4(nb)) * up;
+        }
       }
+      // this lane's four channels of n-block nb: acc * sc + bs
+      auto value = [&](f4 v, int nb) __attribute__((always_inline)) {
+        const f4 bs = PRE ? bsv[PRE ? nb : 0] : ld<f4>(gin(prm.bias) + chan4(nb));
+        const f4 sc = PRE ? scv[PRE ? nb : 0] : ld<f4>(osc_p + chan4(nb)) * up;
+        f4 t;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t[k] = fmaf(v[k], sc[k], bs[k]);
+        return t;
+      };
       if constexpr (SPACED) {
         const int d = max(J.geom & 0xff, 1), lgo = (J.geom >> 16) & 0xf;
         if constexpr (KIND == SK_GROUP) {
@@ -418,26 +478,30 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
           py += (wmem >> 1) * h;  // member (a, b) = (wmem / 2, wmem % 2): phase (gy + a h, gx + b h)
           px += (wmem & 1) * h;
         }
+        gbyte* o[C::MW];
+        bool ok[C::MW];
 #pragma unroll
         for (int u = 0; u < C::MW; ++u) {
           const int y = py + d * (y0 + wrow0 + u / MCOLS), x = px + d * (x0 + (u % MCOLS) * 16 + n16);
-          if (y < J.hout && x < J.wout) {
-            gbyte* o = gout(J.out) + ((int64_t)zz * J.out_zs + frag_pix(y, x, lgo, J.out_rs, J.out_zs)) * (COUT * 2);
-            float m[C::NB][2];
+          ok[u] = y < J.hout && x < J.wout;
+          o[u] = gout(J.out) + ((int64_t)zz * J.out_zs + frag_pix(y, x, lgo, J.out_rs, J.out_zs)) * (COUT * 2);
+        }
+        // a pair of n-blocks at a time (all biases and scales at once would spill)
 #pragma unroll
-            for (int nb = 0; nb < C::NB; ++nb) {
-              float t[4];
+        for (int nb = 0; nb < C::NB; nb += 2) {
+          const int at = split_chan(nb, 4 * g, C::NB, true) * 2;
 #pragma unroll
-              for (int k = 0; k < 4; ++k) t[k] = fmaf(acc[u][nb][k], sc[nb][k], bs[nb][k]);
-              m[nb][0] = fmaxf(t[0], t[1]);
-              m[nb][1] = fmaxf(t[2], t[3]);
+          for (int u = 0; u < C::MW; ++u) {
+            const f4 p = value(acc[u][nb], nb);
+            if (nb + 1 < C::NB) {
+              const f4 q = value(acc[u][nb + 1 < C::NB ? nb + 1 : nb], nb + 1 < C::NB ? nb + 1 : nb);
+              if (ok[u])
+                st<f4>(o[u] + at, f4{fmaxf(p[0], p[1]), fmaxf(p[2], p[3]), fmaxf(q[0], q[1]), fmaxf(q[2], q[3])});
+            } else if (ok[u]) {
+              st<f2>(o[u] + at, f2{fmaxf(p[0], p[1]), fmaxf(p[2], p[3])});
             }
-#pragma unroll
-            for (int nb = 0; nb + 1 < C::NB; nb += 2)
-              st<f4>(o + split_chan(nb, 4 * g, C::NB, true) * 2, f4{m[nb][0], m[nb][1], m[nb + 1][0], m[nb + 1][1]});
-            if constexpr (C::NB & 1)
-              st<f2>(o + split_chan(C::NB - 1, 4 * g, C::NB, true) * 2, f2{m[C::NB - 1][0], m[C::NB - 1][1]});
           }
+          if constexpr (!PRE) __builtin_amdgcn_sched_barrier(0);
         }
       } else {
 #pragma unroll
@@ -447,9 +511,9 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
             gbyte* o = gout(J.out) + ((int64_t)zz * J.out_zs + (int64_t)y * J.out_rs + x) * (COUT * 4) + g * 16;
 #pragma unroll
             for (int nb = 0; nb < C::NB; ++nb) {
-              f4 t;
+              f4 t = value(acc[u][nb], nb);
 #pragma unroll
-              for (int k = 0; k < 4; ++k) t[k] = relu(fmaf(acc[u][nb][k], sc[nb][k], bs[nb][k]));
+              for (int k = 0; k < 4; ++k) t[k] = relu(t[k]);
               st<f4>(o + nb * 64, t);
             }
           }
@@ -499,9 +563,10 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
   EMCNN_SPLITN("conv_split<" #CIN "," #COUT "," #KS "," #POOL "," #HEAD "," #TY "," #TX "," #NCW "," #NPW "," #CB \
                "," #SS ">",                                                                                 \
                CIN, COUT, KS, POOL, (HEAD ? SK_HEAD : SK_RELU), TY, TX, NCW, NPW, CB, SS)
-#define EMCNN_SPLIT_PHASE(CIN, COUT, KS, TY, TX, NCW, NPW, CB, SS)                                          \
-  EMCNN_SPLITN("conv_phase<F32S," #CIN "," #COUT "," #KS "," #TY "," #TX "," #NCW "," #NPW "," #CB "," #SS ">", \
-               CIN, COUT, KS, true, SK_PHASE, TY, TX, NCW, NPW, CB, SS)
+#define EMCNN_SPLIT_PHASE(CIN, COUT, KS, POOL, TY, TX, NCW, NPW, CB, SS)                                    \
+  EMCNN_SPLITN("conv_phase<F32S," #CIN "," #COUT "," #KS "," #POOL "," #TY "," #TX "," #NCW "," #NPW "," #CB "," #SS \
+               ">",                                                                                         \
+               CIN, COUT, KS, POOL, SK_PHASE, TY, TX, NCW, NPW, CB, SS)
 #define EMCNN_SPLIT_GROUP(CIN, COUT, KS, TY, NCW, NPW, CB, SS)                                              \
   EMCNN_SPLITN("conv_phase_group<F32S," #CIN "," #COUT "," #KS "," #TY "," #NCW "," #NPW "," #CB "," #SS ">", \
                CIN, COUT, KS, true, SK_GROUP, TY, 16, NCW, NPW, CB, SS)
@@ -521,12 +586,20 @@ static const VariantInfo kSplit[] = {
     EMCNN_SPLIT(48, 48, 3, true, true, 16, 48, 8, 4, 16, 3), EMCNN_SPLIT(48, 48, 3, true, true, 16, 32, 8, 4, 16, 3),
     EMCNN_SPLIT(48, 48, 3, true, true, 8, 32, 8, 4, 16, 5), EMCNN_SPLIT(48, 48, 3, true, true, 8, 16, 8, 4, 16, 5),
     // net A conv2 and head (0.30 ms on 8 x 1024^2; 8 x 16 0.50)
-    EMCNN_SPLIT(16, 16, 5, false, true, 16, 32, 8, 4, 16, 13), EMCNN_SPLIT(16, 16, 5, false, true, 8, 16, 8, 4, 16, 13),
+    EMCNN_SPLIT(16, 16, 5, false, true, 16, 32, 8, 4, 16, 7), EMCNN_SPLIT(16, 16, 5, false, true, 8, 16, 8, 4, 16, 13),
     // FastMemb and FastMemb_ss body convs: over phase groups (1.28 ms; 12-row
     // members 1.27-1.29, 4-row ones 1.56), per phase 1.32 (8 x 32 1.53)
     EMCNN_SPLIT_GROUP(32, 64, 4, 8, 8, 4, 16, 2), EMCNN_SPLIT_GROUP(32, 64, 4, 12, 8, 4, 16, 1),
     EMCNN_SPLIT_GROUP(32, 64, 4, 4, 8, 4, 16, 2),
-    EMCNN_SPLIT_PHASE(32, 64, 4, 16, 32, 8, 4, 16, 2), EMCNN_SPLIT_PHASE(32, 64, 4, 8, 32, 8, 4, 16, 2),
+    EMCNN_SPLIT_PHASE(32, 64, 4, true, 16, 32, 8, 4, 16, 2), EMCNN_SPLIT_PHASE(32, 64, 4, true, 8, 32, 8, 4, 16, 2),
+    // MaskExtend (4 x 800^2): twelve maps, no max filter; 32 -> 80 (0.58 ms; 4-row
+    // members 0.61), 40 -> 96 in 8-channel stages (0.81; 0.94), 48 -> 112 (1.02 with
+    // 8 consumer waves, 1.05 with 4 of twice the m-blocks), 56 -> 128 (1.32; 1.32).
+    // 8-row members of the two widest would need 112 and 128 accumulators and spill.
+    EMCNN_SPLIT_PHASE(12, 64, 4, false, 16, 32, 8, 4, 16, 2), EMCNN_SPLIT_PHASE(12, 64, 4, false, 8, 32, 8, 4, 16, 2),
+    EMCNN_SPLIT_GROUP(32, 80, 4, 8, 8, 4, 16, 1), EMCNN_SPLIT_GROUP(32, 80, 4, 4, 8, 4, 16, 2),
+    EMCNN_SPLIT_GROUP(40, 96, 4, 8, 8, 4, 8, 2), EMCNN_SPLIT_GROUP(40, 96, 4, 4, 8, 4, 8, 2),
+    EMCNN_SPLIT_GROUP(48, 112, 4, 4, 8, 4, 16, 2), EMCNN_SPLIT_GROUP(56, 128, 4, 4, 8, 4, 8, 2),
 };
 
 int split_variant_count() { return (int)(sizeof(kSplit) / sizeof(kSplit[0])); }

@@ -12,6 +12,7 @@
 
 #include "../../include/emcnn.h"
 #include "common.h"
+#include "device_util.h"
 #include "runtime.h"
 
 namespace emcnn {
@@ -142,6 +143,7 @@ int launch_layer(Net* net, const ExecLayer& L, const JobSet& js, int grid, hipSt
     p.head_w = L.head_w;
     p.head_b = L.head_b;
     p.out_inv_scale = L.out_inv_scale;
+    p.range = net->range;
     if (conv_variant(L.variant)->fused) {
       const ExecLayer& L0 = net->layers[0];
       p.w1 = L0.wpack;
@@ -179,14 +181,32 @@ static int run_region(Net* net, const uint8_t* in, int64_t in_rs, int64_t in_zs,
     int64_t lin_rs = in_rs, lin_zs = in_zs, lout_rs = out_rs, lout_zs = out_zs;
     if (li > 0) map_strides(net->layers[li - 1], d.hin[li], d.win[li], lin_rs, lin_zs);
     if (l < nl - 1) map_strides(L, d.hout[l], d.wout[l], lout_rs, lout_zs);
-    LayerJob j = make_job(L, lin, out, zc, d.hin[li], d.win[li], lin_rs, lin_zs, d.hout[l], d.wout[l], lout_rs,
-                          lout_zs, 0, nullptr);
-    JobSet js;
-    std::memset(&js, 0, sizeof(js));
-    js.njobs = 1;
-    js.total_items = job_items(j);
-    js.single = j;
-    const int rc = launch_layer(net, L, js, persistent_grid(net, L, js.total_items), st, timed);
+    const auto launch = [&](const ExecLayer& V, const int32_t* gate) {
+      LayerJob j = make_job(V, lin, out, zc, d.hin[li], d.win[li], lin_rs, lin_zs, d.hout[l], d.wout[l], lout_rs,
+                            lout_zs, 0, gate);
+      JobSet js;
+      std::memset(&js, 0, sizeof(js));
+      js.njobs = 1;
+      js.total_items = job_items(j);
+      js.single = j;
+      return launch_layer(net, V, js, persistent_grid(net, V, js.total_items), st, timed);
+    };
+    int rc;
+    if (net->range && !L.first && conv_variant(L.variant)->split) {
+      // whichever of the two the maps' range opens; the other finds its gate closed
+      rc = launch(L, &net->range->ok);
+      ExecLayer& M = net->layers[l];
+      const int v0 = M.variant;
+      for (int c : M.candidates)
+        if (!conv_variant(c)->split) {
+          select_variant(M, c);
+          break;
+        }
+      if (!rc) rc = launch(M, &net->range->bad);
+      select_variant(M, v0);
+    } else {
+      rc = launch(L, nullptr);
+    }
     if (rc) return rc;
   }
   return CNN_OK;
@@ -197,6 +217,50 @@ static void region_bytes(const Net* net, int h, int w, size_t& b0, size_t& b1) {
   const std::vector<size_t> lb = layer_bytes(net, layer_dims(net, h, w));
   b0 = b1 = 0;
   for (size_t l = 0; l < lb.size(); ++l) (l % 2 ? b1 : b0) = std::max((l % 2 ? b1 : b0), lb[l]);
+}
+
+// Running maximum of |x| over n floats, as float bits (above those of infinity: a
+// NaN). One read of the maps: 48 of the hundreds of bytes a pixel that the first
+// layer reads and writes.
+__global__ __launch_bounds__(256) void maps_top(const float* __restrict__ x, int64_t n, MapsRange* r) {
+  __shared__ uint32_t red[4];
+  uint32_t top = 0;
+  const int64_t step = (int64_t)gridDim.x * 256;
+  const int64_t n4 = ((uintptr_t)x & 15) == 0 ? n / 4 : 0;
+  const gbyte* b = gin(x);
+  for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < n4; i += step) {
+    const u4v v = ld<u4v>(b + i * 16);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) top = max(top, v[k] & 0x7fffffffu);
+  }
+  for (int64_t i = 4 * n4 + blockIdx.x * 256ll + threadIdx.x; i < n; i += step)
+    top = max(top, ld<uint32_t>(b + i * 4) & 0x7fffffffu);
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, s));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = top;
+  __syncthreads();
+  if (threadIdx.x == 0) atomicMax(&r->top, max(max(red[0], red[1]), max(red[2], red[3])));
+}
+
+// The call's scales and gates from the maximum, which is cleared for the next call.
+__global__ void maps_scale(MapsRange* r) {
+  const uint32_t t = r->top;
+  int k = (int)(t >> 23) - 127 + ((t & 0x7fffffu) ? 1 : 0);  // least k with every |x| <= 2^k
+  k = max(k, 0);
+  const bool ok = k <= kMapsRangeMax;  // infinities and NaN have the largest exponent
+  r->down = ok ? ldexpf(1.0f, -k) : 1.0f;
+  r->up = ok ? ldexpf(1.0f, k) : 1.0f;
+  r->ok = ok;
+  r->bad = !ok;
+  r->top = 0;
+}
+
+static int launch_range(Net* net, const float* maps, int64_t n, hipStream_t st) {
+  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((n / 4 + 1023) / 1024, net->num_cus * 8));
+  hipLaunchKernelGGL(maps_top, dim3(grid), dim3(256), 0, st, maps, n, net->range);
+  hipLaunchKernelGGL(maps_scale, dim3(1), dim3(1), 0, st, net->range);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? CNN_OK : hip_fail(e, "cnn_infer_maps: range of the maps");
 }
 
 // A whole volume: slabs of slices sized so the two inter-layer buffers stay
@@ -217,6 +281,8 @@ int run_volume(Net* net, const uint8_t* vol, int64_t Z, int64_t H, int64_t W, fl
   net->last_W = W;
   net->last_zslab = zs;
   net->last_half = zs * b0;
+  if (net->range && (rc = launch_range(net, reinterpret_cast<const float*>(vol), Z * H * W * net->in_channels, st)))
+    return rc;
   for (int64_t z0 = 0; z0 < Z; z0 += zs) {
     const int zc = (int)std::min<int64_t>(zs, Z - z0);
     rc = run_region(net, vol + z0 * H * W * net->in_elb, W, H * W, zc, (int)H, (int)W, prob + z0 * Ho * Wo, Wo,

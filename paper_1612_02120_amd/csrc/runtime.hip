@@ -340,12 +340,13 @@ static SplitWeights split_weights(const cnn_layer& l, const double* w, const Bou
 
 // Weights of a split conv: fragments [channel block][group-step][n-block][hi,
 // lo][lane][8 f16], lane (n16, g) holding channel split_chan of row n16 for the
-// 8 input channels of slot 4 s + g; then float iscale[cin], oscale[cout].
+// 8 input channels of slot 4 s + g; then float iscale[cin, padded to whole blocks],
+// oscale[cout].
 static int pack_split(ExecLayer& L, int variant, const SplitWeights& sw, const double* b, const double* hw, double hb) {
   const VariantInfo* v = conv_variant(variant);
-  const int cin = v->cin, cout = v->cout, ks = v->ks, cb = v->cb, ncb = cin / cb, nb = cout / 16;
+  const int cin = v->cin, cout = v->cout, ks = v->ks, cb = v->cb, ncb = (cin + cb - 1) / cb, nb = cout / 16;
   const size_t frags = (size_t)ncb * v->ngs * nb * 2 * 1024;
-  std::vector<uint8_t> pk(frags + (size_t)(cin + cout) * 4, 0);
+  std::vector<uint8_t> pk(frags + (size_t)(ncb * cb + cout) * 4, 0);
   for (int c0 = 0; c0 < ncb; ++c0)
     for (int s = 0; s < v->ngs; ++s)
       for (int g = 0; g < 4; ++g) {
@@ -354,14 +355,16 @@ static int pack_split(ExecLayer& L, int variant, const SplitWeights& sw, const d
         for (int q = 0; q < nb; ++q)
           for (int r = 0; r < 16; ++r) {
             const int co = split_chan(q, r, nb, v->split == 2);
-            const size_t at = ((size_t)co * ks * ks + k.i * ks + k.j) * cin + c0 * cb + k.cg * 8;
+            const int ci = c0 * cb + k.cg * 8, live = std::min(8, cin - ci);  // channels past cin: zero weights
+            if (live <= 0) continue;
+            const size_t at = ((size_t)co * ks * ks + k.i * ks + k.j) * cin + ci;
             uint8_t* dst = pk.data() + (((size_t)(c0 * v->ngs + s) * nb + q) * 2 * 64 + g * 16 + r) * 16;
-            std::memcpy(dst, &sw.hi[at], 16);
-            std::memcpy(dst + 1024, &sw.lo[at], 16);
+            std::memcpy(dst, &sw.hi[at], 2 * live);
+            std::memcpy(dst + 1024, &sw.lo[at], 2 * live);
           }
       }
   std::memcpy(pk.data() + frags, sw.iscale.data(), (size_t)cin * 4);
-  std::memcpy(pk.data() + frags + (size_t)cin * 4, sw.oscale.data(), (size_t)cout * 4);
+  std::memcpy(pk.data() + frags + (size_t)ncb * cb * 4, sw.oscale.data(), (size_t)cout * 4);
   return upload_conv(L, v, pk, b, {}, hw, hb, 0.0);
 }
 
@@ -588,9 +591,10 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
   }
   const double* wp = weights;
   int sp = 1;  // spacing of the current layer's input
-  // ranges of the current layer's input channels (V / 255 lies in [0, 1]); real-valued maps have none
-  Bounds act;
-  if (!maps) act = Bounds{{0.0}, {1.0}};
+  // ranges of the current layer's input channels: V / 255 lies in [0, 1]; real-valued
+  // maps are taken to lie in [-1, 1], and MapsRange covers what each call brings
+  Bounds act{{0.0}, {1.0}};
+  if (maps) act = Bounds{std::vector<double>(l0.cin, -1.0), std::vector<double>(l0.cin, 1.0)};
   for (size_t c = 0; c < conv_at.size(); ++c) {
     const cnn_layer& l = Lr[conv_at[c]];
     const int64_t nwl = (int64_t)l.cout * l.cin * l.k * l.k;
@@ -604,7 +608,7 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
     int rc = CNN_OK;
     SplitWeights split;
     if (prec == CNN_PREC_FP32) split = split_weights(l, w, act);
-    if (!act.lo.empty()) act = conv_bounds(l, w, b, act);
+    act = conv_bounds(l, w, b, act);
     if (c == 0 && maps) {
       // a spaced conv straight on the caller's NHWC float maps: no max filter, spacing 1
       E.cout = l.cout;
@@ -617,11 +621,13 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
       E.candidates.erase(std::remove_if(E.candidates.begin(), E.candidates.end(),
                                         [](int v) { return conv_variant(v)->groups != 0; }),
                          E.candidates.end());  // no max filter: no phase groups
-      keep_split(E, false);  // its input has no bound
+      keep_split(E, split.ok);
       if (E.candidates.empty()) return unsupported("no kernel for a first conv " + std::to_string(l.cin) + " -> " +
                                                    std::to_string(l.cout));
       for (int v : E.candidates)
-        if (rc == CNN_OK) rc = pack_conv(E, v, w, b, nullptr, 0.0, 1.0, 0.0);
+        if (rc == CNN_OK)
+          rc = conv_variant(v)->split ? pack_split(E, v, split, b, nullptr, 0.0)
+                                      : pack_conv(E, v, w, b, nullptr, 0.0, 1.0, 0.0);
     } else if (c == 0) {
       E.first = 1;
       E.cout = l.cout;
@@ -721,6 +727,14 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
   net->in_elb = maps ? 4 * l0.cin : 1;
   // every map but the output feeds a spaced conv: stored fragment-major modulo its spacing
   for (size_t l = 0; l + 1 < net->layers.size(); ++l) net->layers[l].out_lg = __builtin_ctz(net->layers[l + 1].dil);
+  bool any = false;
+  for (const ExecLayer& E : net->layers)
+    for (int v : E.candidates) any |= !E.first && conv_variant(v)->split;
+  if (maps && any) {
+    hipError_t e = hipMalloc((void**)&net->range, sizeof(MapsRange));
+    if (e != hipSuccess) return fail(CNN_ENOMEM, "cnn_create: range of the maps");
+    if ((e = hipMemset(net->range, 0, sizeof(MapsRange))) != hipSuccess) return hip_fail(e, "hipMemset(range)");
+  }
   return CNN_OK;
 }
 
@@ -862,6 +876,7 @@ extern "C" int cnn_create(const double* weights, int64_t n_weights, const cnn_la
     const int rc = build_strided(net, weights, Lr, nl);
     if (rc != CNN_OK) {
       for (auto& E : net->layers) free_layer(E);
+      if (net->range) hipFree(net->range);
       delete net;
       return rc;
     }
@@ -990,6 +1005,7 @@ extern "C" int cnn_destroy(cnn_net* h) {
   hipDeviceSynchronize();
   for (auto& E : net->layers) free_layer(E);
   if (net->ws) hipFree(net->ws);
+  if (net->range) hipFree(net->range);
   for (Net::Arena& A : net->arena) {
     if (A.tab_dev) hipFree(A.tab_dev);
     if (A.tab_host) hipHostFree(A.tab_host);

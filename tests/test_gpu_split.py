@@ -7,8 +7,9 @@ import pytest
 import torch
 
 import oracle
-from synth import em_volume
-from synth.nets import NET_A, NET_B, NET_FM, NET_FMSS, bias_slices, calibrated_params, he_normal_params, random_bias_params
+from synth import em_volume, maskextend_maps
+from synth.nets import (NET_A, NET_B, NET_FM, NET_FMSS, NET_ME, bias_slices, calibrated_params, he_normal_params,
+                        random_bias_params)
 
 pytestmark = pytest.mark.gpu
 
@@ -100,7 +101,7 @@ def test_channels_of_very_different_scales(emcnn):
     # activations from 2^-30 to 2^30 beside each other
     p = random_bias_params(NET_B, 41, 42)
     rng = np.random.default_rng(5)
-    q = _rescaled(NET_B, p, [rng.integers(-30, 31, 48).astype(np.float64), rng.integers(-30, 31, 48).astype(np.float64)])
+    q = _rescaled(NET_B, p, [rng.integers(-30, 31, 48).astype(np.float64) for _ in range(2)])
     vol = em_volume(3, 1, 70, 90)
     h = emcnn.cnn_create(q, NET_B, "fp32")
     assert _is_split(emcnn.cnn_variant_names(h, 1)[0])
@@ -123,3 +124,58 @@ def test_unbounded_activations_keep_the_fp32_kernels(emcnn):
     for layer in (1, 2):
         assert not any(_is_split(n) for n in emcnn.cnn_variant_names(h, layer))
     _run(emcnn, h, vol)
+
+
+def _fp32_variants(emcnn, h, layers):
+    for layer in range(layers):
+        names = [n for n in emcnn.cnn_variant_names(h, layer) if not _is_split(n)]
+        if names:
+            emcnn.cnn_set_variant(h, layer, names[0])
+
+
+def test_maskextend_split_error_and_scaled_maps(emcnn):
+    maps = maskextend_maps(31, 2, 150, 141)
+    p = he_normal_params(NET_ME, 51)
+    ref = oracle.forward_maps(np.ascontiguousarray(np.transpose(maps, (0, 3, 1, 2)), dtype=np.float64), NET_ME, p)
+    x = torch.from_numpy(maps).cuda()
+    h = emcnn.cnn_create(p, NET_ME, "fp32")
+    assert all(_is_split(emcnn.cnn_variant_names(h, layer)[0]) for layer in range(5))
+    base = emcnn.cnn_infer_maps(h, x).cpu().numpy()
+    assert np.abs(base - ref).max() <= TOL
+    f = emcnn.cnn_create(p, NET_ME, "fp32")
+    _fp32_variants(emcnn, f, 5)
+    plain = emcnn.cnn_infer_maps(f, x).cpu().numpy()
+    assert np.sqrt(np.mean((base - ref) ** 2)) <= 1.25 * np.sqrt(np.mean((plain - ref) ** 2)) + 2.0 ** -24
+    # maps 2^9 times as large under weights 2^-9 times as large: the same function
+    q = p.copy()
+    q[:64 * 12 * 16] *= 2.0 ** -9
+    hq = emcnn.cnn_create(q, NET_ME, "fp32")
+    big = emcnn.cnn_infer_maps(hq, x * 512.0).cpu().numpy()
+    assert np.abs(big - ref).max() <= TOL
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), -float("inf"), 2.0 ** 30])
+def test_maps_without_a_usable_range_take_the_fp32_kernels(emcnn, value):
+    maps = torch.from_numpy(maskextend_maps(32, 2, 130, 125)).cuda()
+    p = he_normal_params(NET_ME, 52)
+    h, f = emcnn.cnn_create(p, NET_ME, "fp32"), emcnn.cnn_create(p, NET_ME, "fp32")
+    _fp32_variants(emcnn, f, 5)
+    before = emcnn.cnn_infer_maps(h, maps).clone()
+    odd = maps.clone()
+    odd[1, 3, 4, 5] = value
+    a, b = emcnn.cnn_infer_maps(h, odd), emcnn.cnn_infer_maps(f, odd)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.nan_to_num(a, nan=-1.0), torch.nan_to_num(b, nan=-1.0))
+    # the next call starts from its own range
+    assert torch.equal(emcnn.cnn_infer_maps(h, maps), before)
+
+
+def test_maps_range_of_an_unaligned_tensor(emcnn):
+    maps = torch.from_numpy(maskextend_maps(33, 1, 125, 121)).cuda()
+    p = he_normal_params(NET_ME, 53)
+    h = emcnn.cnn_create(p, NET_ME, "fp32")
+    flat = torch.empty(maps.numel() + 4, dtype=torch.float32, device="cuda")
+    for off in (0, 4):  # 16-byte steps: what the layers' own loads take
+        view = flat[off:off + maps.numel()].view(maps.shape)
+        view.copy_(maps)
+        assert torch.equal(emcnn.cnn_infer_maps(h, view), emcnn.cnn_infer_maps(h, maps))
