@@ -94,3 +94,12 @@ def test_watershed_row_ends_and_alignment(emcnn, W, offset):
     lab = emcnn.watershed_3d(view, 0.1)
     torch.cuda.synchronize()
     assert np.array_equal(lab.cpu().numpy(), oracle.watershed(p, 0.1))
+
+
+@pytest.mark.parametrize("shape", [(2, 256, 256), (2, 256, 257), (3, 181, 290)])
+def test_watershed_around_the_small_volume_form(emcnn, shape):
+    """2^17 voxels and just above and beside it: labels in one launch or two."""
+    rng = np.random.default_rng(shape[2])
+    p = ndimage.gaussian_filter(rng.uniform(0, 1, shape), 1.5).astype(np.float32)
+    t = float(np.quantile(p, 0.4))
+    assert np.array_equal(_gpu(emcnn, p, t), oracle.watershed(p, t))
