@@ -90,6 +90,14 @@ struct FirstParams {
   float pad_;
 };
 
+// Measured cost of a kernel's work item, from which the host picks the tile
+// shape of a launch (pick_variant): us of one item alone on a CU, and us per item
+// and CU of a launch that fills the chip. 0: not picked by size. Only variants
+// that contract in the same order carry costs, so that the choice changes no bit.
+struct TileCost {
+  float lone, rate;
+};
+
 // Compile-time description of a conv-kernel variant (also used on the host to
 // pack weights in the layout the variant reads).
 struct VariantInfo {
@@ -118,6 +126,7 @@ struct VariantInfo {
   int groups = 0;       // 1: a work item is a tile of four phases whose max filters share
                         // fragments (spaced layers whose max filter has half their spacing)
   int split = 0;        // FP32 operands as f16 hi + lo pairs (conv_split); 2: max-out row order
+  TileCost cost = {};
 };
 
 // K order of the implicit-GEMM convs over one channel block. K slot c is read
@@ -182,6 +191,7 @@ struct FirstInfo {
   int lds_bytes;  // the uint8 input tile (descriptive; the per-wave epilogue scratch comes on top)
   const void* fn;
   const char* name;
+  TileCost cost = {};
 };
 
 // Registries implemented in conv_kernels.hip and (split FP32 convs, which come

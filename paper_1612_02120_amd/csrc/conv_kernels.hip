@@ -35,7 +35,9 @@
 // range: neighbouring tiles, which share halo rows, meet in the same L2.
 #include <hip/hip_runtime.h>
 
+#include <cstring>
 #include <type_traits>
+#include <vector>
 
 #include "common.h"
 #include "conv_util.h"
@@ -2688,6 +2690,7 @@ static const VariantInfo kConv[] = {
     EMCNN_HEAD_TAPS(F32, 32, 4, 13, 4, 8), EMCNN_HEAD_TAPS(F32, 32, 4, 8, 4, 4), EMCNN_HEAD_TAPS(F32, 32, 4, 5, 4, 4),
     EMCNN_HEAD_TAPS(F32, 32, 4, 8, 8, 8),
     EMCNN_HEAD_STRIP(F32, 32, 4, 61), EMCNN_HEAD_STRIP(F32, 32, 4, 41), EMCNN_HEAD_STRIP(F32, 32, 4, 31),
+    EMCNN_HEAD_STRIP(F32, 32, 4, 15), EMCNN_HEAD_STRIP(F32, 32, 4, 7),
     EMCNN_HEAD_TAPS4(F32, 32, 4, 13, 4, 8), EMCNN_HEAD_TAPS4(F32, 32, 4, 5, 4, 4), EMCNN_HEAD_TAPS4(F32, 32, 4, 6, 4, 4),
     EMCNN_PHASE(F32, 32, 16, 4, 8, 64, 4, 2, 32), EMCNN_PHASE(F32, 32, 16, 4, 16, 64, 8, 2, 16),
     // FastMemb BF16: bf16 activations (NHWC, 64 B per pixel) and weights, FP32
@@ -2708,6 +2711,7 @@ static const VariantInfo kConv[] = {
     EMCNN_HEAD_TAPS(BF16, 32, 4, 13, 4, 8), EMCNN_HEAD_TAPS(BF16, 32, 4, 8, 4, 4), EMCNN_HEAD_TAPS(BF16, 32, 4, 5, 4, 4),
     EMCNN_HEAD_TAPS(BF16, 32, 4, 8, 8, 8),
     EMCNN_HEAD_STRIP(BF16, 32, 4, 61), EMCNN_HEAD_STRIP(BF16, 32, 4, 41), EMCNN_HEAD_STRIP(BF16, 32, 4, 31),
+    EMCNN_HEAD_STRIP(BF16, 32, 4, 15), EMCNN_HEAD_STRIP(BF16, 32, 4, 7),
     EMCNN_HEAD_TAPS4(BF16, 32, 4, 13, 4, 8), EMCNN_HEAD_TAPS4(BF16, 32, 4, 5, 4, 4), EMCNN_HEAD_TAPS4(BF16, 32, 4, 6, 4, 4),
     // MaskExtend (FP32): twelve input maps, max-out convs to 32, 40, 48, 56, 64
     // features (channels staged per LDS pass chosen to fit 160 KB with the
@@ -2761,12 +2765,81 @@ static const FirstInfo kFirst[] = {
     EMCNN_FIRSTS(BF16, 64, 4, 8, 64, true, 2), EMCNN_FIRSTS(BF16, 64, 4, 16, 64, true, 2), EMCNN_FIRSTS(BF16, 64, 4, 4, 64, true, 2),
 };
 
+// Costs of the variants that pick_variant chooses among, by name (us of one item
+// alone on a CU; us per item and CU of a full launch): conv2 / conv3 on
+// 16 x 1024^2, FastMemb's layers on 8 x 1024^2, FastMemb_ss's first layer on
+// 6 x 1501 x 1333.
+struct NamedCost {
+  const char* name;
+  TileCost cost;
+};
+static const NamedCost kCosts[] = {
+    {"conv_ws<BF16,48,48,5,true,false,24,32,8,4,0>", {16.f, 16.5f}},
+    {"conv_ws<BF16,48,48,5,true,false,16,32,8,4,0>", {12.f, 11.7f}},
+    {"conv_ws<BF16,48,48,5,true,false,8,48,8,4,0>", {10.5f, 9.f}},
+    {"conv_ws<BF16,48,48,3,true,true,16,48,8,4,0>", {9.f, 8.9f}},
+    {"conv_ws<BF16,48,48,3,true,true,8,64,8,4,0>", {7.3f, 7.f}},
+    {"conv_ws<BF16,48,48,3,true,true,8,48,8,4,0>", {5.8f, 5.1f}},
+    {"conv_ws<FP8,48,48,5,true,false,24,32,8,4,0>", {12.8f, 9.3f}},
+    {"conv_ws<FP8,48,48,5,true,false,16,32,8,4,0>", {10.5f, 6.8f}},
+    {"conv_ws<FP8,48,48,5,true,false,8,48,8,4,0>", {8.4f, 5.4f}},
+    {"conv_ws<FP8,48,48,3,true,true,16,48,8,4,0>", {7.6f, 5.45f}},
+    {"conv_ws<FP8,48,48,3,true,true,8,64,8,4,0>", {5.8f, 3.9f}},
+    {"conv_ws<FP8,48,48,3,true,true,8,48,8,4,0>", {5.1f, 3.2f}},
+    {"conv_ws_group<BF16,32,64,4,12,8,4>", {11.7f, 10.8f}},
+    {"conv_ws_group<BF16,32,64,4,8,8,4>", {9.1f, 7.8f}},
+    {"conv_ws_phase<BF16,32,64,4,16,32,8,4>", {10.f, 8.4f}},
+    {"conv_ws_phase<BF16,32,64,4,8,64,8,4>", {9.5f, 8.8f}},
+    {"head_strip<F32,32,4,61>", {75.f, 32.f}},
+    {"head_strip<F32,32,4,31>", {42.f, 16.3f}},
+    {"head_strip<F32,32,4,15>", {22.f, 8.4f}},
+    {"head_strip<F32,32,4,7>", {12.f, 4.8f}},
+    {"head_strip<BF16,32,4,61>", {33.f, 16.4f}},
+    {"head_strip<BF16,32,4,31>", {20.5f, 7.8f}},
+    {"head_strip<BF16,32,4,15>", {11.f, 4.1f}},
+    {"head_strip<BF16,32,4,7>", {6.5f, 2.3f}},
+};
+static const NamedCost kFirstCosts[] = {
+    {"conv_first<BF16,48,5,16,128,false,1>", {7.f, 9.3f}},
+    {"conv_first<BF16,48,5,8,64,false,1>", {3.4f, 2.45f}},
+    {"conv_first<BF16,48,5,4,64,false,1>", {2.5f, 1.28f}},
+    {"conv_first<FP8,48,5,32,128,false,1,xs>", {14.8f, 10.7f}},
+    {"conv_first<FP8,48,5,16,128,false,1,xs>", {7.7f, 5.4f}},
+    {"conv_first<FP8,48,5,16,64,false,1,xs>", {5.f, 3.1f}},
+    {"conv_first<FP8,48,5,8,64,false,1>", {2.8f, 2.f}},
+    {"conv_first<F32,64,4,16,128,true,1>", {25.f, 19.9f}},
+    {"conv_first<F32,64,4,4,64,true,1>", {4.4f, 2.8f}},
+    {"conv_first<BF16,64,4,32,128,true,1>", {17.6f, 14.4f}},
+    {"conv_first<BF16,64,4,16,256,true,1>", {16.8f, 14.f}},
+    {"conv_first<BF16,64,4,4,64,true,1>", {2.6f, 1.12f}},
+    {"conv_first<F32,64,4,16,64,true,2>", {15.f, 11.5f}},
+    {"conv_first<F32,64,4,8,64,true,2>", {8.1f, 5.9f}},
+    {"conv_first<F32,64,4,4,64,true,2>", {4.8f, 3.1f}},
+    {"conv_first<BF16,64,4,8,64,true,2>", {3.9f, 2.8f}},
+    {"conv_first<BF16,64,4,16,64,true,2>", {6.1f, 5.8f}},
+    {"conv_first<BF16,64,4,4,64,true,2>", {2.7f, 1.29f}},
+};
+
+// The registries with their costs filled in, once.
+template <class Info, int N, int M>
+static std::vector<Info> with_costs(const Info (&v)[N], const NamedCost (&costs)[M]) {
+  std::vector<Info> out(v, v + N);
+  for (Info& i : out)
+    for (const NamedCost& c : costs)
+      if (std::strcmp(i.name, c.name) == 0) i.cost = c.cost;
+  return out;
+}
+
 int conv_variant_count() { return split_variant_count() + (int)(sizeof(kConv) / sizeof(kConv[0])); }
 const VariantInfo* conv_variant(int i) {
+  static const std::vector<VariantInfo> conv = with_costs(kConv, kCosts);
   const int ns = split_variant_count();
-  return i < ns ? split_variant(i) : &kConv[i - ns];
+  return i < ns ? split_variant(i) : &conv[i - ns];
 }
 int first_variant_count() { return (int)(sizeof(kFirst) / sizeof(kFirst[0])); }
-const FirstInfo* first_variant(int i) { return &kFirst[i]; }
+const FirstInfo* first_variant(int i) {
+  static const std::vector<FirstInfo> first = with_costs(kFirst, kFirstCosts);
+  return &first[i];
+}
 
 }  // namespace emcnn

@@ -551,27 +551,27 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
 
 // ---------------------------------------------------------------- registry
 
-#define EMCNN_SPLITN(NAME, CIN, COUT, KS, POOL, KIND, TY, TX, NCW, NPW, CB, SS)                           \
+#define EMCNN_SPLITN(NAME, CIN, COUT, KS, POOL, KIND, TY, TX, NCW, NPW, CB, SS, LONE, RATE)               \
   VariantInfo{F32, CIN, COUT, KS, KIND >= SK_PHASE ? 1 : POOL, KIND == SK_HEAD, TY, TX,                    \
               CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS>::MW,                                 \
               CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS>::THREADS, CB, 8, 1,                  \
               CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS>::NSL * SS, 0, 0,                     \
               KIND >= SK_PHASE ? 1 : 0, CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS>::LDS,      \
               reinterpret_cast<const void*>(&conv_split<CIN, COUT, KS, POOL, KIND, TY, TX, NCW, NPW, CB, SS>), \
-              NAME, 0, KIND == SK_GROUP, KIND >= SK_PHASE ? 2 : 1}
-#define EMCNN_SPLIT(CIN, COUT, KS, POOL, HEAD, TY, TX, NCW, NPW, CB, SS)                                    \
+              NAME, 0, KIND == SK_GROUP, KIND >= SK_PHASE ? 2 : 1, TileCost{LONE, RATE}}
+#define EMCNN_SPLIT(CIN, COUT, KS, POOL, HEAD, TY, TX, NCW, NPW, CB, SS, LONE, RATE)                       \
   EMCNN_SPLITN("conv_split<" #CIN "," #COUT "," #KS "," #POOL "," #HEAD "," #TY "," #TX "," #NCW "," #NPW "," #CB \
                "," #SS ">",                                                                                 \
-               CIN, COUT, KS, POOL, (HEAD ? SK_HEAD : SK_RELU), TY, TX, NCW, NPW, CB, SS)
-#define EMCNN_SPLIT_PHASE(CIN, COUT, KS, POOL, TY, TX, NCW, NPW, CB, SS)                                    \
+               CIN, COUT, KS, POOL, (HEAD ? SK_HEAD : SK_RELU), TY, TX, NCW, NPW, CB, SS, LONE, RATE)
+#define EMCNN_SPLIT_PHASE(CIN, COUT, KS, POOL, TY, TX, NCW, NPW, CB, SS, LONE, RATE)                        \
   EMCNN_SPLITN("conv_phase<F32S," #CIN "," #COUT "," #KS "," #POOL "," #TY "," #TX "," #NCW "," #NPW "," #CB "," #SS \
                ">",                                                                                         \
-               CIN, COUT, KS, POOL, SK_PHASE, TY, TX, NCW, NPW, CB, SS)
-#define EMCNN_SPLIT_GROUP(CIN, COUT, KS, TY, NCW, NPW, CB, SS)                                              \
+               CIN, COUT, KS, POOL, SK_PHASE, TY, TX, NCW, NPW, CB, SS, LONE, RATE)
+#define EMCNN_SPLIT_GROUP(CIN, COUT, KS, TY, NCW, NPW, CB, SS, LONE, RATE)                                  \
   EMCNN_SPLITN("conv_phase_group<F32S," #CIN "," #COUT "," #KS "," #TY "," #NCW "," #NPW "," #CB "," #SS ">", \
-               CIN, COUT, KS, true, SK_GROUP, TY, 16, NCW, NPW, CB, SS)
+               CIN, COUT, KS, true, SK_GROUP, TY, 16, NCW, NPW, CB, SS, LONE, RATE)
 
-// First entry per signature: the default. All shapes of a signature contract in
+// First entry per signature: the default; last two arguments its TileCost. All shapes of a signature contract in
 // the same order (16-channel stages), so their outputs are bitwise the same.
 // Against the FP32 kernels, on 32 x 1024^2 (net B) and 8 x 1024^2 (FastMemb):
 // conv2 28.2 -> 8.6 ms (1.33 PFLOP/s of f16 products, 98 % of them useful),
@@ -579,27 +579,34 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
 static const VariantInfo kSplit[] = {
     // net B conv2: 24 x 32 tiles, 6 m-blocks per consumer wave (8.6 ms on
     // 32 x 1024^2; 16 x 32 8.8, 8 x 32 9.9, 8 x 16 12.9)
-    EMCNN_SPLIT(48, 48, 5, true, false, 24, 32, 8, 4, 16, 2), EMCNN_SPLIT(48, 48, 5, true, false, 16, 32, 8, 4, 16, 3),
-    EMCNN_SPLIT(48, 48, 5, true, false, 8, 32, 8, 4, 16, 4), EMCNN_SPLIT(48, 48, 5, true, false, 8, 16, 8, 4, 16, 4),
+    EMCNN_SPLIT(48, 48, 5, true, false, 24, 32, 8, 4, 16, 2, 45, 50),
+    EMCNN_SPLIT(48, 48, 5, true, false, 16, 32, 8, 4, 16, 3, 31, 34.3),
+    EMCNN_SPLIT(48, 48, 5, true, false, 8, 32, 8, 4, 16, 4, 20, 19.5),
+    EMCNN_SPLIT(48, 48, 5, true, false, 8, 16, 8, 4, 16, 4, 14, 12.7),
     // net B conv3 and head (3.5 ms; 16 x 32 3.6, 8 x 32 4.1, 8 x 16 5.6; the
     // whole stage's weights as one slice of 5 steps spills at 16 x 32, 7.0 ms)
-    EMCNN_SPLIT(48, 48, 3, true, true, 16, 48, 8, 4, 16, 3), EMCNN_SPLIT(48, 48, 3, true, true, 16, 32, 8, 4, 16, 3),
-    EMCNN_SPLIT(48, 48, 3, true, true, 8, 32, 8, 4, 16, 5), EMCNN_SPLIT(48, 48, 3, true, true, 8, 16, 8, 4, 16, 5),
+    EMCNN_SPLIT(48, 48, 3, true, true, 16, 48, 8, 4, 16, 3, 19, 20),
+    EMCNN_SPLIT(48, 48, 3, true, true, 16, 32, 8, 4, 16, 3, 14.5, 13.9),
+    EMCNN_SPLIT(48, 48, 3, true, true, 8, 32, 8, 4, 16, 5, 9.8, 8.1),
+    EMCNN_SPLIT(48, 48, 3, true, true, 8, 16, 8, 4, 16, 5, 6.5, 5.5),
     // net A conv2 and head (0.30 ms on 8 x 1024^2; 8 x 16 0.50)
-    EMCNN_SPLIT(16, 16, 5, false, true, 16, 32, 8, 4, 16, 7), EMCNN_SPLIT(16, 16, 5, false, true, 8, 16, 8, 4, 16, 13),
+    EMCNN_SPLIT(16, 16, 5, false, true, 16, 32, 8, 4, 16, 7, 6.5, 4.7),
+    EMCNN_SPLIT(16, 16, 5, false, true, 8, 16, 8, 4, 16, 13, 3, 1.95),
     // FastMemb and FastMemb_ss body convs: over phase groups (1.28 ms; 12-row
     // members 1.27-1.29, 4-row ones 1.56), per phase 1.32 (8 x 32 1.53)
-    EMCNN_SPLIT_GROUP(32, 64, 4, 8, 8, 4, 16, 2), EMCNN_SPLIT_GROUP(32, 64, 4, 12, 8, 4, 16, 1),
-    EMCNN_SPLIT_GROUP(32, 64, 4, 4, 8, 4, 16, 2),
-    EMCNN_SPLIT_PHASE(32, 64, 4, true, 16, 32, 8, 4, 16, 2), EMCNN_SPLIT_PHASE(32, 64, 4, true, 8, 32, 8, 4, 16, 2),
+    EMCNN_SPLIT_GROUP(32, 64, 4, 8, 8, 4, 16, 2, 20, 20), EMCNN_SPLIT_GROUP(32, 64, 4, 12, 8, 4, 16, 1, 28, 29.8),
+    EMCNN_SPLIT_GROUP(32, 64, 4, 4, 8, 4, 16, 2, 13, 12.3),
+    EMCNN_SPLIT_PHASE(32, 64, 4, true, 16, 32, 8, 4, 16, 2, 21.5, 20.6),
+    EMCNN_SPLIT_PHASE(32, 64, 4, true, 8, 32, 8, 4, 16, 2, 13, 12),
     // MaskExtend (4 x 800^2): twelve maps, no max filter; 32 -> 80 (0.58 ms; 4-row
     // members 0.61), 40 -> 96 in 8-channel stages (0.81; 0.94), 48 -> 112 (1.02 with
     // 8 consumer waves, 1.05 with 4 of twice the m-blocks), 56 -> 128 (1.32; 1.32).
     // 8-row members of the two widest would need 112 and 128 accumulators and spill.
-    EMCNN_SPLIT_PHASE(12, 64, 4, false, 16, 32, 8, 4, 16, 2), EMCNN_SPLIT_PHASE(12, 64, 4, false, 8, 32, 8, 4, 16, 2),
-    EMCNN_SPLIT_GROUP(32, 80, 4, 8, 8, 4, 16, 1), EMCNN_SPLIT_GROUP(32, 80, 4, 4, 8, 4, 16, 2),
-    EMCNN_SPLIT_GROUP(40, 96, 4, 8, 8, 4, 8, 2), EMCNN_SPLIT_GROUP(40, 96, 4, 4, 8, 4, 8, 2),
-    EMCNN_SPLIT_GROUP(48, 112, 4, 4, 8, 4, 16, 2), EMCNN_SPLIT_GROUP(56, 128, 4, 4, 8, 4, 8, 2),
+    EMCNN_SPLIT_PHASE(12, 64, 4, false, 16, 32, 8, 4, 16, 2, 14, 14.5),
+    EMCNN_SPLIT_PHASE(12, 64, 4, false, 8, 32, 8, 4, 16, 2, 8, 7.4),
+    EMCNN_SPLIT_GROUP(32, 80, 4, 8, 8, 4, 16, 1, 28, 29.7), EMCNN_SPLIT_GROUP(32, 80, 4, 4, 8, 4, 16, 2, 15, 15.8),
+    EMCNN_SPLIT_GROUP(40, 96, 4, 8, 8, 4, 8, 2, 39, 39.9), EMCNN_SPLIT_GROUP(40, 96, 4, 4, 8, 4, 8, 2, 22, 23.5),
+    EMCNN_SPLIT_GROUP(48, 112, 4, 4, 8, 4, 16, 2, 0, 0), EMCNN_SPLIT_GROUP(56, 128, 4, 4, 8, 4, 8, 2, 0, 0),
 };
 
 int split_variant_count() { return (int)(sizeof(kSplit) / sizeof(kSplit[0])); }

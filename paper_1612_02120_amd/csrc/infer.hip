@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <fstream>
@@ -105,6 +106,48 @@ static LayerJob make_job(const ExecLayer& L, const void* in, void* out, int z, i
 
 static int64_t job_items(const LayerJob& j) { return (int64_t)j.z * j.tiles_y * j.tiles_x; }
 
+// Select the layer's variant for a launch: the one whose measured costs
+// (TileCost) give the least time for the items it would cut the work into.
+// Large tiles have the better rate (less halo, more work per weight read), small
+// ones fill the chip: a launch takes as many rounds of one item per CU as its
+// busiest CU gets, where a CU holds one or two workgroups, and its share of the
+// items at the full rate where it holds more. Net B in FP32 on one 160 x 160
+// slice: conv2 48 us with the 24 x 32 tiles that are the fastest on 32 x 1024^2,
+// 18 with 8 x 16. items: the work items under the layer's selected variant.
+template <class Items>
+static void pick_variant(Net* net, ExecLayer& L, Items items) {
+  if (L.pinned || layer_cost(L).rate <= 0.f) return;
+  const int dflt = L.variant;
+  const auto cost = [&](int c) {
+    if (!select_variant(L, c)) return 1e300;
+    const TileCost& t = layer_cost(L);
+    if (t.rate <= 0.f) return 1e300;
+    const int occ = layer_occupancy(net, L);
+    const double q = (double)items() / net->num_cus;
+    const double rounds = occ <= 2 ? std::ceil(q / occ) * occ : q;
+    return q <= 1.0 ? (double)t.lone : std::max<double>(t.lone, rounds * t.rate);
+  };
+  int best = dflt;
+  double best_us = 0.95 * cost(dflt);  // the costs are no better than that: the default unless it clearly loses
+  for (int c : L.candidates) {
+    if (c == dflt) continue;
+    const double us = cost(c);
+    if (us < best_us) {
+      best_us = us;
+      best = c;
+    }
+  }
+  select_variant(L, best);
+}
+
+// The layer's selected variant is put back when this goes out of scope.
+struct KeepVariant {
+  ExecLayer& L;
+  const int variant;
+  explicit KeepVariant(ExecLayer& l) : L(l), variant(l.variant) {}
+  ~KeepVariant() { select_variant(L, variant); }
+};
+
 static hipEvent_t pool_event(Net* net) {
   if (!net->event_pool.empty()) {
     hipEvent_t e = net->event_pool.back();
@@ -173,7 +216,8 @@ static int run_region(Net* net, const uint8_t* in, int64_t in_rs, int64_t in_zs,
   const bool fused = first_fused(net);
   unsigned char* buf[2] = {buf0, buf1};
   for (int l = fused ? 1 : 0; l < nl; ++l) {
-    const ExecLayer& L = net->layers[l];
+    ExecLayer& L = net->layers[l];
+    const KeepVariant keep(L);
     // a fused layer 1 reads the uint8 input with layer 0's geometry
     const int li = (l == 1 && fused) ? 0 : l;
     const void* lin = (li == 0) ? (const void*)in : (const void*)buf[(l - 1) % 2];
@@ -181,31 +225,31 @@ static int run_region(Net* net, const uint8_t* in, int64_t in_rs, int64_t in_zs,
     int64_t lin_rs = in_rs, lin_zs = in_zs, lout_rs = out_rs, lout_zs = out_zs;
     if (li > 0) map_strides(net->layers[li - 1], d.hin[li], d.win[li], lin_rs, lin_zs);
     if (l < nl - 1) map_strides(L, d.hout[l], d.wout[l], lout_rs, lout_zs);
-    const auto launch = [&](const ExecLayer& V, const int32_t* gate) {
-      LayerJob j = make_job(V, lin, out, zc, d.hin[li], d.win[li], lin_rs, lin_zs, d.hout[l], d.wout[l], lout_rs,
-                            lout_zs, 0, gate);
+    const auto job = [&](const int32_t* gate) {
+      return make_job(L, lin, out, zc, d.hin[li], d.win[li], lin_rs, lin_zs, d.hout[l], d.wout[l], lout_rs, lout_zs, 0,
+                      gate);
+    };
+    const auto launch = [&](const int32_t* gate) {
       JobSet js;
       std::memset(&js, 0, sizeof(js));
+      js.single = job(gate);
       js.njobs = 1;
-      js.total_items = job_items(j);
-      js.single = j;
-      return launch_layer(net, V, js, persistent_grid(net, V, js.total_items), st, timed);
+      js.total_items = job_items(js.single);
+      return launch_layer(net, L, js, persistent_grid(net, L, js.total_items), st, timed);
     };
+    pick_variant(net, L, [&] { return job_items(job(nullptr)); });
     int rc;
     if (net->range && !L.first && conv_variant(L.variant)->split) {
       // whichever of the two the maps' range opens; the other finds its gate closed
-      rc = launch(L, &net->range->ok);
-      ExecLayer& M = net->layers[l];
-      const int v0 = M.variant;
-      for (int c : M.candidates)
+      rc = launch(&net->range->ok);
+      for (int c : L.candidates)
         if (!conv_variant(c)->split) {
-          select_variant(M, c);
+          select_variant(L, c);
           break;
         }
-      if (!rc) rc = launch(M, &net->range->bad);
-      select_variant(M, v0);
+      if (!rc) rc = launch(&net->range->bad);
     } else {
-      rc = launch(L, nullptr);
+      rc = launch(nullptr);
     }
     if (rc) return rc;
   }
@@ -397,7 +441,7 @@ int arena_reserve(Net* net, size_t njobs) {
 // (group, layer, region) into the arena from `job_off` on and appends the
 // launches. Returns the workspace bytes needed in ws_need.
 int plan_regions(Net* net, const std::vector<Region>& in_regions, size_t job_off, std::vector<Launch>& launches,
-                 size_t& njobs_used, size_t& ws_need, bool dry) {
+                 size_t& njobs_used, size_t& ws_need, bool dry, bool fixed) {
   const int nl = (int)net->layers.size();
   // per-region geometry; regions with too many slices are split by z
   std::vector<Region> regs;
@@ -472,7 +516,18 @@ int plan_regions(Net* net, const std::vector<Region>& in_regions, size_t job_off
     }
     const bool fused = first_fused(net);
     for (int l = fused ? 1 : 0; l < nl; ++l) {
-      const ExecLayer& L = net->layers[l];
+      ExecLayer& L = net->layers[l];
+      const KeepVariant keep(L);
+      if (!fixed) {
+        const int li = (l == 1 && fused) ? 0 : l;
+        pick_variant(net, L, [&] {
+          int64_t n = 0;
+          for (int t = G.first; t < G.second; ++t)
+            n += job_items(make_job(L, nullptr, nullptr, regs[t].z, dims[t].hin[li], dims[t].win[li], 0, 0,
+                                    dims[t].hout[l], dims[t].wout[l], 0, 0, 0, nullptr));
+          return n;
+        });
+      }
       const size_t first = pos;
       int64_t item0 = 0;
       for (int t = G.first; t < G.second; ++t) {
@@ -840,7 +895,7 @@ extern "C" int cnn_infer_batch(cnn_net* h, const cnn_tile* tiles, int32_t n, voi
       use(net->class_variants[c]);
       std::vector<Launch> none;
       size_t u = 0, wn = 0;
-      rc = plan_regions(net, byc[c], 0, none, u, wn, true);
+      rc = plan_regions(net, byc[c], 0, none, u, wn, true, true);
       ws_max = std::max(ws_max, wn);
     }
     use(defaults);
@@ -851,7 +906,7 @@ extern "C" int cnn_infer_batch(cnn_net* h, const cnn_tile* tiles, int32_t n, voi
       if (byc[c].empty()) continue;
       use(net->class_variants[c]);
       size_t u = 0;
-      rc = plan_regions(net, byc[c], used, launches, u, ws_need);
+      rc = plan_regions(net, byc[c], used, launches, u, ws_need, false, true);
       used += u;
     }
     use(defaults);
@@ -932,7 +987,7 @@ extern "C" int cnn_autotune(cnn_net* h, int64_t H, int64_t W, const char* cache_
     if (net->layers[l].candidates.size() > 1 && chosen[l] < 0) all = false;
   if (all) {
     for (int l = 0; l < nl; ++l)
-      if (chosen[l] >= 0) select_variant(net->layers[l], chosen[l]);
+      if (chosen[l] >= 0) net->layers[l].pinned = select_variant(net->layers[l], chosen[l]);
     return CNN_OK;
   }
   // synthetic slice (fixed LCG pattern) and per-layer buffers
@@ -986,7 +1041,7 @@ extern "C" int cnn_autotune(cnn_net* h, int64_t H, int64_t W, const char* cache_
   for (int l = 0; l < nl && !rc; ++l) {
     ExecLayer& L = net->layers[l];
     if (chosen[l] >= 0) {
-      select_variant(L, chosen[l]);
+      L.pinned = select_variant(L, chosen[l]);
       continue;
     }
     if (L.candidates.size() < 2 || (l == 0 && fused)) continue;  // a fused layer 0 is never launched
@@ -1041,6 +1096,7 @@ extern "C" int cnn_autotune(cnn_net* h, int64_t H, int64_t W, const char* cache_
       }
     }
     select_variant(L, rc ? def : best);
+    L.pinned = !rc;
     chosen[l] = L.variant;
   }
   cleanup();
@@ -1130,7 +1186,7 @@ extern "C" int cnn_autotune_batch(cnn_net* h, const cnn_tile* tiles, int32_t n, 
       int r = arena_reserve(net, count_region_jobs(net, rc_regs));
       std::vector<Launch> launches;
       size_t used = 0, wn = 0;
-      if (!r) r = plan_regions(net, rc_regs, 0, launches, used, wn);
+      if (!r) r = plan_regions(net, rc_regs, 0, launches, used, wn, false, true);
       if (!r) r = submit(net, launches, 0, used, st, false);
       return r;
     };
@@ -1256,6 +1312,7 @@ extern "C" int cnn_set_variant(cnn_net* h, int32_t layer, const char* name) {
   ExecLayer& L = net->layers[layer];
   const int c = candidate_name_index(L, name);
   if (c < 0 || !select_variant(L, c)) return fail(CNN_EINVAL, std::string("cnn_set_variant: no candidate ") + name);
+  L.pinned = true;
   net->class_variants.clear();  // an explicit choice applies to batches too
   return CNN_OK;
 }

@@ -29,6 +29,7 @@ struct ExecLayer {
   int stride = 1;  // output stride of a first layer (2: only where a 2x subsample keeps pixels)
   int spaced = 0;  // conv of a stride-2 pool net: tiled per phase, max-filter spacing from the job
   int variant = -1;
+  bool pinned = false;  // chosen by the caller or the autotuner: not by a launch's size
   std::vector<int> candidates;
   std::vector<void*> wpacks;  // packed weights per candidate (layouts differ between variants)
   void* wpack = nullptr;      // == wpacks[index of variant in candidates]
@@ -93,6 +94,7 @@ struct Net {
   };
   std::vector<Timed> timed;
   std::vector<hipEvent_t> event_pool;
+  std::vector<int> occ_conv, occ_first;  // workgroups per CU of each variant (0: not asked yet)
   // per tile class (kTileClasses), the variant of every layer that batched
   // submissions use for that class's tiles; empty: the selected variants
   std::vector<std::vector<int>> class_variants;
@@ -147,8 +149,9 @@ size_t count_region_jobs(const Net* net, const std::vector<Region>& regs);
 // Plan the regions' launches into the job arena from job_off on; ws_need
 // receives the workspace bytes they need, which this call allocates (growing
 // frees the previous workspace). dry: compute ws_need only, write nothing.
+// fixed: every layer's selected variant, whatever the size.
 int plan_regions(Net* net, const std::vector<Region>& regs, size_t job_off, std::vector<Launch>& launches,
-                 size_t& njobs_used, size_t& ws_need, bool dry = false);
+                 size_t& njobs_used, size_t& ws_need, bool dry = false, bool fixed = false);
 int submit(Net* net, const std::vector<Launch>& launches, size_t job_off, size_t njobs, hipStream_t st, bool graph);
 int launch_layer(Net* net, const ExecLayer& L, const JobSet& js, int grid, hipStream_t st, bool timed = true);
 int check_device(const Net* net);
@@ -168,6 +171,11 @@ bool layer_phase_groups(const ExecLayer& L);  // work items are groups of four p
 const void* layer_fn(const ExecLayer& L);
 const char* layer_name(const ExecLayer& L);
 int persistent_grid(Net* net, const ExecLayer& L, int64_t total_items);
+// Workgroups of layer L's selected variant that fit a CU.
+int layer_occupancy(Net* net, const ExecLayer& L);
+inline const TileCost& layer_cost(const ExecLayer& L) {
+  return L.first ? first_variant(L.variant)->cost : conv_variant(L.variant)->cost;
+}
 // Select candidate `variant` of layer L (binds its packed weights).
 bool select_variant(ExecLayer& L, int variant);
 // True when layer 1 runs a fused variant: it reads the uint8 input and computes

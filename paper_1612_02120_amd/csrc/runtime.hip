@@ -765,11 +765,18 @@ bool first_fused(const Net* net) {
   return net->layers.size() > 1 && !net->layers[1].first && conv_variant(net->layers[1].variant)->fused > 0;
 }
 
-int persistent_grid(Net* net, const ExecLayer& L, int64_t total_items) {
-  int per_cu = 0;
-  const void* fn = layer_fn(L);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, layer_threads(L), 0) != hipSuccess || per_cu < 1)
+int layer_occupancy(Net* net, const ExecLayer& L) {
+  std::vector<int>& occ = L.first ? net->occ_first : net->occ_conv;
+  if (occ.empty()) occ.assign(L.first ? first_variant_count() : conv_variant_count(), 0);
+  int& per_cu = occ[L.variant];
+  if (per_cu == 0 &&
+      (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, layer_fn(L), layer_threads(L), 0) != hipSuccess || per_cu < 1))
     per_cu = 1;
+  return per_cu;
+}
+
+int persistent_grid(Net* net, const ExecLayer& L, int64_t total_items) {
+  const int per_cu = layer_occupancy(net, L);
   int64_t cap = (int64_t)net->num_cus * per_cu;
   cap = std::max<int64_t>(8, cap / 8 * 8);
   int64_t want = (total_items + 7) / 8 * 8;

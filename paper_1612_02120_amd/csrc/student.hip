@@ -1372,7 +1372,7 @@ extern "C" int student_infer_with_fallback(cnn_student* h, cnn_net* th, const ui
   // 4) teacher re-run of flagged tiles (unflagged tiles are skipped by the gate);
   // the job table of both passes went up with the first submission
   for (const Launch& la : l2) {
-    rc = launch_layer(net, net->layers[la.layer], la.js, la.grid, st);
+    rc = launch_planned(net, la, st);
     if (rc) return rc;
   }
   if ((e = hipEventRecord(net->arena[net->cur].done, st)) != hipSuccess) return hip_fail(e, "fallback: hipEventRecord");
