@@ -17,6 +17,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/emcnn.h"
@@ -108,156 +109,177 @@ __global__ __launch_bounds__((TY * TX)) void student_fused(const uint8_t* __rest
 
 // BF16 mode on MFMA. Both convs run as D = W X on 16x16x32 bf16 MFMAs: the
 // working weights and h1 are bf16 values and uint8 inputs are exact in bf16,
-// so every product is exact and sums are FP32 (in the MFMA's order). The 8
-// output channels fill half of the MFMA's 16 rows: lane (g, n) receives
-// channels 4g..4g+3 of pixel n, lanes g >= 2 the zero-weight rows. One
-// workgroup of 4 waves computes a TY x TX output tile:
-//   input: the uint8 tile converted once to bf16 in LDS (the high half of
-//          the float of a byte, whose low half is zero);
-//   conv1: h1 for (TY+2) x (16 ceil((TX+2)/16)) positions, one MFMA per 16
-//          pixels (K = 25 taps padded to 32), bias, ReLU, bf16 -> LDS
-//          (16 bytes per position: 8 channels); wave w takes the h1 rows
-//          w, w + 4, ..., so its LDS offsets are a per-lane base plus
-//          compile-time immediates;
-//   conv2: K = 9 taps x 8 channels in 3 MFMAs per 16 outputs (taps 4s + g,
-//          padded to 12), one 16-byte LDS read per lane per MFMA;
-//   head:  each lane's 4-channel partial dot; the two real lane groups' sums
-//          are gathered for four m-blocks at a time, so that lane group j
-//          holds m-block j's 16 probabilities and one sigmoid and one store
-//          per lane serve four m-blocks.
-template <int TY, int TX>
-__global__ __launch_bounds__(256) void student_mfma(const uint8_t* in, int64_t in_rs, int64_t in_zs, float* out,
-                                                    int64_t out_rs, int64_t out_zs, int Ho, int Wo, int crop,
-                                                    const float* ww) {
-  constexpr int HR = TY + 2;               // h1 rows
-  constexpr int HMC = (TX + 2 + 15) / 16;  // h1 m-blocks per row
-  constexpr int HC = HMC * 16;             // h1 row pitch (positions)
-  constexpr int IR = HR + 4, IC = HC + 4;  // input tile (covers the padded h1 columns)
-  constexpr int OMC = TX / 16;             // output m-blocks per row
-  static_assert(TX % 16 == 0, "output m-blocks of 16 pixels");
-  static_assert(OMC == 4 && TY % 4 == 0, "wave w owns output m-block column w; rows in groups of four");
-  __shared__ __attribute__((aligned(16))) unsigned short xin[IR * IC];  // bf16 bits
-  __shared__ __attribute__((aligned(16))) unsigned char h1[HR * HC * 16];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+// so every product is exact and sums are FP32 (in the MFMA's order).
+//
+// The 8 channels fill the 16 rows of an MFMA as two adjacent pixels: column n is
+// the pixel pair 2n, 2n + 1, rows 0..7 the channels of pixel 2n and rows 8..15
+// those of pixel 2n + 1, whose weights are the same ones one tap to the right. A
+// pair's window is 5 x 6 = 30 of conv1's 32 K slots (one pixel's 25), and 3 x 4
+// taps x 8 channels = 96 of conv2's three MFMAs (one pixel's 72): one MFMA gives
+// conv1 at 32 positions and three give 32 outputs, half the instructions of one
+// pixel per column. The K slots are laid out so that an operand is what LDS holds:
+//   conv1: lane group g reads the six pixels of window row g (three dwords of bf16
+//          pairs), and pixels 2g, 2g + 1 of row 4 (one dword; g = 3: zero weights);
+//   conv2: MFMA i, lane group g reads the 8 channels of h1 pixel (i, g), 16 bytes.
+// A wave computes a strip of 62 output columns (64 of h1, two MFMA columns of 32)
+// from the top down, with rings of its own in LDS (8 input rows, 4 h1 rows): no
+// barrier, no halo rows but the strip's first six, and the loads of the row after
+// next in flight. One sigmoid and one store per lane and row. On 8 x 2048^2: 312 us
+// with tiles of 16 x 64 outputs shared by four waves and one pixel per column
+// (2.6 times the vector instructions), MEASURED now; 55 us of MFMA issue became 28.
+constexpr int SW = 62;            // output columns of a strip
+constexpr int SXP = 144;          // bytes per input ring row: 34 pixel pairs of bf16, padded
+constexpr int SHP = 66 * 16;      // bytes per h1 ring row: 64 pixels of 8 channels, and what the last pair over-reads
+constexpr int SLDS = 8 * SXP + 4 * SHP;
+__global__ __launch_bounds__(256) void student_strip(const uint8_t* in, int64_t in_rs, int64_t in_zs, float* out,
+                                                     int64_t out_rs, int64_t out_zs, int Ho, int Wo, int crop,
+                                                     const float* ww, int rows, int nsy, int nsx, int nstrips) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds_all[4 * SLDS];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int strip = blockIdx.x * 4 + wave;
+  if (strip >= nstrips) return;
+  unsigned char* const xr = lds_all + wave * SLDS;
+  unsigned char* const hr = xr + 8 * SXP;
   const int g = lane >> 4, n16 = lane & 15;
-  const int y0 = blockIdx.y * TY, x0 = blockIdx.x * TX, z = blockIdx.z;
+  const int sx = strip % nsx, sy = (strip / nsx) % nsy, z = strip / (nsx * nsy);
+  const int x0 = sx * SW, y0 = sy * rows;
+  const int nout = min(rows, Ho - y0);
+  // the strip's input: 68 columns from x0 + crop, clamped to the last valid row and column
+  const int ylim = Ho + 2 * crop + 5, xlim = Wo + 2 * crop + 5;
   const gbyte* src = gin(in) + (int64_t)z * in_zs;
-  const int hin_lim = Ho + 2 * crop + 6, win_lim = Wo + 2 * crop + 6;  // input dims implied by the output
-  {
-    // rows wave + 4k, columns lane + 64 m: all byte loads issued before any is used
-    constexpr int NK = (IR + 3) / 4, NM = (IC + 63) / 64;
-    unsigned int b[NK][NM];
+  const int ca = min(x0 + crop + 2 * lane, xlim), cb = min(x0 + crop + 2 * lane + 1, xlim);  // this lane's pixel pair
+  auto load = [&](int r, unsigned& a, unsigned& b) __attribute__((always_inline)) {
+    const gbyte* row = src + (int64_t)min(y0 + crop + r, ylim) * in_rs;
+    a = row[ca];
+    b = row[cb];
+  };
+  unsigned pa[2], pb[2];  // rows r and r + 1 ahead of their use
+  load(0, pa[0], pb[0]);
+  load(1, pa[1], pb[1]);
+  // weight fragments: lane (g, m) holds row m's K slots 8g..8g+7 (every load is
+  // unconditional, from a clamped index, and the padding is selected afterwards,
+  // so that all of them are in flight together)
+  const int ch = n16 & 7, dx = n16 >> 3;
+  bf16x8 w1f, w2f[3];
 #pragma unroll
-    for (int k = 0; k < NK; ++k) {
-      const gbyte* row = src + (int64_t)min(y0 + crop + wave + 4 * k, hin_lim - 1) * in_rs;
-#pragma unroll
-      for (int m = 0; m < NM; ++m) b[k][m] = row[min(x0 + crop + lane + 64 * m, win_lim - 1)];
-    }
-#pragma unroll
-    for (int k = 0; k < NK; ++k)
-#pragma unroll
-      for (int m = 0; m < NM; ++m)
-        if (wave + 4 * k < IR && lane + 64 * m < IC)
-          xin[(wave + 4 * k) * IC + lane + 64 * m] =
-              (unsigned short)(__builtin_bit_cast(unsigned int, (float)b[k][m]) >> 16);
+  for (int e = 0; e < 8; ++e) {
+    const int i = e < 6 ? g : 4, j = (e < 6 ? e : 2 * g + e - 6) - dx;
+    const bool there = j >= 0 && j < 5 && !(e >= 6 && g == 3);
+    const float v = ldf(ww, OFF_W1 + ch * 25 + i * 5 + min(max(j, 0), 4));
+    w1f[e] = (__bf16)(there ? v : 0.f);
   }
-  // weight fragments: lane (g, c) holds output channel c's K elements 8g..8g+7
-  // (every load is unconditional, from a clamped index, and the padding is
-  // selected afterwards, so that all of them are in flight together)
-  const bool realc = n16 < S_C;
-  const int c8 = realc ? n16 : 0;
-  float w1v[8], w2v[3][8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) w1v[e] = ldf(ww, OFF_W1 + c8 * 25 + min(8 * g + e, 24));
+  for (int i = 0; i < 3; ++i)
 #pragma unroll
-  for (int s3 = 0; s3 < 3; ++s3)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) w2v[s3][e] = ldf(ww, OFF_W2 + (c8 * 8 + e) * 9 + min(4 * s3 + g, 8));
-  const bool realg = g < 2;  // this lane's rows are real channels 4g..4g+3
-  float b1[4], b2[4], wh[4];
+    for (int e = 0; e < 8; ++e) {
+      const int j = g - dx;
+      const float v = ldf(ww, OFF_W2 + (ch * 8 + e) * 9 + i * 3 + min(max(j, 0), 2));
+      w2f[i][e] = (__bf16)(j >= 0 && j < 3 ? v : 0.f);
+    }
+  // accumulator row 4g + k is channel 4 (g & 1) + k of pixel 2n + (g >> 1)
+  f4 b1, b2, wh;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const int co = realg ? 4 * g + k : 0;
+    const int co = 4 * (g & 1) + k;
     b1[k] = ldf(ww, OFF_B1 + co);
     b2[k] = ldf(ww, OFF_B2 + co);
     wh[k] = ldf(ww, OFF_WH + co);
-    wh[k] = realg ? wh[k] : 0.f;
   }
   const float bh = ldf(ww, OFF_BH);
-  bf16x8 w1f, w2f[3];
+  // A pair's window holds a pixel that one of the two has zero weights for: were its
+  // h1 infinite, the product would be NaN. Weights that bound h1 well below the
+  // largest bf16 (any but a diverged student's) rule that out; others take the loop
+  // that gives each pixel of the pair its own three MFMAs.
+  float top = 0.f;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) w1f[e] = (__bf16)(realc && 8 * g + e < 25 ? w1v[e] : 0.f);
+  for (int e = 0; e < 8; ++e) top += 255.f * fabsf((float)w1f[e]);
 #pragma unroll
-  for (int s3 = 0; s3 < 3; ++s3)
+  for (int k = 0; k < 4; ++k) top += fabsf(b1[k]);
+  const bool apart = __any(!(top < 1e36f));
+  // per-lane bases: conv1's pixels of row 4 (g = 3: zero weights, any pixels), h1 writes and reads
+  const int x4 = (n16 + (g < 3 ? g : 0)) * 4;
+  unsigned char* const hw = hr + (2 * n16 + (g >> 1)) * 16 + (g & 1) * 8;
+  const unsigned char* const hrd = hr + (2 * n16 + g) * 16;
+  // the lane's output column after the exchange below: MFMA column g & 1, pixel 2n + (g >> 1)
+  const int xo = 32 * (g & 1) + 2 * n16 + (g >> 1);
+  const bool col_ok = xo < SW && x0 + xo < Wo;
+  gbyte* const od = gout(out) + ((int64_t)z * out_zs + (int64_t)y0 * out_rs + x0 + xo) * 4;
+
+  // LDS between lanes of one wave needs no wait (its accesses stay in order), only
+  // that the compiler keeps that order
+  auto in_order = []() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  const int total = nout + 6;
+  auto rows_down = [&](auto apart_c) __attribute__((always_inline)) {
+    for (int base = 0; base < total; base += 8) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) w2f[s3][e] = (__bf16)(realc && 4 * s3 + g < 9 ? w2v[s3][e] : 0.f);
-  // per-lane bases of the tap reads in the bf16 tile, at h1 row `wave`
-  // (taps past 25 read element 0 of that row: zero weights)
-  const unsigned short* xb[8];
+      for (int p = 0; p < 8; ++p) {
+        const int r = base + p;  // input row
+        if (r >= total) break;
+        // uint8 -> bf16 is exact: the float of an integer below 256 has a zero low half
+        if (lane < 34)
+          *reinterpret_cast<uint32_t*>(xr + p * SXP + lane * 4) =
+              __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, (float)pb[p & 1]),
+                                    __builtin_bit_cast(unsigned, (float)pa[p & 1]), 0x07060302u);
+        load(r + 2, pa[p & 1], pb[p & 1]);
+        in_order();
+        if (r < 4) continue;
+        // ---- conv1: h1 row r - 4 from input rows r - 4 .. r
+        const unsigned char* const xg = xr + ((p + 4 + g) & 7) * SXP + n16 * 4;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int t = 8 * g + e;
-    xb[e] = xin + wave * IC + n16 + (t < 25 ? (t / 5) * IC + t % 5 : 0);
-  }
-  unsigned char* const h1w = h1 + ((wave * HC + n16) * 16 + g * 8);
-  __syncthreads();
-  // ---- conv1: h1 rows wave + 4k
-#pragma unroll
-  for (int k = 0; k < (HR + 3) / 4; ++k) {
-    if (wave + 4 * k < HR) {
-#pragma unroll
-      for (int mc = 0; mc < HMC; ++mc) {
-        const int off = 4 * k * IC + mc * 16;  // compile-time
-        u4v pk;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          pk[e] = (unsigned)xb[2 * e][off] | ((unsigned)xb[2 * e + 1][off] << 16);
-        const f4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f, __builtin_bit_cast(bf16x8, pk),
-                                                             f4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        if (realg) {
-          const __bf16 h0 = (__bf16)s_relu(d[0] + b1[0]), h1v = (__bf16)s_relu(d[1] + b1[1]);
-          const __bf16 h2 = (__bf16)s_relu(d[2] + b1[2]), h3 = (__bf16)s_relu(d[3] + b1[3]);
-          const u2v wv = {(unsigned)__builtin_bit_cast(unsigned short, h0) |
-                              ((unsigned)__builtin_bit_cast(unsigned short, h1v) << 16),
-                          (unsigned)__builtin_bit_cast(unsigned short, h2) |
-                              ((unsigned)__builtin_bit_cast(unsigned short, h3) << 16)};
-          st<u2v>(h1w + (4 * k * HC + mc * 16) * 16, wv);
+        for (int c = 0; c < 2; ++c) {
+          const uint32_t* q = reinterpret_cast<const uint32_t*>(xg + c * 64);
+          const u4v xv = {q[0], q[1], q[2], *reinterpret_cast<const uint32_t*>(xr + p * SXP + x4 + c * 64)};
+          const f4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f, __builtin_bit_cast(bf16x8, xv), f4{0.f, 0.f, 0.f, 0.f}, 0,
+                                                               0, 0);
+          typedef float f2v __attribute__((ext_vector_type(2)));
+          typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+          auto pack = [](float lo, float hi) __attribute__((always_inline)) {
+            return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){lo, hi}, bf16x2v));
+          };
+          st<u2v>(hw + (p & 3) * SHP + c * 512, u2v{pack(s_relu(d[0] + b1[0]), s_relu(d[1] + b1[1])),
+                                                    pack(s_relu(d[2] + b1[2]), s_relu(d[3] + b1[3]))});
         }
+        in_order();
+        if (r < 6) continue;
+        // ---- conv2 and head: output row r - 6 from h1 rows r - 6 .. r - 4
+        float part[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          f4 acc = f4{0.f, 0.f, 0.f, 0.f}, acc1 = acc;
+#pragma unroll
+          for (int i = 0; i < 3; ++i) {
+            const u4v h = ld<u4v>(hrd + ((p + 2 + i) & 3) * SHP + c * 512);
+            const u4v h0 = apart_c.value && g == 3 ? u4v{0, 0, 0, 0} : h;
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2f[i], __builtin_bit_cast(bf16x8, h0), acc, 0, 0, 0);
+            if constexpr (apart_c.value) {
+              const u4v h1 = g == 0 ? u4v{0, 0, 0, 0} : h;
+              acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2f[i], __builtin_bit_cast(bf16x8, h1), acc1, 0, 0, 0);
+            }
+          }
+          if (apart_c.value && g >= 2) acc = acc1;
+          part[c] = 0.f;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) part[c] = fmaf(wh[k], s_relu(acc[k] + b2[k]), part[c]);
+        }
+        // channels 0..3 (even lane groups) and 4..7 (odd ones) of each pixel: even
+        // groups keep MFMA column 0, odd ones column 1
+        const bool odd = g & 1;
+        const float give = odd ? part[0] : part[1], keep = odd ? part[1] : part[0];
+        const float zl = keep + __shfl_xor(give, 16) + bh;
+        const float e = expf(-fabsf(zl));
+        const float prob = (zl >= 0.0f ? 1.0f : e) / (1.0f + e);
+        if (col_ok) st<float>(od + (int64_t)(r - 6) * out_rs * 4, prob);
       }
     }
-  }
-  __syncthreads();
-  // ---- conv2 + head: output rows 0..TY-1 of m-block column `wave`
-  int hoff[3];
-#pragma unroll
-  for (int s3 = 0; s3 < 3; ++s3) {
-    const int t = 4 * s3 + g < 9 ? 4 * s3 + g : 0;  // padded taps: zero weights
-    hoff[s3] = ((t / 3) * HC + t % 3) * 16;
-  }
-  const unsigned char* const b0w = h1 + (wave * 16 + n16) * 16;
-  const int x = x0 + wave * 16 + n16;
-#pragma unroll
-  for (int grp = 0; grp < TY / 4; ++grp) {
-    float mine = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const unsigned char* b0 = b0w + (4 * grp + j) * HC * 16;
-      f4 acc = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s3 = 0; s3 < 3; ++s3)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2f[s3], ld<bf16x8>(b0 + hoff[s3]), acc, 0, 0, 0);
-      float part = 0.f;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) part = fmaf(wh[k], s_relu(acc[k] + b2[k]), part);
-      // channels 0..3 (lane group 0) + 4..7 (lane group 1) of pixel n16
-      const float sum = __shfl(part, n16) + __shfl(part, n16 + 16);
-      mine = g == j ? sum : mine;
-    }
-    const int y = y0 + 4 * grp + g;
-    if (y < Ho && x < Wo) st<float>(gout(out) + ((int64_t)z * out_zs + (int64_t)y * out_rs + x) * 4,
-                                   s_sigmoid(mine + bh));
-  }
+  };
+  if (apart)
+    rows_down(std::true_type{});
+  else
+    rows_down(std::false_type{});
 }
 
 // ------------------------------------------------------------------ training kernels
@@ -1200,11 +1222,16 @@ static int student_launch(Student* s, const uint8_t* vol, int64_t Z, int64_t H, 
                           int64_t out_zs, int Ho, int Wo, int crop, hipStream_t st) {
   hipError_t e;
   if (s->prec == CNN_PREC_BF16) {
-    constexpr int TY = 16, TX = 64;
-    dim3 grid((Wo + TX - 1) / TX, (Ho + TY - 1) / TY, (unsigned)Z);
-    hipLaunchKernelGGL((student_mfma<TY, TX>), grid, dim3(256), 0, st, vol, W, H * W, out, out_rs, out_zs, Ho, Wo, crop,
-                       s->ww);
-    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "student_mfma");
+    // strips as tall as still give every SIMD four (a strip computes six input and
+    // two h1 rows beyond its own)
+    const int64_t nsx = (Wo + SW - 1) / SW;
+    int rows = 128;
+    while (rows > 8 && Z * nsx * ((Ho + rows - 1) / rows) < 4096) rows /= 2;
+    const int64_t nsy = (Ho + rows - 1) / rows, n = Z * nsx * nsy;
+    if (n > 2147483647ll - 4) return fail(CNN_EUNSUPPORTED, "student: volume too large");
+    hipLaunchKernelGGL(student_strip, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, vol, W, H * W, out, out_rs, out_zs,
+                       Ho, Wo, crop, s->ww, rows, (int)nsy, (int)nsx, (int)n);
+    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "student_strip");
     return CNN_OK;
   }
   constexpr int TY = 16, TX = 16;
