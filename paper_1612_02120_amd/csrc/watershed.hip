@@ -12,33 +12,32 @@
 // both parts: a non-seed points along its descent, a seed into its
 // component's tree. Roots are fixed points: component minima and non-seed
 // local minima.
-//   ws_init   one pass: a seed points to the first seed of its run along x
-//             (the run's least index), any other voxel to next(v). The x-links
-//             of the seed graph are then made.
-//   ws_union  one pass over the seeds: runs adjacent along y or z are united
+//   ws_tile   a workgroup per tile of 4 x 8 x 128 voxels, its forest in LDS. A seed
+//             points to the first seed of its run along x in the tile, any other
+//             voxel to next(v); runs adjacent along y or z in the tile are united
 //             by a lock-free union-find (the structure of ECL-CC): find both
 //             roots, hook the larger root under the smaller with a
-//             compare-and-swap that only succeeds while it is still a root,
-//             and retry from the new roots when another thread hooked it
-//             first. Two runs that touch are united once, at the first column
-//             where they do (the pair one column left, when both are seeds,
-//             joins the same two runs). A seed's parent index only
-//             decreases, so every component ends rooted at its least index.
-//   ws_flat   every run's first seed finds its component's root r, halving the
-//             path as it goes, and takes ~r, which ends a walk.
-//   ws_label  every voxel follows its parents to a run's ~r (a seed in two
-//             steps, a non-seed after its descent) or to a local minimum r, and
-//             takes r + 1. Nothing changes the forest any more.
-// Path halving points a node at its grandparent, an ancestor in the same
-// tree, so concurrent finds stay valid; it never writes a root.
+//             compare-and-swap that only succeeds while it is still a root, and
+//             retry from the new roots when another thread hooked it first. Then
+//             every voxel follows its parents as far as the tile goes, and a[]
+//             takes where it got: its tile component's least voxel, a local
+//             minimum, or the voxel of another tile that its descent goes on at.
+//   ws_border the same union-find on a[] for seeds that touch across the faces of
+//             tiles. Of touching pairs that are linked anyway through their
+//             neighbours' pair (one column left, one row up) one is united.
+//   ws_label  every voxel follows its parents to its root r, and takes r + 1.
+// A seed's parent index only decreases, so every component ends rooted at its
+// least index. Path halving points a node at its grandparent, an ancestor in the
+// same tree, so concurrent finds stay valid; it never writes a root.
 //
-// Every kernel gives a row to a wave, four consecutive columns to a lane, as one
-// 16-byte access where rows and pointers allow it. On a 32 x 1012^2 membrane map
-// with seeds below 0.05 (44 % of the voxels): ws_init 90 us, ws_union 220-234, ws_flat
-// 55, ws_label 227; 1.57 ms in all when a row was a workgroup, one column a
-// thread, and ws_label halved paths from every voxel (ws_init 228, ws_union 392,
-// ws_label 944 us). ws_init moves 0.26 GB, the rate of a large copy; the other
-// passes are chains of dependent loads and, in ws_union, 1.4 M compare-and-swaps.
+// A wave works on rows, four consecutive columns to a lane, as one 16-byte access
+// where rows and pointers allow it. On a 32 x 1012^2 membrane map
+// with seeds below 0.05 (44 % of the voxels): ws_tile 173 us (reading, links and
+// writing 93, unions 43, walks 40), ws_border 59, ws_label 109. With the whole forest
+// in memory, links, unions, the flattening of runs and walks to the root were passes
+// of 90, 220-234, 55 and 227 us; a step of a walk costs a trip to the L2 or the memory
+// there, and every union is one of 1.4 M compare-and-swaps, on one address where a
+// volume is one component (2 M voxels: 350 us per call, in tiles 69).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -59,8 +58,7 @@ struct Vol3 {
 // older value is an ancestor all the same, and a root that has been hooked since
 // shows in the compare-and-swap, whose answer the walk goes on from. (Past the
 // caches, the root of a large component is one address that every find of every
-// CU waits for: ws_union 268 us there, 217-234 here, and 259 against 111-128 on a
-// volume of 2 M voxels in one component.)
+// CU waits for: unions over a whole forest in memory took 268 us there, 217-234 here.)
 __device__ __forceinline__ int32_t wa(const int32_t* a, int64_t v) {
   return __hip_atomic_load(a + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -89,6 +87,9 @@ __device__ __forceinline__ unsigned below4(f4 q, int n, float t) {
   return m;
 }
 
+// Columns per step of a wave.
+constexpr int WC = 256;
+
 // body(row) for the rows of this wave: groups of four rows, one per wave of a
 // workgroup, dealt out so that consecutive groups run on the same XCD (workgroup
 // b on XCD b % 8) and its L2 serves the rows that neighbours share.
@@ -101,78 +102,169 @@ __device__ __forceinline__ void wave_rows(unsigned nrow, Body body) {
   }
 }
 
-// Columns per step of a wave.
-constexpr int WC = 256;
-
-// The last non-seed column before this lane's columns x .. x + 3 (m: which of
-// them are seeds); carry: the last one before the wave's step, updated.
-__device__ __forceinline__ int break_before(unsigned m, int x, int lane, int& carry) {
-  // the last non-seed column of this lane's (columns past the row count as non-seeds)
-  const int last = m == 15u ? -1 : x + 31 - __builtin_clz(~m & 15u);
-  const uint64_t brk = __ballot(m != 15u);
-  const uint64_t before = brk & ((1ull << lane) - 1);
-  const int from = __shfl(last, before ? 63 - __builtin_clzll(before) : 0);
-  const int lb = before ? from : carry;
-  if (brk) carry = __shfl(last, 63 - __builtin_clzll(brk));
-  return lb;
+// Bits of m whose left neighbour's bit is clear, in rows of 32 lanes: the first
+// columns of m's runs.
+__device__ __forceinline__ unsigned half_starts(unsigned m, int l32) {
+  const unsigned left = (unsigned)__shfl_up((int)(m >> 3), 1);
+  return m & ~((m << 1) | (l32 ? left : 0u));
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(256) void ws_init(const float* __restrict__ p, Vol3 g, float t, int32_t* __restrict__ a) {
-  const int HW = g.H * g.W, lane = threadIdx.x & 63;
-  wave_rows((unsigned)(g.Z * g.H), [&](int row) __attribute__((always_inline)) {
-    const int z = row / g.H, y = row - z * g.H, base = row * g.W;
-    int carry = -1;  // the last non-seed column before the step
-    for (int x0 = 0; x0 < g.W; x0 += WC) {
-      const int x = x0 + 4 * lane, v = base + x, n = min(max(g.W - x, 0), 4);
-      const f4 q = row4<VEC>(p, v, n);
-      const f4 zm = row4<VEC>(p, z > 0 ? v - HW : v, n), zp = row4<VEC>(p, z < g.Z - 1 ? v + HW : v, n);
-      const f4 ym = row4<VEC>(p, y > 0 ? v - g.W : v, n), yp = row4<VEC>(p, y < g.H - 1 ? v + g.W : v, n);
-      float left = __shfl_up(q[3], 1), right = __shfl_down(q[0], 1);
-      if (lane == 0 && x > 0) left = ld<float>(gin(p) + ((int64_t)v - 1) * 4);
-      if (lane == 63 && x + 4 < g.W) right = ld<float>(gin(p) + ((int64_t)v + 4) * 4);
-      const unsigned m = below4(q, n, t);
-      int lb = break_before(m, x, lane, carry);
-      i4 out;
+// ---- tiles
+// LDS answers a step of a walk in a tenth of the time of the caches, and a tile of 4 x
+// 8 x 128 leaves to ws_border a quarter of the contacts along z, an eighth along y and
+// the ends along x. us on 32 x 1012^2 (tile, border, label) and on 2^20 voxels in all:
+// 4 x 8 rows 173, 59, 109 and 35; 4 x 16 197, 50, 103 and 45; 2 x 8 175, 89, 134 and
+// 32; 2 x 16 172, 77, 127 and 35; 4 x 4 179, 79, 122 and 34.
+constexpr int TX = 128;
+
+// parents in LDS, as ws_find and ws_unite below
+__device__ __forceinline__ int lp(const int* par, int l) {
+  return __hip_atomic_load(par + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ int tile_find(int* par, int r) {
+  int up = lp(par, r);
+  while (up != r) {
+    const int gp = lp(par, up);
+    if (gp == up) return up;
+    __hip_atomic_store(par + r, gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    r = gp;
+    up = lp(par, r);
+  }
+  return r;
+}
+__device__ __forceinline__ void tile_unite(int* par, int u, int v) {
+  int ru = tile_find(par, u), rv = tile_find(par, v);
+  while (ru != rv) {
+    const int hi = ru > rv ? ru : rv, lo = ru < rv ? ru : rv;
+    int old = hi;
+    if (__hip_atomic_compare_exchange_strong(par + hi, &old, lo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP))
+      return;
+    ru = tile_find(par, old);
+    rv = lo;
+  }
+}
+
+template <bool VEC, int TZ, int TY>
+__global__ __launch_bounds__(512) void ws_tile(const float* __restrict__ p, Vol3 g, float t, int32_t* __restrict__ a,
+                                               unsigned ntz, unsigned ntx, unsigned ntiles) {
+  constexpr int STEPS = TZ * TY / 16;  // of 16 rows, two per wave
+  static_assert(TZ * TY == 16 * STEPS && STEPS <= 4, "whole steps; four fill the masks below");
+  __shared__ __attribute__((aligned(16))) int par[TX * TY * TZ];  // >= 0: a voxel of the tile; else ~ one outside it
+  // consecutive tiles (along z, then x, then y: the largest shared faces first) on the
+  // same XCD (workgroup b on XCD b % 8), whose L2 serves the rows that neighbours share
+  const unsigned tile = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (tile >= ntiles) return;
+  const int z0 = (int)(tile % ntz) * TZ, x0 = (int)(tile / ntz % ntx) * TX, y0 = (int)(tile / (ntz * ntx)) * TY;
+  const int HW = g.H * g.W, lane = threadIdx.x & 63, l32 = lane & 31;
+  const int base = (z0 * g.H + y0) * g.W + x0;
+  const int x = x0 + 4 * l32;
+  // step s of wave w: two rows of the tile, lanes 0..31 and lanes 32..63
+  const int row0 = (int)(threadIdx.x >> 6) * 2 * STEPS + (lane >> 5);
+  unsigned touch = 0, first = 0;  // per step: columns to unite along y, along z; first columns of runs
+#pragma unroll
+  for (int s = 0; s < STEPS; ++s) {
+    const int r = row0 + 2 * s, lz = r / TY, ly = r % TY, z = z0 + lz, y = y0 + ly;
+    const int n = z < g.Z && y < g.H ? min(max(g.W - x, 0), 4) : 0;
+    const int v = n ? base + lz * HW + ly * g.W + 4 * l32 : 0, l = r * TX + 4 * l32;
+    const f4 q = row4<VEC>(p, v, n);
+    const f4 zm = row4<VEC>(p, v - HW, z > 0 ? n : 0), zp = row4<VEC>(p, v + HW, z < g.Z - 1 ? n : 0);
+    const f4 ym = row4<VEC>(p, v - g.W, y > 0 ? n : 0), yp = row4<VEC>(p, v + g.W, y < g.H - 1 ? n : 0);
+    float left = __shfl_up(q[3], 1), right = __shfl_down(q[0], 1);
+    if (l32 == 0 && n && x > 0) left = ld<float>(gin(p) + ((int64_t)v - 1) * 4);
+    if (l32 == 31 && n && x + 4 < g.W) right = ld<float>(gin(p) + ((int64_t)v + 4) * 4);
+    const unsigned m = below4(q, n, t);
+    // the last column before this lane's that is no seed (columns past the row count as none)
+    const int last = m == 15u ? -1 : 4 * l32 + 31 - __builtin_clz(~m & 15u);
+    const uint64_t brk = __ballot(m != 15u);
+    const unsigned before = (unsigned)(brk >> (lane & 32)) & ((1u << l32) - 1);
+    const int from = __shfl(last, (lane & 32) + (before ? 31 - __builtin_clz(before) : 0));
+    int lb = before ? from : -1;
+    i4 up;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (m >> k & 1) {
+        up[k] = r * TX + lb + 1;  // the run's first seed
+        continue;
+      }
+      lb = 4 * l32 + k;
+      const int self = l + k;
+      int best = self;
+      float pb = q[k];
+      // candidates in ascending index order: an equal one wins only over v itself, from
+      // before v; one of another tile is held as ~ its index
+      auto cand = [&](bool there, bool lower, float pu, bool inside, int lu, int u) __attribute__((always_inline)) {
+        const bool take = there && (pu < pb || (lower && pu == pb && best == self));
+        pb = take ? pu : pb;
+        best = take ? (inside ? lu : ~u) : best;
+      };
+      cand(z > 0, true, zm[k], lz > 0, self - TY * TX, v + k - HW);
+      cand(y > 0, true, ym[k], ly > 0, self - TX, v + k - g.W);
+      cand(x + k > 0, true, k > 0 ? q[k > 0 ? k - 1 : 0] : left, k > 0 || l32 > 0, self - 1, v + k - 1);
+      cand(x + k < g.W - 1, false, k < 3 ? q[k < 3 ? k + 1 : 3] : right, k < 3 || l32 < 31, self + 1, v + k + 1);
+      cand(y < g.H - 1, false, yp[k], ly < TY - 1, self + TX, v + k + g.W);
+      cand(z < g.Z - 1, false, zp[k], lz < TZ - 1, self + TY * TX, v + k + HW);
+      up[k] = best;
+    }
+    *reinterpret_cast<i4*>(par + l) = up;
+    // first columns where the run of this row touches one of the next row / slice of the tile
+    const unsigned my = ly < TY - 1 && y < g.H - 1 ? m & below4(yp, n, t) : 0u;
+    const unsigned mz = lz < TZ - 1 && z < g.Z - 1 ? m & below4(zp, n, t) : 0u;
+    touch |= (half_starts(my, l32) | half_starts(mz, l32) << 4) << 8 * s;
+    first |= half_starts(m, l32) << 4 * s;
+  }
+  __syncthreads();
+  for (unsigned b = touch; b; b &= b - 1) {
+    const int i = __builtin_ctz(b), l = (row0 + 2 * (i >> 3)) * TX + 4 * l32 + (i & 3);
+    tile_unite(par, l, l + (i & 4 ? TY * TX : TX));
+  }
+  __syncthreads();
+  for (unsigned b = first; b; b &= b - 1) {
+    const int i = __builtin_ctz(b), l = (row0 + 2 * (i >> 2)) * TX + 4 * l32 + (i & 3);
+    const int r = tile_find(par, l);
+    __hip_atomic_store(par + l, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < STEPS; ++s) {
+    const int r = row0 + 2 * s, lz = r / TY, ly = r % TY;
+    const int n = z0 + lz < g.Z && y0 + ly < g.H ? min(max(g.W - x, 0), 4) : 0;
+    if (n == 0) continue;
+    const int l = r * TX + 4 * l32;
+    i4 c = {l, l + 1, l + 2, l + 3}, up = *reinterpret_cast<const i4*>(par + l);
+#pragma unroll
+    for (int k = 1; k < 4; ++k) up[k] = k < n ? up[k] : c[k];
+    // the four walks step together
+    auto open = [&](int k) __attribute__((always_inline)) { return up[k] >= 0 && up[k] != c[k]; };
+    while (open(0) || open(1) || open(2) || open(3)) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        if (m >> k & 1) {
-          out[k] = base + lb + 1;  // the run's first seed
-        } else {
-          lb = x + k;
-          int best = v + k;
-          float pb = q[k];
-          // candidates in ascending index order: a later one wins only if strictly lower
-          auto cand = [&](bool there, float pu, int u) __attribute__((always_inline)) {
-            const bool take = there && (pu < pb || (pu == pb && u < best));
-            pb = take ? pu : pb;
-            best = take ? u : best;
-          };
-          cand(z > 0, zm[k], v + k - HW);
-          cand(y > 0, ym[k], v + k - g.W);
-          cand(x + k > 0, k > 0 ? q[k > 0 ? k - 1 : 0] : left, v + k - 1);
-          cand(x + k < g.W - 1, k < 3 ? q[k < 3 ? k + 1 : 3] : right, v + k + 1);
-          cand(y < g.H - 1, yp[k], v + k + g.W);
-          cand(z < g.Z - 1, zp[k], v + k + HW);
-          out[k] = best;
-        }
-      }
-      if constexpr (VEC) {
-        if (n > 0) st<i4>(gout(a) + (int64_t)v * 4, out);
-      } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (k < n) st<int32_t>(gout(a) + ((int64_t)v + k) * 4, out[k]);
+        const bool o = open(k);
+        c[k] = o ? up[k] : c[k];
+        up[k] = o ? par[c[k]] : up[k];
       }
     }
-  });
+    i4 out;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      out[k] = up[k] < 0 ? ~up[k] : base + c[k] / (TY * TX) * HW + c[k] / TX % TY * g.W + c[k] % TX;
+    const int64_t v = base + lz * HW + ly * g.W + 4 * l32;
+    if constexpr (VEC) {
+      st<i4>(gout(a) + v * 4, out);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (k < n) st<int32_t>(gout(a) + (v + k) * 4, out[k]);
+    }
+  }
 }
 
+// ---- across tiles
 // Root of r with path halving (any node may be passed; roots are fixed points).
 __device__ __forceinline__ int32_t ws_find(int32_t* a, int32_t r) {
   int32_t par = wa(a, r);
   while (par != r) {
-    if (par < 0) return ~par;  // ws_flat has written the root here
+    if (par < 0) return ~par;  // ws_label has written the root here
     const int32_t gp = wa(a, par);
     if (gp == par) return par;
     if (gp < 0) return ~gp;
@@ -206,9 +298,8 @@ __device__ __forceinline__ unsigned run_starts(unsigned m, int lane, unsigned& p
 }
 
 // Finds are chains of dependent loads, and the columns that start one are sparse
-// (a few per wave and step): done where they are met, one lane in ten works while
-// the wave waits. So a wave queues them in LDS and works them off 64 at a time
-// (ws_flat 59 -> 55 us; ws_union, which waits for its atomics, the same).
+// (a few per wave and step), so a wave queues them in LDS and works them off 64 at
+// a time.
 constexpr int WQCAP = 64 + 2 * WC;
 struct WaveQueue {
   int* q;
@@ -235,8 +326,13 @@ struct WaveQueue {
   }
 };
 
-template <bool VEC>
-__global__ __launch_bounds__(256) void ws_union(const float* __restrict__ p, Vol3 g, float t, int32_t* a) {
+// Contacts across the faces of tiles. A pair of touching voxels needs no union
+// where a neighbouring pair is united and the links between the two pairs are made
+// without this pair's: across y, the pair one column left; across z, the pair one
+// column left or one row up; across x, the pair one row up in the same tiles (the
+// links along y inside a tile, whose runs start at its edge, need none across x).
+template <bool VEC, int TZ, int TY>
+__global__ __launch_bounds__(256) void ws_border(const float* __restrict__ p, Vol3 g, float t, int32_t* a) {
   __shared__ int queue[4][WQCAP];
   const int HW = g.H * g.W, lane = threadIdx.x & 63;
   WaveQueue wq{queue[threadIdx.x >> 6], 0, lane};
@@ -247,50 +343,48 @@ __global__ __launch_bounds__(256) void ws_union(const float* __restrict__ p, Vol
   };
   wave_rows((unsigned)(g.Z * g.H), [&](int row) __attribute__((always_inline)) {
     const int z = row / g.H, y = row - z * g.H, base = row * g.W;
-    unsigned prevy = 0, prevz = 0;
-    for (int x0 = 0; x0 < g.W; x0 += WC) {
-      const int x = x0 + 4 * lane, v = base + x, n = min(max(g.W - x, 0), 4);
-      const unsigned m = below4(row4<VEC>(p, v, n), n, t);
-      const unsigned my = y < g.H - 1 ? below4(row4<VEC>(p, v + g.W, n), n, t) : 0u;
-      const unsigned mz = z < g.Z - 1 ? below4(row4<VEC>(p, v + HW, n), n, t) : 0u;
-      // first columns where the run of this row touches one of the next row / slice
-      const unsigned sy = run_starts(m & my, lane, prevy), sz = run_starts(m & mz, lane, prevz);
+    const bool fy = y % TY == TY - 1 && y < g.H - 1, fz = z % TZ == TZ - 1 && z < g.Z - 1;
+    const bool up = fz && y > 0;
+    if (fy || fz) {
+      unsigned prevy = 0, prevz = 0;
+      for (int x0 = 0; x0 < g.W; x0 += WC) {
+        const int x = x0 + 4 * lane, v = base + x, n = min(max(g.W - x, 0), 4);
+        const f4 q = row4<VEC>(p, v, n), qy = row4<VEC>(p, v + g.W, fy ? n : 0), qz = row4<VEC>(p, v + HW, fz ? n : 0);
+        const f4 qu = row4<VEC>(p, v - g.W, up ? n : 0), qzu = row4<VEC>(p, v + HW - g.W, up ? n : 0);
+        const unsigned m = below4(q, n, t);
+        const unsigned my = m & below4(qy, fy ? n : 0, t), mz = m & below4(qz, fz ? n : 0, t);
+        const unsigned sy = run_starts(my, lane, prevy);
+        const unsigned sz = run_starts(mz, lane, prevz) & ~(below4(qu, up ? n : 0, t) & below4(qzu, up ? n : 0, t));
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        wq.push(sy >> k & 1, v + k);
-        wq.push(sz >> k & 1, ~(v + k));
+        for (int k = 0; k < 4; ++k) {
+          wq.push(sy >> k & 1, v + k);
+          wq.push(sz >> k & 1, ~(v + k));
+        }
+        wq.drain(false, work);
       }
-      wq.drain(false, work);
+    }
+    for (int x0 = TX; x0 < g.W; x0 += 64 * TX) {
+      const int64_t x = x0 + (int64_t)lane * TX;
+      if (x >= g.W) continue;
+      auto both = [&](int64_t v) __attribute__((always_inline)) {
+        return ld<float>(gin(p) + v * 4) < t && ld<float>(gin(p) + (v - 1) * 4) < t;
+      };
+      const int64_t v = base + x;
+      if (both(v) && !(y % TY != 0 && both(v - g.W))) ws_unite(a, (int32_t)v, (int32_t)v - 1);
     }
   });
   wq.drain(true, work);
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(256) void ws_flat(const float* __restrict__ p, Vol3 g, float t, int32_t* a) {
-  __shared__ int queue[4][WQCAP];
-  const int lane = threadIdx.x & 63;
-  WaveQueue wq{queue[threadIdx.x >> 6], 0, lane};
-  auto work = [&](int v) __attribute__((always_inline)) {
-    const int32_t r = ws_find(a, v);
-    __hip_atomic_store(a + v, ~r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  };
-  wave_rows((unsigned)(g.Z * g.H), [&](int row) __attribute__((always_inline)) {
-    const int base = row * g.W;
-    unsigned prev = 0;
-    for (int x0 = 0; x0 < g.W; x0 += WC) {
-      const int x = x0 + 4 * lane, v = base + x, n = min(max(g.W - x, 0), 4);
-      const unsigned s = run_starts(below4(row4<VEC>(p, v, n), n, t), lane, prev);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) wq.push(s >> k & 1, v + k);
-      wq.drain(false, work);
-    }
-  });
-  wq.drain(true, work);
-}
+// Parents followed before a walk goes on with writes. Walks are short here (a
+// tile's component, the components it was hooked under; the tiles of a descent), and
+// writes from every voxel cost more than they save; a component whose tree is deep
+// all the same gets its paths halved, and its root's complement, which ends a walk,
+// where the walk was after these steps.
+constexpr int kPlainSteps = 16;
 
 template <bool VEC>
-__global__ __launch_bounds__(256) void ws_label(Vol3 g, const int32_t* __restrict__ a, int32_t* out) {
+__global__ __launch_bounds__(256) void ws_label(Vol3 g, int32_t* a, int32_t* out) {
   const gbyte* ab = gin(a);
   const int64_t v = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (v >= g.N) return;
@@ -301,14 +395,14 @@ __global__ __launch_bounds__(256) void ws_label(Vol3 g, const int32_t* __restric
     par = ld<i4>(ab + v * 4);
   } else {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) par[k] = ld<int32_t>(ab + (int64_t)r[k] * 4);
+    for (int k = 0; k < 4; ++k) par[k] = wa(a, r[k]);
   }
   // the four walks step together, so that their loads overlap
   auto open = [&](int k) __attribute__((always_inline)) { return par[k] >= 0 && par[k] != r[k]; };
-  while (open(0) || open(1) || open(2) || open(3)) {
+  for (int i = 0; i < kPlainSteps && (open(0) || open(1) || open(2) || open(3)); ++i) {
     i4 nx;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) nx[k] = open(k) ? ld<int32_t>(ab + (int64_t)par[k] * 4) : par[k];
+    for (int k = 0; k < 4; ++k) nx[k] = open(k) ? wa(a, par[k]) : par[k];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       r[k] = open(k) ? par[k] : r[k];
@@ -316,7 +410,15 @@ __global__ __launch_bounds__(256) void ws_label(Vol3 g, const int32_t* __restric
     }
   }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) r[k] = (par[k] < 0 ? ~par[k] : r[k]) + 1;
+  for (int k = 0; k < 4; ++k) {
+    if (open(k)) {
+      const int32_t root = ws_find(a, par[k]);
+      // (r is no root, and its complement is only ever read as the end of a walk)
+      __hip_atomic_store(a + r[k], ~root, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      par[k] = ~root;
+    }
+    r[k] = (par[k] < 0 ? ~par[k] : r[k]) + 1;
+  }
   if constexpr (VEC) {
     st<i4>(gout(out) + v * 4, r);
   } else {
@@ -326,31 +428,21 @@ __global__ __launch_bounds__(256) void ws_label(Vol3 g, const int32_t* __restric
   }
 }
 
-// ws_flat and ws_label in one launch: every voxel finds its root, halving the path
-// as it goes, one voxel a thread. For volumes whose time is their launches.
-__global__ __launch_bounds__(256) void ws_label_small(Vol3 g, int32_t* a, int32_t* __restrict__ out) {
-  const int v = blockIdx.x * 256 + threadIdx.x;
-  if (v < (int)g.N) out[v] = ws_find(a, v) + 1;
-}
-// Voxels up to which it is used (us per call, three launches against four: 15.6
-// against 20.1 on 2^12 voxels, 22 against 29 on 2^15, 31-33 against 33 on 2^17,
-// 39 against 34 on 2^18).
-constexpr int64_t kSmall = 1 << 17;
+// Voxels up to which tiles of 2 x 8 rows are taken: a step of a wave less, twice the
+// workgroups (us with 2 x 8 against 4 x 8 rows: 25.6 against 30.7 on 2^19 voxels, 32 against
+// 35 on 2^20, 48-50 against 46 on 1.2 M, 62 against 60 on 2^22).
+constexpr int64_t kSmall = 1 << 20;
 
-template <bool VEC>
+template <bool VEC, int TZ, int TY>
 static hipError_t ws_run(const float* p, const Vol3& g, float t, int32_t* labels, int32_t* work, hipStream_t st) {
+  const int64_t ntz = (g.Z + TZ - 1) / TZ, ntx = (g.W + TX - 1) / TX, nty = (g.H + TY - 1) / TY, nt = ntz * ntx * nty;
   const int64_t groups = ((int64_t)g.Z * g.H + 3) / 4;  // of four rows
-  // multiples of 8 (wave_rows); the kernels with a queue run persistent waves, which keep theirs filled
-  const dim3 rows((unsigned)std::min<int64_t>((groups + 7) / 8 * 8, 1 << 20)), block(256);
-  const dim3 few(std::min(rows.x, 2048u));
-  hipLaunchKernelGGL(ws_init<VEC>, rows, block, 0, st, p, g, t, work);
-  hipLaunchKernelGGL(ws_union<VEC>, few, block, 0, st, p, g, t, work);
-  if (g.N <= kSmall) {
-    hipLaunchKernelGGL(ws_label_small, dim3((unsigned)((g.N + 255) / 256)), block, 0, st, g, work, labels);
-  } else {
-    hipLaunchKernelGGL(ws_flat<VEC>, few, block, 0, st, p, g, t, work);
-    hipLaunchKernelGGL(ws_label<VEC>, dim3((unsigned)((g.N + 1023) / 1024)), block, 0, st, g, work, labels);
-  }
+  // grids in multiples of 8, one share per XCD; ws_border runs persistent waves, which keep their queues filled
+  hipLaunchKernelGGL((ws_tile<VEC, TZ, TY>), dim3((unsigned)((nt + 7) / 8 * 8)), dim3(512), 0, st, p, g, t, work,
+                     (unsigned)ntz, (unsigned)ntx, (unsigned)nt);
+  hipLaunchKernelGGL((ws_border<VEC, TZ, TY>), dim3((unsigned)std::min<int64_t>((groups + 7) / 8 * 8, 2048)), dim3(256), 0,
+                     st, p, g, t, work);
+  hipLaunchKernelGGL(ws_label<VEC>, dim3((unsigned)((g.N + 1023) / 1024)), dim3(256), 0, st, g, work, labels);
   return hipGetLastError();
 }
 
@@ -370,8 +462,10 @@ extern "C" int watershed_3d(const float* prob, const int64_t dims[3], float seed
   Vol3 g{(int)Z, (int)H, (int)W, Z * H * W};
   // 16-byte accesses where every row starts at one
   const bool vec = W % 4 == 0 && ((uintptr_t)prob | (uintptr_t)work | (uintptr_t)labels_out) % 16 == 0;
-  const hipError_t e = vec ? ws_run<true>(prob, g, seed_threshold, labels_out, work, st)
-                           : ws_run<false>(prob, g, seed_threshold, labels_out, work, st);
+  const bool small = g.N <= kSmall;
+  const auto run = vec ? (small ? ws_run<true, 2, 8> : ws_run<true, 4, 8>)
+                       : (small ? ws_run<false, 2, 8> : ws_run<false, 4, 8>);
+  const hipError_t e = run(prob, g, seed_threshold, labels_out, work, st);
   if (e != hipSuccess) return hip_fail(e, "watershed_3d");
   return CNN_OK;
 }

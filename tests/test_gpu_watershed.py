@@ -98,8 +98,29 @@ def test_watershed_row_ends_and_alignment(emcnn, W, offset):
 
 @pytest.mark.parametrize("shape", [(2, 256, 256), (2, 256, 257), (3, 181, 290)])
 def test_watershed_around_the_small_volume_form(emcnn, shape):
-    """2^17 voxels and just above and beside it: labels in one launch or two."""
+    """Volumes of 2^17 voxels and just above and beside it."""
     rng = np.random.default_rng(shape[2])
     p = ndimage.gaussian_filter(rng.uniform(0, 1, shape), 1.5).astype(np.float32)
     t = float(np.quantile(p, 0.4))
     assert np.array_equal(_gpu(emcnn, p, t), oracle.watershed(p, t))
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (2, 8, 128), (3, 9, 129), (4, 17, 257), (1, 31, 127), (9, 2, 130),  # 2 x 8 x 128
+                                   (5, 517, 413), (9, 257, 512), (4, 8, 33000)])  # 4 x 8 x 128
+def test_watershed_across_tiles(emcnn, shape):
+    """Volumes that end inside, at and past a tile, with seeds and ties through all faces."""
+    print("watershed tiles case", shape, flush=True)
+    rng = np.random.default_rng(shape[2])
+    p = np.floor(rng.uniform(0, 1, shape) * 6) / 6
+    p = np.where(rng.uniform(0, 1, shape) < 0.5, 0.05, p + 0.1).astype(np.float32)
+    assert np.array_equal(_gpu(emcnn, p, 0.08), oracle.watershed(p, 0.08))
+
+
+@pytest.mark.parametrize("H,W", [(300, 700), (800, 1500)])
+def test_watershed_one_long_component(emcnn, H, W):
+    """A seed path that winds through every tile: the deepest trees that tiles leave."""
+    p = np.random.default_rng(H).uniform(0.2, 1, (1, H, W)).astype(np.float32)
+    p[0, ::2] = 0.1
+    p[0, 1::4, -1] = 0.1
+    p[0, 3::4, 0] = 0.1
+    assert np.array_equal(_gpu(emcnn, p, 0.15), oracle.watershed(p, 0.15))
