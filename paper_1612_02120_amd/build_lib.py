@@ -28,7 +28,8 @@ FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",
 # outputs, every other kernel unchanged).
 FILE_FLAGS = {"probe.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
               "conv_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-              "conv_split.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+              "conv_split.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+              "student.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def sources():

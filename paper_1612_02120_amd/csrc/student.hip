@@ -17,7 +17,6 @@
 #include <cmath>
 #include <cstring>
 #include <string>
-#include <type_traits>
 #include <vector>
 
 #include "../../include/emcnn.h"
@@ -111,27 +110,63 @@ __global__ __launch_bounds__((TY * TX)) void student_fused(const uint8_t* __rest
 // working weights and h1 are bf16 values and uint8 inputs are exact in bf16,
 // so every product is exact and sums are FP32 (in the MFMA's order).
 //
-// The 8 channels fill the 16 rows of an MFMA as two adjacent pixels: column n is
-// the pixel pair 2n, 2n + 1, rows 0..7 the channels of pixel 2n and rows 8..15
-// those of pixel 2n + 1, whose weights are the same ones one tap to the right. A
-// pair's window is 5 x 6 = 30 of conv1's 32 K slots (one pixel's 25), and 3 x 4
-// taps x 8 channels = 96 of conv2's three MFMAs (one pixel's 72): one MFMA gives
-// conv1 at 32 positions and three give 32 outputs, half the instructions of one
-// pixel per column. The K slots are laid out so that an operand is what LDS holds:
-//   conv1: lane group g reads the six pixels of window row g (three dwords of bf16
-//          pairs), and pixels 2g, 2g + 1 of row 4 (one dword; g = 3: zero weights);
-//   conv2: MFMA i, lane group g reads the 8 channels of h1 pixel (i, g), 16 bytes.
+// The 8 channels would leave half of an MFMA's 16 rows empty:
+//   conv1: two MFMAs on one accumulator, the channels in the weights' rows 0..7 for
+//          the first 16 pixels and in rows 8..15 for the next 16. K slot t is tap t,
+//          as h1 is rounded to bf16 after this sum: in another order of the slots, a few
+//          h1 pixels in a million round the other way.
+//   conv2: a column is the pixel pair 2n, 2n + 1, rows 0..7 the channels of pixel 2n,
+//          rows 8..15 those of pixel 2n + 1, whose weights are the same ones one tap
+//          to the right. A pair's window, 3 x 4 taps x 8 channels, is the K of three
+//          MFMAs; lane group g of MFMA i reads h1 pixel (i, g), 16 bytes.
+// conv1's operand is two pixels a dword, each row kept twice in LDS, from an even
+// and from an odd pixel, so that any two neighbours are one; the two dwords that hold
+// a row's end and the next one's start in some lane groups are put together from two.
 // A wave computes a strip of 62 output columns (64 of h1, two MFMA columns of 32)
-// from the top down, with rings of its own in LDS (8 input rows, 4 h1 rows): no
-// barrier, no halo rows but the strip's first six, and the loads of the row after
-// next in flight. One sigmoid and one store per lane and row. On 8 x 2048^2: 312 us
-// with tiles of 16 x 64 outputs shared by four waves and one pixel per column
-// (2.6 times the vector instructions), MEASURED now; 55 us of MFMA issue became 28.
+// from the top down, with rings of its own (6 input rows in LDS, each in two places so
+// that five consecutive ones always lie in order; three h1 rows as conv2's operands in
+// registers, where LDS turns each row once): no barrier, no halo rows but the strip's
+// first six, and the loads of the row after next in flight. One sigmoid and one store
+// per lane and row. On 8 x 2048^2: 312 us with tiles of 16 x 64 outputs shared by
+// four waves and half of each MFMA empty, 165 now, of which the vector instructions
+// (95 per row of 62 outputs, 16 of them the sigmoid) fill 77 % and LDS about as much.
+
+// Outputs (y0 .. y0 + n - 1, x) of slice z, one lane each (see where it is called).
+__device__ __forceinline__ void student_pixels(const uint8_t* in, int64_t in_rs, int64_t in_zs, float* out, int64_t out_rs,
+                                               int64_t out_zs, int Ho, int Wo, int crop, const float* ww, int z, int y0,
+                                               int n, int x, bool mine) {
+  if (!mine || x >= Wo) return;
+  for (int y = y0; y < y0 + n; ++y) {
+    const uint8_t* src = in + (int64_t)z * in_zs + (int64_t)(y + crop) * in_rs + x + crop;
+    float a[S_C];
+#pragma unroll
+    for (int co = 0; co < S_C; ++co) a[co] = ww[OFF_B2 + co];
+#pragma clang loop unroll(disable)
+    for (int e = 0; e < S_C * 9; ++e) {
+      const int ci = e / 9, i = e % 9 / 3, j = e % 3;
+      float s = 0.f;
+#pragma clang loop unroll(disable)
+      for (int k = 0; k < 25; ++k) s = fmaf(ww[OFF_W1 + ci * 25 + k], (float)src[(i + k / 5) * in_rs + j + k % 5], s);
+      const float h = s_bf16(s_relu(s + ww[OFF_B1 + ci]));
+#pragma unroll
+      for (int co = 0; co < S_C; ++co) a[co] = fmaf(ww[OFF_W2 + (co * 8 + ci) * 9 + i * 3 + j], h, a[co]);
+    }
+    float zl = ww[OFF_BH];
+#pragma unroll
+    for (int co = 0; co < S_C; ++co) zl = fmaf(ww[OFF_WH + co], s_relu(a[co]), zl);
+    out[(int64_t)z * out_zs + (int64_t)y * out_rs + x] = s_sigmoid(zl);
+  }
+}
+
 constexpr int SW = 62;            // output columns of a strip
-constexpr int SXP = 144;          // bytes per input ring row: 34 pixel pairs of bf16, padded
-constexpr int SHP = 66 * 16;      // bytes per h1 ring row: 64 pixels of 8 channels, and what the last pair over-reads
-constexpr int SLDS = 8 * SXP + 4 * SHP;
-__global__ __launch_bounds__(256) void student_strip(const uint8_t* in, int64_t in_rs, int64_t in_zs, float* out,
+constexpr int SXP = 42 * 4;       // bytes per input row: 70 pixels of bf16, padded
+constexpr int SXC = 528 * 4;      // from the copy that starts at pixel 0 to the one that starts at pixel 1
+constexpr int SX = 2 * SXC;       // both copies of 12 rows
+constexpr int SHO = 40 * 16;      // in an h1 row, from its even pixels to its odd ones: lanes that read every other pixel read on end
+constexpr int SHP = SHO + 33 * 16;  // bytes per h1 row: 64 pixels of 8 channels, and what the last pair over-reads
+constexpr int SLDS = SX + 2 * SHP;
+static_assert(SXC >= 12 * SXP && SX % 16 == 0 && SHO >= 33 * 16, "rows do not overlap");
+__global__ __launch_bounds__(256, 4) void student_strip(const uint8_t* in, int64_t in_rs, int64_t in_zs, float* out,
                                                      int64_t out_rs, int64_t out_zs, int Ho, int Wo, int crop,
                                                      const float* ww, int rows, int nsy, int nsx, int nstrips) {
   __shared__ __attribute__((aligned(16))) unsigned char lds_all[4 * SLDS];
@@ -140,34 +175,37 @@ __global__ __launch_bounds__(256) void student_strip(const uint8_t* in, int64_t 
   const int strip = blockIdx.x * 4 + wave;
   if (strip >= nstrips) return;
   unsigned char* const xr = lds_all + wave * SLDS;
-  unsigned char* const hr = xr + 8 * SXP;
+  unsigned char* const hr = xr + SX;
   const int g = lane >> 4, n16 = lane & 15;
   const int sx = strip % nsx, sy = (strip / nsx) % nsy, z = strip / (nsx * nsy);
   const int x0 = sx * SW, y0 = sy * rows;
   const int nout = min(rows, Ho - y0);
-  // the strip's input: 68 columns from x0 + crop, clamped to the last valid row and column
+  // the strip's input: 71 columns from x0 + crop, clamped to the last valid row and column
   const int ylim = Ho + 2 * crop + 5, xlim = Wo + 2 * crop + 5;
-  const gbyte* src = gin(in) + (int64_t)z * in_zs;
-  const int ca = min(x0 + crop + 2 * lane, xlim), cb = min(x0 + crop + 2 * lane + 1, xlim);  // this lane's pixel pair
-  auto load = [&](int r, unsigned& a, unsigned& b) __attribute__((always_inline)) {
-    const gbyte* row = src + (int64_t)min(y0 + crop + r, ylim) * in_rs;
-    a = row[ca];
-    b = row[cb];
+  const gbyte* srow = gin(in) + (int64_t)z * in_zs + (int64_t)min(y0 + crop, ylim) * in_rs;  // the next row to load
+  int below = ylim - (y0 + crop);                                                            // rows below it
+  const unsigned ca = min(x0 + crop + 2 * lane, xlim), cb = min(x0 + crop + 2 * lane + 1, xlim),
+                 cc = min(x0 + crop + 2 * lane + 2, xlim);  // this lane's pixels
+  unsigned pa[2], pb[2], pc[2];  // rows r and r + 1 ahead of their use
+  auto load = [&](int i) __attribute__((always_inline)) {
+    pa[i] = srow[ca];
+    pb[i] = srow[cb];
+    pc[i] = srow[cc];
+    srow += below > 0 ? in_rs : 0;
+    --below;
   };
-  unsigned pa[2], pb[2];  // rows r and r + 1 ahead of their use
-  load(0, pa[0], pb[0]);
-  load(1, pa[1], pb[1]);
+  load(0);
+  load(1);
   // weight fragments: lane (g, m) holds row m's K slots 8g..8g+7 (every load is
   // unconditional, from a clamped index, and the padding is selected afterwards,
   // so that all of them are in flight together)
   const int ch = n16 & 7, dx = n16 >> 3;
-  bf16x8 w1f, w2f[3];
+  bf16x8 w1f[2], w2f[3];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const int i = e < 6 ? g : 4, j = (e < 6 ? e : 2 * g + e - 6) - dx;
-    const bool there = j >= 0 && j < 5 && !(e >= 6 && g == 3);
-    const float v = ldf(ww, OFF_W1 + ch * 25 + i * 5 + min(max(j, 0), 4));
-    w1f[e] = (__bf16)(there ? v : 0.f);
+    const __bf16 v = (__bf16)ldf(ww, OFF_W1 + ch * 25 + min(8 * g + e, 24));
+#pragma unroll
+    for (int b = 0; b < 2; ++b) w1f[b][e] = b == dx && 8 * g + e < 25 ? v : (__bf16)0.f;
   }
 #pragma unroll
   for (int i = 0; i < 3; ++i)
@@ -189,22 +227,35 @@ __global__ __launch_bounds__(256) void student_strip(const uint8_t* in, int64_t 
   const float bh = ldf(ww, OFF_BH);
   // A pair's window holds a pixel that one of the two has zero weights for: were its
   // h1 infinite, the product would be NaN. Weights that bound h1 well below the
-  // largest bf16 (any but a diverged student's) rule that out; others take the loop
-  // that gives each pixel of the pair its own three MFMAs.
+  // largest bf16 (any but a diverged student's) rule that out; with others the strip
+  // is computed pixel by pixel.
   float top = 0.f;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) top += 255.f * fabsf((float)w1f[e]);
+  for (int e = 0; e < 8; ++e) top += 255.f * (fabsf((float)w1f[0][e]) + fabsf((float)w1f[1][e]));
 #pragma unroll
   for (int k = 0; k < 4; ++k) top += fabsf(b1[k]);
-  const bool apart = __any(!(top < 1e36f));
-  // per-lane bases: conv1's pixels of row 4 (g = 3: zero weights, any pixels), h1 writes and reads
-  const int x4 = (n16 + (g < 3 ? g : 0)) * 4;
-  unsigned char* const hw = hr + (2 * n16 + (g >> 1)) * 16 + (g & 1) * 8;
-  const unsigned char* const hrd = hr + (2 * n16 + g) * 16;
+  if (__any(!(top < 1e36f))) {
+    student_pixels(in, in_rs, in_zs, out, out_rs, out_zs, Ho, Wo, crop, ww, z, y0, nout, x0 + lane, lane < SW);
+    return;
+  }
+  // per-lane bases: pixel pairs from taps 8g + 2k (xa) and 8g + 2k + 1 (xb) of pixel n16, h1 writes and reads
+  auto tap_at = [&](int tap) __attribute__((always_inline)) {
+    tap = tap > 24 ? tap - 8 : tap;  // zero weights there: the address of the lane group before
+    const int i = tap / 5, px = n16 + tap % 5;
+    return xr + (px & 1) * SXC + i * SXP + (px >> 1) * 4;
+  };
+  const unsigned char *xa[4], *xb[2];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) xa[k] = tap_at(8 * g + 2 * k);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) xb[k] = tap_at(8 * g + 5 + 2 * k);
+  unsigned char* const hw = hr + (n16 & 1) * SHO + (8 * (g >> 1) + (n16 >> 1)) * 16 + (g & 1) * 8;
+  const unsigned char* const hrd = hr + (g & 1) * SHO + (n16 + (g >> 1)) * 16;
   // the lane's output column after the exchange below: MFMA column g & 1, pixel 2n + (g >> 1)
   const int xo = 32 * (g & 1) + 2 * n16 + (g >> 1);
+  const unsigned xo4 = xo * 4;
   const bool col_ok = xo < SW && x0 + xo < Wo;
-  gbyte* const od = gout(out) + ((int64_t)z * out_zs + (int64_t)y0 * out_rs + x0 + xo) * 4;
+  gbyte* orow = gout(out) + ((int64_t)z * out_zs + (int64_t)y0 * out_rs + x0) * 4;  // the next output row
 
   // LDS between lanes of one wave needs no wait (its accesses stay in order), only
   // that the compiler keeps that order
@@ -212,74 +263,114 @@ __global__ __launch_bounds__(256) void student_strip(const uint8_t* in, int64_t 
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   };
-  const int total = nout + 6;
-  auto rows_down = [&](auto apart_c) __attribute__((always_inline)) {
-    for (int base = 0; base < total; base += 8) {
+  u4v h[3][2];  // conv2's operands of the last three h1 rows
+  // input row r = p (mod 6) to LDS
+  auto take_row = [&](int p) __attribute__((always_inline)) {
+    // uint8 -> bf16 is exact: the float of an integer below 256 has a zero low half
+    auto pair = [](unsigned lo, unsigned hi) __attribute__((always_inline)) {
+      return __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, (float)hi), __builtin_bit_cast(unsigned, (float)lo),
+                                   0x07060302u);
+    };
+    if (lane < 35) {
+      const unsigned even = pair(pa[p & 1], pb[p & 1]), odd = pair(pb[p & 1], pc[p & 1]);
+      unsigned char* const x = xr + p * SXP + lane * 4;
+      st<uint32_t>(x, even);
+      st<uint32_t>(x + 6 * SXP, even);
+      st<uint32_t>(x + SXC, odd);
+      st<uint32_t>(x + SXC + 6 * SXP, odd);
+    }
+    load(p & 1);
+    in_order();
+  };
+  // input rows r - 4 .. r as conv1 reads them
+  unsigned x[2][2][6];
+  auto conv1_in = [&](int p) __attribute__((always_inline)) {
 #pragma unroll
-      for (int p = 0; p < 8; ++p) {
-        const int r = base + p;  // input row
-        if (r >= total) break;
-        // uint8 -> bf16 is exact: the float of an integer below 256 has a zero low half
-        if (lane < 34)
-          *reinterpret_cast<uint32_t*>(xr + p * SXP + lane * 4) =
-              __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, (float)pb[p & 1]),
-                                    __builtin_bit_cast(unsigned, (float)pa[p & 1]), 0x07060302u);
-        load(r + 2, pa[p & 1], pb[p & 1]);
-        in_order();
-        if (r < 4) continue;
-        // ---- conv1: h1 row r - 4 from input rows r - 4 .. r
-        const unsigned char* const xg = xr + ((p + 4 + g) & 7) * SXP + n16 * 4;
+    for (int c = 0; c < 2; ++c)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const uint32_t* q = reinterpret_cast<const uint32_t*>(xg + c * 64);
-          const u4v xv = {q[0], q[1], q[2], *reinterpret_cast<const uint32_t*>(xr + p * SXP + x4 + c * 64)};
-          const f4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f, __builtin_bit_cast(bf16x8, xv), f4{0.f, 0.f, 0.f, 0.f}, 0,
-                                                               0, 0);
-          typedef float f2v __attribute__((ext_vector_type(2)));
-          typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-          auto pack = [](float lo, float hi) __attribute__((always_inline)) {
-            return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){lo, hi}, bf16x2v));
-          };
-          st<u2v>(hw + (p & 3) * SHP + c * 512, u2v{pack(s_relu(d[0] + b1[0]), s_relu(d[1] + b1[1])),
-                                                    pack(s_relu(d[2] + b1[2]), s_relu(d[3] + b1[3]))});
-        }
-        in_order();
-        if (r < 6) continue;
-        // ---- conv2 and head: output row r - 6 from h1 rows r - 6 .. r - 4
-        float part[2];
+      for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          f4 acc = f4{0.f, 0.f, 0.f, 0.f}, acc1 = acc;
+        for (int k = 0; k < 6; ++k)
+          x[c][b][k] = ld<uint32_t>((k < 4 ? xa[k & 3] : xb[k & 1]) + (p + 2) % 6 * SXP + c * 64 + b * 32);
+  };
+  // conv1: h1 row r - 4, and its operands back for conv2
+  auto h1_row = [&](int p) __attribute__((always_inline)) {
+    typedef float f2v __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+    auto pack = [](float lo, float hi) __attribute__((always_inline)) {
+      return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){lo, hi}, bf16x2v));
+    };
+    f4 d[2];
 #pragma unroll
-          for (int i = 0; i < 3; ++i) {
-            const u4v h = ld<u4v>(hrd + ((p + 2 + i) & 3) * SHP + c * 512);
-            const u4v h0 = apart_c.value && g == 3 ? u4v{0, 0, 0, 0} : h;
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2f[i], __builtin_bit_cast(bf16x8, h0), acc, 0, 0, 0);
-            if constexpr (apart_c.value) {
-              const u4v h1 = g == 0 ? u4v{0, 0, 0, 0} : h;
-              acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2f[i], __builtin_bit_cast(bf16x8, h1), acc1, 0, 0, 0);
-            }
-          }
-          if (apart_c.value && g >= 2) acc = acc1;
-          part[c] = 0.f;
+    for (int c = 0; c < 2; ++c) {
+      d[c] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int k = 0; k < 4; ++k) part[c] = fmaf(wh[k], s_relu(acc[k] + b2[k]), part[c]);
-        }
-        // channels 0..3 (even lane groups) and 4..7 (odd ones) of each pixel: even
-        // groups keep MFMA column 0, odd ones column 1
-        const bool odd = g & 1;
-        const float give = odd ? part[0] : part[1], keep = odd ? part[1] : part[0];
-        const float zl = keep + __shfl_xor(give, 16) + bh;
-        const float e = expf(-fabsf(zl));
-        const float prob = (zl >= 0.0f ? 1.0f : e) / (1.0f + e);
-        if (col_ok) st<float>(od + (int64_t)(r - 6) * out_rs * 4, prob);
+      for (int b = 0; b < 2; ++b) {
+        u4v xv;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xv[k] = k < 2 ? x[c][b][k] : __builtin_amdgcn_perm(x[c][b][k + 2], x[c][b][k], 0x05040100u);
+        d[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f[b], __builtin_bit_cast(bf16x8, xv), d[c], 0, 0, 0);
       }
     }
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      st<u2v>(hw + (p & 1) * SHP + c * 256, u2v{pack(s_relu(d[c][0] + b1[0]), s_relu(d[c][1] + b1[1])),
+                                                pack(s_relu(d[c][2] + b1[2]), s_relu(d[c][3] + b1[3]))});
+    in_order();
+#pragma unroll
+    for (int c = 0; c < 2; ++c) h[p % 3][c] = ld<u4v>(hrd + (p & 1) * SHP + c * 256);
   };
-  if (apart)
-    rows_down(std::true_type{});
-  else
-    rows_down(std::false_type{});
+  // conv2 and head: output row r - 6 from h1 rows r - 6 .. r - 4
+  auto out_row = [&](int p) __attribute__((always_inline)) {
+    float part[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2f[i], __builtin_bit_cast(bf16x8, h[(p + 1 + i) % 3][c]), acc, 0, 0, 0);
+      part[c] = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) part[c] = fmaf(wh[k], s_relu(acc[k] + b2[k]), part[c]);
+    }
+    // channels 0..3 (even lane groups) and 4..7 (odd ones) of each pixel: even
+    // groups take MFMA column 0, odd ones column 1
+    const bool odd = g & 1;
+    const float give = odd ? part[0] : part[1], keep = odd ? part[1] : part[0];
+    const int got = __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, give), 16 << 10 | 31);  // of lane ^ 16
+    const float zl = keep + __builtin_bit_cast(float, got) + bh;
+    const float e = expf(-fabsf(zl));
+    // (z >= 0 ? 1 : e) / d, d in [1, 2]: the reciprocal and the quotient each corrected
+    // once by their residual, which needs no scaling here
+    const float num = zl >= 0.0f ? 1.0f : e, d = 1.0f + e;
+    float rc = __builtin_amdgcn_rcpf(d);
+    rc = fmaf(fmaf(-d, rc, 1.0f), rc, rc);
+    const float q = num * rc;
+    const float prob = fmaf(fmaf(-d, q, num), rc, q);
+    if (col_ok) st<float>(orow + xo4, prob);
+    orow += out_rs * 4;
+  };
+#pragma unroll
+  for (int r = 0; r < 7; ++r) {
+    take_row(r % 6);
+    if (r >= 4) {
+      conv1_in(r % 6);
+      h1_row(r % 6);
+    }
+  }
+  // an output row a step behind, so that its MFMAs and its sigmoid run while conv1's
+  // operands come from LDS
+  for (int left = nout; left > 0; left -= 6) {
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      const int p = (q + 1) % 6;
+      take_row(p);
+      conv1_in(p);
+      out_row(q);
+      if (q + 1 >= left) return;
+      h1_row(p);
+    }
+  }
 }
 
 // ------------------------------------------------------------------ training kernels
@@ -1222,11 +1313,11 @@ static int student_launch(Student* s, const uint8_t* vol, int64_t Z, int64_t H, 
                           int64_t out_zs, int Ho, int Wo, int crop, hipStream_t st) {
   hipError_t e;
   if (s->prec == CNN_PREC_BF16) {
-    // strips as tall as still give every SIMD four (a strip computes six input and
-    // two h1 rows beyond its own)
+    // strips as tall as still give every SIMD eight (a strip computes six input and
+    // two h1 rows beyond its own; with four 180 us, with sixteen 164)
     const int64_t nsx = (Wo + SW - 1) / SW;
     int rows = 128;
-    while (rows > 8 && Z * nsx * ((Ho + rows - 1) / rows) < 4096) rows /= 2;
+    while (rows > 8 && Z * nsx * ((Ho + rows - 1) / rows) < 8192) rows /= 2;
     const int64_t nsy = (Ho + rows - 1) / rows, n = Z * nsx * nsy;
     if (n > 2147483647ll - 4) return fail(CNN_EUNSUPPORTED, "student: volume too large");
     hipLaunchKernelGGL(student_strip, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, vol, W, H * W, out, out_rs, out_zs,
