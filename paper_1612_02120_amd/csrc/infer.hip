@@ -7,8 +7,10 @@
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <map>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/emcnn.h"
@@ -436,6 +438,37 @@ int arena_reserve(Net* net, size_t njobs) {
   return CNN_OK;
 }
 
+// The layer dims and inter-layer bytes of each region shape, once per list of
+// regions: such lists are a few shapes many times over.
+struct Shapes {
+  struct Shape {
+    Dims d;
+    std::vector<size_t> lb;  // bytes per slice and layer
+    int64_t zmax;            // slices that fit the workspace budget
+  };
+  const Net* net;
+  std::vector<Shape> all;
+  std::map<std::pair<int, int>, int> index;
+  int h = -1, w = -1, at = -1;  // the last one asked for
+  explicit Shapes(const Net* n) : net(n) {}
+  int find(const Region& r) {
+    if (r.h == h && r.w == w) return at;
+    const auto it = index.emplace(std::make_pair(r.h, r.w), (int)all.size());
+    if (it.second) {
+      Shape s;
+      s.d = layer_dims(net, r.h, r.w);
+      s.lb = layer_bytes(net, s.d);
+      size_t per = 0;
+      for (size_t x : s.lb) per += x;
+      s.zmax = std::max<int64_t>(1, (int64_t)(net->ws_budget / std::max<size_t>(per, 1)));
+      all.push_back(std::move(s));
+    }
+    h = r.h;
+    w = r.w;
+    return at = it.first->second;
+  }
+};
+
 // Split regions whose slices alone exceed the budget, then group regions so a
 // group's inter-layer buffers fit the workspace budget. Writes one job per
 // (group, layer, region) into the arena from `job_off` on and appends the
@@ -444,30 +477,28 @@ int plan_regions(Net* net, const std::vector<Region>& in_regions, size_t job_off
                  size_t& njobs_used, size_t& ws_need, bool dry, bool fixed) {
   const int nl = (int)net->layers.size();
   // per-region geometry; regions with too many slices are split by z
+  Shapes shapes(net);
   std::vector<Region> regs;
-  std::vector<Dims> dims;
-  std::vector<std::vector<size_t>> lbs;
+  std::vector<int> shape;  // of each region
+  regs.reserve(in_regions.size());
+  shape.reserve(in_regions.size());
   for (const Region& r0 : in_regions) {
-    Dims d = layer_dims(net, r0.h, r0.w);
-    std::vector<size_t> lb = layer_bytes(net, d);
-    size_t per = 0;
-    for (size_t x : lb) per += x;
-    int64_t zmax = std::max<int64_t>(1, (int64_t)(net->ws_budget / std::max<size_t>(per, 1)));
+    const int s = shapes.find(r0);
+    const int64_t zmax = shapes.all[s].zmax;
     for (int z0 = 0; z0 < r0.z; z0 += (int)zmax) {
       Region r = r0;
       r.z = (int)std::min<int64_t>(zmax, r0.z - z0);
       r.in = r0.in + (int64_t)z0 * r0.in_zs;
       r.out = r0.out + (int64_t)z0 * r0.out_zs;
       regs.push_back(r);
-      dims.push_back(d);
-      lbs.push_back(lb);
+      shape.push_back(s);
     }
   }
   const int n = (int)regs.size();
   std::vector<size_t> b0(n), b1(n);
   for (int t = 0; t < n; ++t) {
     b0[t] = b1[t] = 0;
-    for (int l = 0; l < nl; ++l) (l % 2 ? b1[t] : b0[t]) += lbs[t][l] * regs[t].z;
+    for (int l = 0; l < nl; ++l) (l % 2 ? b1[t] : b0[t]) += shapes.all[shape[t]].lb[l] * regs[t].z;
   }
   std::vector<std::pair<int, int>> groups;
   ws_need = 0;
@@ -514,6 +545,9 @@ int plan_regions(Net* net, const std::vector<Region>& in_regions, size_t job_off
         b += b1[t];
       }
     }
+    std::map<std::pair<int, int>, int64_t> kinds;  // regions of each shape and slice count
+    if (!fixed)
+      for (int t = G.first; t < G.second; ++t) ++kinds[{shape[t], regs[t].z}];
     const bool fused = first_fused(net);
     for (int l = fused ? 1 : 0; l < nl; ++l) {
       ExecLayer& L = net->layers[l];
@@ -522,9 +556,11 @@ int plan_regions(Net* net, const std::vector<Region>& in_regions, size_t job_off
         const int li = (l == 1 && fused) ? 0 : l;
         pick_variant(net, L, [&] {
           int64_t n = 0;
-          for (int t = G.first; t < G.second; ++t)
-            n += job_items(make_job(L, nullptr, nullptr, regs[t].z, dims[t].hin[li], dims[t].win[li], 0, 0,
-                                    dims[t].hout[l], dims[t].wout[l], 0, 0, 0, nullptr));
+          for (const auto& k : kinds) {
+            const Dims& d = shapes.all[k.first.first].d;
+            n += k.second * job_items(make_job(L, nullptr, nullptr, k.first.second, d.hin[li], d.win[li], 0, 0, d.hout[l],
+                                               d.wout[l], 0, 0, 0, nullptr));
+          }
           return n;
         });
       }
@@ -532,11 +568,11 @@ int plan_regions(Net* net, const std::vector<Region>& in_regions, size_t job_off
       int64_t item0 = 0;
       for (int t = G.first; t < G.second; ++t) {
         const Region& R = regs[t];
-        const Dims& d = dims[t];
+        const Dims& d = shapes.all[shape[t]].d;
         // output of layer q lives in half q % 2 after earlier layers of that parity
         auto buf_of = [&](int q) -> unsigned char* {
           size_t off = 0;
-          for (int p = q % 2; p < q; p += 2) off += lbs[t][p] * R.z;
+          for (int p = q % 2; p < q; p += 2) off += shapes.all[shape[t]].lb[p] * R.z;
           return (q % 2 ? r1[t] : r0[t]) + off;
         };
         const void* in;
@@ -583,14 +619,11 @@ int plan_regions(Net* net, const std::vector<Region>& in_regions, size_t job_off
 
 size_t count_region_jobs(const Net* net, const std::vector<Region>& regs) {
   // upper bound of the jobs plan_regions writes (regions may split by z)
-  const int nl = (int)net->layers.size();
+  const size_t nl = net->layers.size();
+  Shapes shapes(net);
   size_t n = 0;
   for (const Region& r : regs) {
-    Dims d = layer_dims(net, r.h, r.w);
-    std::vector<size_t> lb = layer_bytes(net, d);
-    size_t per = 0;
-    for (size_t x : lb) per += x;
-    int64_t zmax = std::max<int64_t>(1, (int64_t)(net->ws_budget / std::max<size_t>(per, 1)));
+    const int64_t zmax = shapes.all[shapes.find(r)].zmax;
     n += (size_t)((r.z + zmax - 1) / zmax) * nl;
   }
   return n;

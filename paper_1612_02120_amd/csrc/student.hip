@@ -1406,7 +1406,10 @@ extern "C" int student_infer_with_fallback(cnn_student* h, cnn_net* th, const ui
   float* samples = reinterpret_cast<float*>(s->fb);
   int32_t* win_dev = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(s->fb) + sz_samp);
   int32_t* flags = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(s->fb) + sz_samp + sz_win);
-  // 1) seeded sample windows per tile (positions do not depend on the data)
+  // 1) student everywhere, in the teacher's output frame (it runs while the teacher's passes are planned)
+  rc = student_launch(s, vol, Z, H, W, prob, Wo, (int64_t)Ho * Wo, Ho, Wo, crop, st);
+  if (rc) return rc;
+  // 2) seeded sample windows per tile (positions do not depend on the data)
   std::vector<Region> sample_regs, rerun_regs;
   for (int64_t z = 0; z < Z; ++z)
     for (int a = 0; a < ty; ++a)
@@ -1471,9 +1474,6 @@ extern "C" int student_infer_with_fallback(cnn_student* h, cnn_net* th, const ui
   rc = plan_regions(net, rerun_regs, used1, l2, used2, ws2);
   if (rc) return rc;
   if (net->ws != ws_before) return fail(CNN_EHIP, "fallback: internal: workspace moved during planning");
-  // 2) student everywhere, in the teacher's output frame
-  rc = student_launch(s, vol, Z, H, W, prob, Wo, (int64_t)Ho * Wo, Ho, Wo, crop, st);
-  if (rc) return rc;
   if ((e = hipMemcpyAsync(win_dev, s->win_host, nwin * 4, hipMemcpyHostToDevice, st)) != hipSuccess)
     return hip_fail(e, "fallback: window upload");
   if ((e = hipEventRecord(s->win_done, st)) != hipSuccess) return hip_fail(e, "fallback: hipEventRecord");
