@@ -202,9 +202,8 @@ __global__ __launch_bounds__((FirstCfg<PO, COUT, KS, TY, TX, ST>::THREADS)) void
   const ItemRange rg = item_range(js.total_items);
   int cur = 0;
   if (js.table && rg.begin < rg.end) cur = find_job(js.table, js.njobs, rg.begin);
-  for (int64_t item = rg.begin; item < rg.end; item += rg.step) {
-    const LayerJob J = job_at(js, cur, item);
-    if (gated_off(J)) continue;
+  LayerJob J;
+  for (int64_t item = rg.begin; open_item(js, cur, item, rg.end, rg.step, J); item += rg.step) {
     const int64_t local = item - J.item0;
     const int bx = (int)(local % J.tiles_x);
     const int64_t t2 = local / J.tiles_x;
