@@ -31,6 +31,9 @@ sys.path.insert(0, ROOT)
 
 METRIC = "membrane-prob voxels/sec at 1 MI355X and % MFMA peak, plain FP32 vs BF16/FP8/student"
 PEAK_TFLOPS = {"fp32": 157.3, "bf16": 2500.0, "fp8": 5000.0}
+# What the convs of each form can reach: the FP32 ones take three f16 products per
+# FP32 product (operands as f16 hi + lo pairs), so a third of the dense f16 rate
+CONV_TFLOPS = dict(PEAK_TFLOPS, fp32=PEAK_TFLOPS["bf16"] / 3)
 HBM_GBS = 8000.0
 # algorithmic work of net B per output voxel: 2 x (1200 + 57600 + 20736 + 48) MAC
 NET_B_FLOP_PER_VOXEL = 159168
@@ -55,7 +58,7 @@ def kernel_source_sha():
     """sha1 of the conv kernels' source and of the build script (its per-file
     compiler flags change the code of the same source)."""
     h = hashlib.sha1()
-    for f in ("csrc/conv_kernels.hip", "build_lib.py"):
+    for f in ("csrc/conv_kernels.hip", "csrc/conv_split.hip", "csrc/conv_util.h", "build_lib.py"):
         with open(os.path.join(ROOT, "paper_1612_02120_amd", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
@@ -235,7 +238,7 @@ def fastmemb_ss_form(emcnn, torch, em_volume, calibrated_params, dev, stream, ar
         nv = o.numel()
         out[prec] = {"voxels_per_s": nv / (ms * 1e-3), "ms_per_pass": ms, "output": list(o.shape),
                      "path_tflops": nv * FASTMEMB_SS_FLOP_PER_VOXEL / (ms * 1e-3) / 1e12,
-                     "path_mfma_frac": nv * FASTMEMB_SS_FLOP_PER_VOXEL / (ms * 1e-3) / 1e12 / PEAK_TFLOPS[prec],
+                     "path_mfma_frac": nv * FASTMEMB_SS_FLOP_PER_VOXEL / (ms * 1e-3) / 1e12 / CONV_TFLOPS[prec],
                      "layer_ms": pl[:5], "tiles": emcnn.cnn_describe(h)}
         fm = forms.get("fastmemb" if prec == "fp32" else "fastmemb_bf16")
         if fm:
@@ -282,7 +285,7 @@ def maskextend_form(emcnn, torch, dev, stream, args):
                        % (Z, Z),
            "voxels_per_s": nv / dt, "ms_per_pass": dt * 1e3,
            "path_tflops": nv * MASKEXTEND_FLOP_PER_VOXEL / dt / 1e12,
-           "path_mfma_frac": nv * MASKEXTEND_FLOP_PER_VOXEL / dt / 1e12 / PEAK_TFLOPS["fp32"],
+           "path_mfma_frac": nv * MASKEXTEND_FLOP_PER_VOXEL / dt / 1e12 / CONV_TFLOPS["fp32"],
            "layer_ms": [m / reps for m in ms[:6]], "tiles": emcnn.cnn_describe(h)}
     log("maskextend", json.dumps(res))
     del maps, out, h
@@ -412,12 +415,12 @@ def main():
                    "net": "conv5x5 1->48, pool2x2/s1, conv5x5 48->48, pool2x2/s1, conv3x3 48->48, "
                           "conv1x1 48->1 sigmoid",
                    "precision": "fp32", "output_voxels": nvox, "tiles": emcnn.cnn_describe(h)},
-        "path_mfma_frac": path_tflops / PEAK_TFLOPS["fp32"],
+        "path_mfma_frac": path_tflops / CONV_TFLOPS["fp32"],
         "path_tflops": path_tflops,
         "layer_ms": per_layer[:3],
-        "roofline": {"bound": "mfma", "kernel": "conv2 (conv_mfma FP32 48->48 5x5, pool fused)",
-                     "achieved": achieved, "peak": PEAK_TFLOPS["fp32"], "unit": "TFLOP/s",
-                     "frac": (achieved / PEAK_TFLOPS["fp32"]) if achieved else None,
+        "roofline": {"bound": "mfma", "kernel": "conv2 (conv_split FP32 48->48 5x5, pool fused)",
+                     "achieved": achieved, "peak": CONV_TFLOPS["fp32"], "unit": "TFLOP/s",
+                     "frac": (achieved / CONV_TFLOPS["fp32"]) if achieved else None,
                      "flop_per_launch": conv2_flop, "avg_launch_ms": conv2_ms,
                      "traffic": traffic_from_profiles("conv2_fp32_plain_traffic.json")},
     }
@@ -449,8 +452,8 @@ def main():
                         "FoV 53), %d x %d x %d (seed 2) -> %d x %d x %d"
                         % (fm_prec.upper(), Z, H, W, Z, H - hf.R, W - hf.R),
             "voxels_per_s": nvf / (msf * 1e-3), "ms_per_pass": msf,
-            "path_mfma_frac": nvf * FASTMEMB_FLOP_PER_VOXEL / (msf * 1e-3) / 1e12 / PEAK_TFLOPS[fm_prec],
-            "body_conv_tflops": body_tf, "body_conv_frac": [t / PEAK_TFLOPS[fm_prec] for t in body_tf],
+            "path_mfma_frac": nvf * FASTMEMB_FLOP_PER_VOXEL / (msf * 1e-3) / 1e12 / CONV_TFLOPS[fm_prec],
+            "body_conv_tflops": body_tf, "body_conv_frac": [t / CONV_TFLOPS[fm_prec] for t in body_tf],
             "layer_ms": plf[:4], "tiles": emcnn.cnn_describe(hf)}
         log(key, json.dumps(forms[key]))
         del outf, hf

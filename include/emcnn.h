@@ -120,7 +120,12 @@ typedef struct cnn_net cnn_net;
  * weights: host float64, for each conv in order W[cout][cin][k][k] (C order)
  *   followed by b[cout]; n_weights must equal that total. Copied, then packed
  *   and quantised once here:
- *     FP32: all products in FP32 with FP32 accumulation;
+ *     FP32: FP32 weights and activations, FP32 accumulation. A conv whose
+ *           inputs the weights and biases of the layers before it bound (all
+ *           but degenerate nets) takes each operand as a pair of f16 values,
+ *           hi + lo, scaled by powers of two, and three products per pair: 22
+ *           significant bits per operand, no further from the exact result
+ *           than FP32 products (the first conv and the head stay in FP32);
  *     BF16: every conv but the 1x1 head takes bf16 weights and bf16 input
  *           activations (round to nearest even), FP32 accumulation;
  *     FP8:  the first conv as BF16; later convs except the head take e4m3fn
@@ -165,7 +170,10 @@ int cnn_infer(cnn_net* net, const uint8_t* volume_u8, const int64_t dims[3], flo
  * stacked as the input of one section), FP32.
  * maps: device, Z x H x W x C float32 (C fastest), taken as they are (no
  * scaling); dims: host {Z, H, W, C} with C the first conv's cin.
- * prob_out: device, Z x (H-R) x (W-R) float32. Otherwise as cnn_infer. */
+ * prob_out: device, Z x (H-R) x (W-R) float32. Otherwise as cnn_infer.
+ * A pass over the maps takes their largest magnitude, on the device; maps that
+ * reach past 2^20 or are not finite run with FP32 products throughout (both
+ * forms of a layer are enqueued, and a device flag lets one run). */
 int cnn_infer_maps(cnn_net* net, const float* maps, const int64_t dims[4], float* prob_out, void* stream);
 
 /* cnn_infer for callers that cannot allocate device memory: code under HIP
@@ -205,7 +213,10 @@ typedef struct cnn_tile {
  * Results equal per-block cnn_infer on each block's input, bit for bit. */
 int cnn_infer_batch(cnn_net* net, const cnn_tile* tiles, int32_t n, void* stream);
 
-/* Pick, per layer, the fastest compiled tile shape for H x W slices by timing
+/* A layer's tile shape is otherwise picked for each launch from measured costs
+ * of the compiled ones and the launch's size (the result does not depend on
+ * it); a choice made here, by cnn_autotune_batch or by cnn_set_variant stays.
+ * Pick, per layer, the fastest compiled tile shape for H x W slices by timing
  * every candidate on the device (synchronous; repeated launches totalling about
  * 5 ms per candidate). Each candidate's output must be
  * bitwise equal to the default's or it is rejected. cache_path (nullable): a
@@ -387,8 +398,8 @@ int student_infer_with_fallback(cnn_student* s, cnn_net* teacher, const uint8_t*
  * prob: device Z x H x W float32, finite; labels_out: device int32, same
  * shape; work: device int32[Z H W + 1] scratch (caller-owned, overwritten;
  * its last word is not used); Z H W < 2^31 - 1. The call only enqueues
- * three or four kernels on `stream` (descent pointers, one lock-free union-find pass over
- * the seeds, path compression, labels) and never waits on the host. */
+ * three kernels on `stream` (forests of tiles, unions across their faces,
+ * labels) and never waits on the host. */
 int watershed_3d(const float* prob, const int64_t dims[3], float seed_threshold, int32_t* labels_out,
                  int32_t* work, void* stream);
 

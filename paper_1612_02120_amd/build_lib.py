@@ -25,7 +25,8 @@ FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",
 # loop-carried accumulator tuples through AGPR copies every iteration; in the
 # conv kernels it saves the accumulator reads of the epilogues (measured: the
 # FP8 first layer 5 % and FastMemb's first layer 7 % faster, bitwise the same
-# outputs, every other kernel unchanged).
+# outputs, every other kernel unchanged). The student's inference kernel
+# reads 24 accumulator registers per row, each a copy in the other form.
 FILE_FLAGS = {"probe.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
               "conv_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
               "conv_split.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
