@@ -33,7 +33,7 @@
 // A wave works on rows, four consecutive columns to a lane, as one 16-byte access
 // where rows and pointers allow it. On a 32 x 1012^2 membrane map
 // with seeds below 0.05 (44 % of the voxels): ws_tile 173 us (reading, links and
-// writing 93, unions 43, walks 40), ws_border 59, ws_label 109. With the whole forest
+// writing 93, unions 43, walks 40), ws_border 57, ws_label 109. With the whole forest
 // in memory, links, unions, the flattening of runs and walks to the root were passes
 // of 90, 220-234, 55 and 227 us; a step of a walk costs a trip to the L2 or the memory
 // there, and every union is one of 1.4 M compare-and-swaps, on one address where a
@@ -276,12 +276,19 @@ __device__ __forceinline__ int32_t ws_find(int32_t* a, int32_t r) {
   return r;
 }
 
+// The larger root may have been hooked since the caches saw it: a fresh look at it
+// costs a load, where a compare-and-swap that fails is one more on an address that
+// many threads may be at (465 -> 388 us on a map whose seeds are many small runs,
+// 333 -> 324 on one with fewer and longer ones, both 32 x 1012^2).
 __device__ __forceinline__ void ws_unite(int32_t* a, int32_t u, int32_t v) {
   int32_t ru = ws_find(a, u), rv = ws_find(a, v);
   while (ru != rv) {
     const int32_t hi = ru > rv ? ru : rv, lo = ru < rv ? ru : rv;
-    const int32_t old = atomicCAS(a + hi, hi, lo);
-    if (old == hi) return;  // hooked while hi was still a root
+    int32_t old = __hip_atomic_load(a + hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (old == hi) {
+      old = atomicCAS(a + hi, hi, lo);
+      if (old == hi) return;  // hooked while hi was still a root
+    }
     // hi had been hooked (under old < hi): continue from there
     ru = ws_find(a, old);
     rv = lo;
