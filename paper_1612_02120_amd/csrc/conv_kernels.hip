@@ -202,8 +202,14 @@ __global__ __launch_bounds__((FirstCfg<PO, COUT, KS, TY, TX, ST>::THREADS)) void
   const ItemRange rg = item_range(js.total_items);
   int cur = 0;
   if (js.table && rg.begin < rg.end) cur = find_job(js.table, js.njobs, rg.begin);
-  LayerJob J;
-  for (int64_t item = rg.begin; open_item(js, cur, item, rg.end, rg.step, J); item += rg.step) {
+  for (int64_t item = rg.begin; item < rg.end; item += rg.step) {
+    LayerJob J;
+    if constexpr (PO == F32) {
+      if (!open_item(js, cur, item, rg.end, rg.step, J)) break;
+    } else {
+      J = job_at(js, cur, item);
+      if (gated_off(J)) continue;
+    }
     const int64_t local = item - J.item0;
     const int bx = (int)(local % J.tiles_x);
     const int64_t t2 = local / J.tiles_x;

@@ -234,7 +234,7 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
   const ItemRange rg = item_range(js.total_items);
   TileWalk w;
   w.init(js, rg);
-  if (!w.next(js)) return;  // no work for this workgroup (uniform)
+  if (!w.next_open(js)) return;  // no work for this workgroup (uniform)
 
   // origin of the walk's tile: slice, first phase (spaced), tile origin
   auto origin = [&](int& zz, int& py, int& px, int& y0, int& x0) __attribute__((always_inline)) {
@@ -293,7 +293,7 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
     auto advance = [&]() __attribute__((always_inline)) -> bool {
       if (++cb == C::NCB) {
         cb = 0;
-        if (!w.next(js)) return false;
+        if (!w.next_open(js)) return false;
         new_tile();
       }
       new_stage();
@@ -544,7 +544,7 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
     sel ^= 1;
     if (++cb == C::NCB) {
       cb = 0;
-      if (!w.next(js)) return;
+      if (!w.next_open(js)) return;
     }
   }
 }
