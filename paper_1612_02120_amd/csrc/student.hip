@@ -128,7 +128,7 @@ __global__ __launch_bounds__((TY * TX)) void student_fused(const uint8_t* __rest
 // registers, where LDS turns each row once): no barrier, no halo rows but the strip's
 // first six, and the loads of the row after next in flight. One sigmoid and one store
 // per lane and row. On 8 x 2048^2: 312 us with tiles of 16 x 64 outputs shared by
-// four waves and half of each MFMA empty, 165 now, of which the vector instructions
+// four waves and half of each MFMA empty, 157 now, of which the vector instructions
 // (95 per row of 62 outputs, 16 of them the sigmoid) fill 77 % and LDS about as much.
 
 // Outputs (y0 .. y0 + n - 1, x) of slice z, one lane each (see where it is called).
