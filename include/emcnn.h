@@ -171,9 +171,12 @@ int cnn_infer(cnn_net* net, const uint8_t* volume_u8, const int64_t dims[3], flo
  * maps: device, Z x H x W x C float32 (C fastest), taken as they are (no
  * scaling); dims: host {Z, H, W, C} with C the first conv's cin.
  * prob_out: device, Z x (H-R) x (W-R) float32. Otherwise as cnn_infer.
- * A pass over the maps takes their largest magnitude, on the device; maps that
- * reach past 2^20 or are not finite run with FP32 products throughout (both
- * forms of a layer are enqueued, and a device flag lets one run). */
+ * Each FP32 operand of a conv is the exact sum of three bf16 values, and a
+ * product six of theirs (all but those below 2^-24 of it): an output depends on
+ * the maps in its own window alone, whatever their range elsewhere. Maps that
+ * reach past 2^20 or are not finite somewhere (found by a pass over them, on the
+ * device) run with FP32 products throughout: both forms of a layer are enqueued,
+ * and a device flag lets one run. */
 int cnn_infer_maps(cnn_net* net, const float* maps, const int64_t dims[4], float* prob_out, void* stream);
 
 /* cnn_infer for callers that cannot allocate device memory: code under HIP

@@ -55,16 +55,14 @@ struct JobSet {
 };
 
 // Range of one call's real-valued input maps, found on the device before the
-// layers run (nets on more than one input channel). The scales of split convs
-// (conv_split) assume maps in [-1, 1]; maps in [-2^k, 2^k] scale every bound by
-// at most 2^k, so the operands take 2^-k more and the sums 2^k. ok / bad gate the
-// split kernels and the FP32 ones that run instead where the maps are too large
-// (k > kMapsRangeMax) or not finite.
+// layers run (nets on more than one input channel). ok / bad gate the split
+// kernels and the FP32 ones that run instead where a map reaches past
+// 2^kMapsRangeMax or is not finite: an infinite operand has no parts, and the
+// bounds that keep every activation finite (split_bounds_ok) start from this range.
 struct MapsRange {
-  float down, up;  // 2^-k, 2^k
   int32_t ok, bad;
   uint32_t top;  // running maximum of the maps' magnitudes (float bits); 0 between calls
-  uint32_t pad_[3];
+  uint32_t pad_;
 };
 constexpr int kMapsRangeMax = 20;
 
@@ -80,7 +78,6 @@ struct ConvParams {
   const float* b1;       // [cin] first-layer bias
   float w1_inv_scale;    // FP8: first-layer output codes e4m3(v * w1_inv_scale)
   float pad_;
-  const MapsRange* range;  // split convs of nets on real-valued maps (nullptr: none)
 };
 
 struct FirstParams {
@@ -125,8 +122,9 @@ struct VariantInfo {
   int rowq = 0;         // 1: row-quad K order (k_slot); 0: flattened
   int groups = 0;       // 1: a work item is a tile of four phases whose max filters share
                         // fragments (spaced layers whose max filter has half their spacing)
-  int split = 0;        // FP32 operands as f16 hi + lo pairs (conv_split); 2: max-out row order
+  int split = 0;        // FP32 operands as 16-bit parts (conv_split); 2: max-out row order
   TileCost cost = {};
+  int parts = 0;        // of a split operand: 2 (f16 pairs) or 3 (bf16 triples)
 };
 
 // K order of the implicit-GEMM convs over one channel block. K slot c is read

@@ -1,24 +1,33 @@
 // FP32 convolutions on the 16-bit matrix cores, for gfx950.
 //
-// The FP32 MFMA (16x16x4) runs at 1/16 of the rate of the f16 one (16x16x32),
+// The FP32 MFMA (16x16x4) runs at 1/16 of the rate of the 16-bit ones (16x16x32),
 // and the FP32 body convs are bound by it (conv_mfma: 84 % of its peak). Here
-// every FP32 operand is the sum of two f16 values, x = hi + lo with
-// hi = f16(x), lo = f16(x - hi), and each product is three f16 products
-// accumulated in FP32: hi hi + hi lo + lo hi (lo lo is below 2^-22 of the
-// product). hi + lo holds x to within one unit of the 24th bit, and a K = 32
-// MFMA rounds its FP32 accumulator an eighth as often as K = 4 steps do; the
-// measured error against 64 bits is no larger than the FP32 MFMA's (rms on a
-// K = 1200 / 512 / 432 contraction: 3.9 / 2.6 / 2.3e-7 against 4.5 / 4.0 /
-// 2.6e-7 of the result's rms).
+// every FP32 operand is a sum of 16-bit values, and a product is the products of
+// the parts that matter, accumulated in FP32, as Ootomo and Yokota (2022,
+// "Recovering single precision accuracy from Tensor Cores ...") do with f16 and
+// Henry, Tang and Heinecke (2019, "Leveraging the bfloat16 artificial
+// intelligence datatype for higher-precision computations") with bf16:
 //
-// f16 has a 5-bit exponent, so both sides are scaled by powers of two that the
-// host derives (exactly, see split_scales in runtime.hip): each input channel
-// by a bound on its activations, which uint8 input and known weights give by
-// interval arithmetic (no value can overflow whatever the image), and each
-// output channel's weights by their largest magnitude. Values down to 2^-11 of
-// a channel's bound keep all their bits; below, the error is 2^-40 of the bound
-// (f16 subnormals, which the MFMA does not flush). Nets whose bounds or weights
-// are not finite or leave the exponent range keep the FP32 kernels.
+// * Triples, x = x0 + x1 + x2 with x0 = bf16(x), x1 = bf16(x - x0), x2 the rest:
+//   bf16 has FP32's exponents and 3 x 8 bits hold all 24, so a triple is x itself.
+//   Six products (the three others are below 2^-24 of the whole). Nothing depends
+//   on the range of the values.
+// * Pairs, x = hi + lo with hi = f16(x), lo = f16(x - hi), and three products, hi
+//   hi + hi lo + lo hi (lo lo is below 2^-22 of the product): half the work.
+//   hi + lo holds x to within one unit of the 24th bit, and a K = 32 MFMA rounds
+//   its FP32 accumulator an eighth as often as K = 4 steps do; the measured error
+//   against 64 bits is no larger than the FP32 MFMA's (rms on a K = 1200 / 512 /
+//   432 contraction: 3.9 / 2.6 / 2.3e-7 against 4.5 / 4.0 / 2.6e-7 of the
+//   result's rms).
+//
+// f16 has a 5-bit exponent, so both sides of a pair's products are scaled by powers
+// of two that the host derives (exactly, see split_scales in runtime.hip): each
+// input channel by a bound on its activations, which uint8 input and known weights
+// give by interval arithmetic, and each output channel's weights by their largest
+// magnitude. Values down to 2^-11 of a channel's bound keep all their bits; below,
+// the error is 2^-40 of the bound (f16 subnormals, which the MFMA does not flush).
+// Nets whose bounds or weights are not finite or leave the exponent range keep the
+// FP32 kernels, and nets on real-valued maps, which have no bound, take triples.
 //
 // The kernel is warp-specialised as conv_ws: NCW consumer waves run the
 // implicit GEMM with both operands in LDS, NPW producer waves fill it. A stage
@@ -29,9 +38,11 @@
 // barrier per slice. While the consumers run slice w the producers store slice
 // w + 1 and the w-th part of the next stage's operand tile, and issue the loads
 // of the parts after those: the loads and registers are spread evenly over the
-// stage. LDS reads per MFMA are 2/3 of the BF16 kernel's (two fragments of each
-// operand feed three MFMAs), so the matrix cores, not the LDS, are the limit.
+// stage. LDS reads per MFMA are 2/3 of the BF16 kernel's with pairs (two fragments
+// of each operand feed three MFMAs) and half with triples (three feed six).
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "common.h"
 #include "conv_util.h"
@@ -41,19 +52,22 @@ namespace emcnn {
 
 typedef _Float16 h4v __attribute__((ext_vector_type(4)));
 typedef _Float16 h8v __attribute__((ext_vector_type(8)));
+typedef __bf16 b4v __attribute__((ext_vector_type(4)));
 
 // Kinds of layer: a plain conv (bias, ReLU, NHWC output), the same with the
 // 1x1 sigmoid head fused, a spaced max-out conv per phase, and over groups of
 // four phases whose max filters share fragments.
 enum SplitKind : int { SK_RELU = 0, SK_HEAD = 1, SK_PHASE = 2, SK_GROUP = 3 };
 
-template <int CIN, int COUT, int KS, int KIND, int TY, int TX, int NCW, int NPW, int CB_, int SS_>
+// NP: 16-bit values per operand, 2 (f16 pairs) or 3 (bf16 triples).
+template <int CIN, int COUT, int KS, int KIND, int TY, int TX, int NCW, int NPW, int CB_, int SS_, int NP>
 struct CfgSplit {
+  static_assert(NP == 2 || NP == 3, "pairs or triples");
   static constexpr int KSZ = KS, CB = CB_, SS = SS_;
   static constexpr int NMEM = KIND == SK_GROUP ? 4 : 1;
   static_assert(CIN % 4 == 0 && CB % 8 == 0, "whole 16-byte chunks, stored and of f16");
   // channels past CIN of the last block are zeros (12 input maps: 16 channels, a
-  // quarter of the products padding, still a third of the FP32 MFMA's time)
+  // quarter of the products padding)
   static constexpr int NCB = (CIN + CB - 1) / CB;
   static constexpr int CINP = NCB * CB;
   static constexpr int NCIN = CIN;
@@ -64,14 +78,14 @@ struct CfgSplit {
   static constexpr int NB = COUT / 16;
   static_assert(NB * 16 == COUT, "COUT must be a multiple of 16");
   static constexpr int LR = TY + KS - 1, LC = TX + KS - 1;
-  // hi and lo chunks in separate halves of a buffer: 32 B (16 channels) or
+  // the parts' chunks in separate planes of a buffer: 32 B (16 channels) or
   // 16 B per pixel in each. A half-wave reads 16 pixels x 2 lane groups: 512
   // contiguous bytes (32 B), or two 256-byte runs 16 B apart whose common
   // addresses broadcast (16 B), free of bank conflicts without padding.
   static constexpr int PSB = 16 * NCHB;
-  static constexpr int HALF = NMEM * LR * LC * PSB;
-  static constexpr int BUF = 2 * HALF;
-  static constexpr int STEPB = NB * 2 * 1024;  // packed weights of one group-step
+  static constexpr int PLANE = NMEM * LR * LC * PSB;
+  static constexpr int BUF = NP * PLANE;
+  static constexpr int STEPB = NB * NP * 1024;  // packed weights of one group-step
   static constexpr int SLB = SS * STEPB;
   static constexpr int WOFF = 2 * BUF;
   static constexpr int LDS = WOFF + 2 * SLB;
@@ -84,7 +98,7 @@ struct CfgSplit {
   static_assert(NMEM == 1 || (TX == 16 && TY % WROWS == 0), "a consumer wave's rows lie in one member's tile");
   static constexpr int THREADS = (NCW + NPW) * 64;
   static_assert(THREADS <= 1024, "workgroup size limit");
-  static constexpr size_t PACKB = (size_t)NCB * NSL * SLB;  // fragments; then iscale[CINP], oscale[COUT]
+  static constexpr size_t PACKB = (size_t)NCB * NSL * SLB;  // fragments; pairs: then iscale[CINP], oscale[COUT]
 };
 
 // Four scaled FP32 values to f16 hi and lo halves (8 bytes each).
@@ -96,11 +110,21 @@ __device__ __forceinline__ void split4(f4 v, f4 sc, u2v& hi, u2v& lo) {
   lo = __builtin_bit_cast(u2v, l);
 }
 
+// Four FP32 values to the three bf16 values whose sum each is.
+__device__ __forceinline__ void split4(f4 x, u2v (&part)[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const b4v b = __builtin_convertvector(x, b4v);
+    part[k] = __builtin_bit_cast(u2v, b);
+    if (k < 2) x = x - __builtin_convertvector(b, f4);
+  }
+}
+
 // The producers' walk over the operand tile of one stage: item t = 4 channels
 // (16 stored bytes) of a 2x2 block of operand pixels (plain, POOL), of one
 // operand position of all four members (group) or of one operand pixel. NL
 // 16-byte loads per item; the max filter runs on the FP32 values.
-template <class C, int KIND, bool POOL, int NPT>
+template <class C, int KIND, bool POOL, int NPT, int NP>
 struct SplitStage {
   static constexpr int NC4 = C::CB / 4;
   static constexpr bool BLK = KIND <= SK_HEAD && POOL;
@@ -173,10 +197,11 @@ struct SplitStage {
     return f4{fmaxf(a[0], b[0]), fmaxf(a[1], b[1]), fmaxf(a[2], b[2]), fmaxf(a[3], b[3])};
   }
   static __device__ __forceinline__ void put(unsigned char* lds, int pix, int cg, f4 v, f4 sc) {
-    u2v hi, lo;
-    split4(v, sc, hi, lo);
-    st<u2v>(lds + pix * C::PSB + cg * 8, hi);
-    st<u2v>(lds + C::HALF + pix * C::PSB + cg * 8, lo);
+    u2v part[NP];
+    if constexpr (NP == 2) split4(v, sc, part[0], part[1]);
+    else split4(v, part);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) st<u2v>(lds + k * C::PLANE + pix * C::PSB + cg * 8, part[k]);
   }
   __device__ __forceinline__ void store_item(int k, int n, unsigned char* lds, f4 sc, int ptid) const {
     const int t = ptid + k * NPT;
@@ -219,10 +244,10 @@ struct SplitStage {
   }
 };
 
-template <int CIN, int COUT, int KS, bool POOL, int KIND, int TY, int TX, int NCW, int NPW, int CB, int SS>
-__global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS>::THREADS)) void conv_split(
+template <int CIN, int COUT, int KS, bool POOL, int KIND, int TY, int TX, int NCW, int NPW, int CB, int SS, int NP>
+__global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS, NP>::THREADS)) void conv_split(
     JobSet js, ConvParams prm) {
-  using C = CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS>;
+  using C = CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS, NP>;
   constexpr bool SPACED = KIND >= SK_PHASE;
   constexpr int MCOLS = TX / 16;
   constexpr int ELB = CIN * 4;  // bytes per stored input pixel (NHWC)
@@ -248,12 +273,11 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
     // ---------------- producer waves
     const int ptid = tid - NCW * 64;
     constexpr int NPT = NPW * 64;
-    SplitStage<C, KIND, POOL, NPT> a;
+    SplitStage<C, KIND, POOL, NPT, NP> a;
     WStage<C::SLB, NPT> ws;
     a.elb = ELB;
     const gbyte* isc = wglob + C::PACKB + (ptid % (C::CB / 4)) * 16;  // this thread's channel scales
-    f4 sc;
-    const float down = prm.range ? ldf(&prm.range->down, 0) : 1.0f;
+    f4 sc = {};
     int cb = 0;
     const gbyte* tile0 = nullptr;  // channel 0 of the tile's slice (spaced: of its fragment)
     auto new_tile = [&]() __attribute__((always_inline)) {
@@ -287,7 +311,7 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
     };
     auto new_stage = [&]() __attribute__((always_inline)) {
       a.base = tile0 + cb * (C::CB * 4);
-      sc = ld<f4>(isc + cb * (C::CB * 4)) * down;
+      if constexpr (NP == 2) sc = ld<f4>(isc + cb * (C::CB * 4));
     };
     // the next stage of the walk; false past the last
     auto advance = [&]() __attribute__((always_inline)) -> bool {
@@ -359,10 +383,15 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
   // four channels of pixel n16, stored as 16 bytes. With the fused head the
   // other way round: channel n16 of pixels 4g .. 4g + 3 (head_epilogue).
   constexpr bool TRANS = KIND != SK_HEAD;
+  static_assert(NP == 2 || TRANS, "triples: max-out convs");
   f4 acc[C::MW][C::NB];
   int cb = 0, sel = 0, wsel = 0;
 
-  // one group-step: three products per (m-block, n-block), small terms first
+  // one group-step: three (pairs) or six (triples) products per (m-block, n-block), small terms first
+  using Frag16 = std::conditional_t<NP == 2, h8v, bf16x8>;
+  // the products: part of the pixels, part of the weights (triples: weights part by part)
+  constexpr int XP[6] = {NP == 2 ? 1 : 0, NP == 2 ? 0 : 1, 0, 2, 1, 0};
+  constexpr int WP[6] = {NP == 2 ? 0 : 2, 1, NP == 2 ? 0 : 1, 0, 0, 0};
   auto step = [&](const unsigned char* abase, const unsigned char* wl, int s) __attribute__((always_inline)) {
     // LDS offset of this lane group's chunk: slot 4 s + g, chunk-major inside a tap
     int o[4];
@@ -373,62 +402,85 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
     }
     const int off = g < 2 ? (g == 0 ? o[0] : o[1]) : (g == 2 ? o[2] : o[3]);
     const unsigned char* ap = abase + off;
-    auto mm = [&](f4& c, const h8v& x, const h8v& wv) __attribute__((always_inline)) {
-      if constexpr (TRANS) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(wv, x, c, 0, 0, 0);
+    auto mm = [&](f4& c, const Frag16& x, const Frag16& wv) __attribute__((always_inline)) {
+      if constexpr (NP == 3) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, x, c, 0, 0, 0);
+      else if constexpr (TRANS) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(wv, x, c, 0, 0, 0);
       else c = __builtin_amdgcn_mfma_f32_16x16x32_f16(x, wv, c, 0, 0, 0);
     };
-    auto a_at = [&](int u) __attribute__((always_inline)) {
-      return ap + ((u / MCOLS) * C::LC + (u % MCOLS) * 16) * C::PSB;
+    auto a_at = [&](int u, int k) __attribute__((always_inline)) {
+      return ap + ((u / MCOLS) * C::LC + (u % MCOLS) * 16) * C::PSB + k * C::PLANE;
     };
+    auto w_at = [&](int nb, int k) __attribute__((always_inline)) { return wl + (nb * NP + k) * 1024; };
     // the operand with fewer fragments stays in registers, the other streams
-    if constexpr (C::NB <= C::MW) {
-      h8v bh[C::NB], bl[C::NB];
+    if constexpr (NP == 2 && C::NB <= C::MW) {
+      Frag16 wv[C::NB][NP];
 #pragma unroll
-      for (int nb = 0; nb < C::NB; ++nb) {
-        bh[nb] = ld<h8v>(wl + (nb * 2) * 1024);
-        bl[nb] = ld<h8v>(wl + (nb * 2 + 1) * 1024);
-      }
+      for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+        for (int k = 0; k < NP; ++k) wv[nb][k] = ld<Frag16>(w_at(nb, k));
 #pragma unroll
       for (int u = 0; u < C::MW; ++u) {
-        const h8v ah = ld<h8v>(a_at(u)), al = ld<h8v>(a_at(u) + C::HALF);
+        Frag16 x[NP];
 #pragma unroll
-        for (int nb = 0; nb < C::NB; ++nb) mm(acc[u][nb], al, bh[nb]);
+        for (int k = 0; k < NP; ++k) x[k] = ld<Frag16>(a_at(u, k));
 #pragma unroll
-        for (int nb = 0; nb < C::NB; ++nb) mm(acc[u][nb], ah, bl[nb]);
+        for (int t = 0; t < 3; ++t)
 #pragma unroll
-        for (int nb = 0; nb < C::NB; ++nb) mm(acc[u][nb], ah, bh[nb]);
+          for (int nb = 0; nb < C::NB; ++nb) mm(acc[u][nb], x[XP[t]], wv[nb][WP[t]]);
       }
     } else {
-      h8v ah[C::MW], al[C::MW];
+      Frag16 x[C::MW][NP];
 #pragma unroll
-      for (int u = 0; u < C::MW; ++u) {
-        ah[u] = ld<h8v>(a_at(u));
-        al[u] = ld<h8v>(a_at(u) + C::HALF);
-      }
-      // the next n-block's weights are loaded ahead of this one's MFMAs, and no
-      // earlier (the scheduler would hoist them until the registers spill)
-      h8v bh[2], bl[2];
-      bh[0] = ld<h8v>(wl);
-      bl[0] = ld<h8v>(wl + 1024);
+      for (int u = 0; u < C::MW; ++u)
 #pragma unroll
-      for (int nb = 0; nb < C::NB; ++nb) {
-        if (nb + 1 < C::NB) {
-          bh[(nb + 1) & 1] = ld<h8v>(wl + (nb * 2 + 2) * 1024);
-          bl[(nb + 1) & 1] = ld<h8v>(wl + (nb * 2 + 3) * 1024);
+        for (int k = 0; k < NP; ++k) x[u][k] = ld<Frag16>(a_at(u, k));
+      if constexpr (NP == 2) {
+        // the next n-block's weights are loaded ahead of this one's MFMAs, and no
+        // earlier (the scheduler would hoist them until the registers spill)
+        Frag16 wv[2][NP];
+#pragma unroll
+        for (int k = 0; k < NP; ++k) wv[0][k] = ld<Frag16>(w_at(0, k));
+#pragma unroll
+        for (int nb = 0; nb < C::NB; ++nb) {
+          if (nb + 1 < C::NB) {
+#pragma unroll
+            for (int k = 0; k < NP; ++k) wv[(nb + 1) & 1][k] = ld<Frag16>(w_at(nb + 1, k));
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int u = 0; u < C::MW; ++u) mm(acc[u][nb], x[u][XP[t]], wv[nb & 1][WP[t]]);
         }
-        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        // The small products are summed in accumulators of their own, which a sum takes
+        // with the large one: six roundings of a whole sum per step would cost what the
+        // operands gain (MaskExtend's rms error against 64 bits 1.26 of that with pairs,
+        // 0.6 this way, for 8 % of the time). A part of the weights makes way for the next
+        // n-block's where its last product is issued.
+        Frag16 wv[3];
 #pragma unroll
-        for (int u = 0; u < C::MW; ++u) mm(acc[u][nb], al[u], bh[nb & 1]);
+        for (int k = 0; k < 3; ++k) wv[k] = ld<Frag16>(w_at(0, k));
 #pragma unroll
-        for (int u = 0; u < C::MW; ++u) mm(acc[u][nb], ah[u], bl[nb & 1]);
+        for (int nb = 0; nb < C::NB; ++nb) {
+          f4 low[C::MW];
 #pragma unroll
-        for (int u = 0; u < C::MW; ++u) mm(acc[u][nb], ah[u], bh[nb & 1]);
+          for (int t = 0; t < 6; ++t) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < C::MW; ++u) {
+              if (t == 0) low[u] = f4{0.f, 0.f, 0.f, 0.f};
+              if (t == 5) acc[u][nb] += low[u];
+              mm(t < 5 ? low[u] : acc[u][nb], x[u][XP[t]], wv[WP[t]]);
+            }
+            if (nb + 1 < C::NB && (t == 5 || WP[t + 1] != WP[t])) wv[WP[t]] = ld<Frag16>(w_at(nb + 1, WP[t]));
+          }
+        }
       }
     }
   };
 
   const gbyte* osc_p = wglob + C::PACKB + C::CINP * 4;
-  const float up = prm.range ? ldf(&prm.range->up, 0) : 1.0f;
   auto epilogue = [&]() __attribute__((always_inline)) {
     int zz, py, px, y0, x0;
     origin(zz, py, px, y0, x0);
@@ -438,7 +490,7 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
 #pragma unroll
       for (int nb = 0; nb < C::NB; ++nb) {
         bias[nb] = ldf(prm.bias, nb * 16 + n16);
-        osc[nb] = ld<float>(osc_p + (nb * 16 + n16) * 4) * up;
+        osc[nb] = ld<float>(osc_p + (nb * 16 + n16) * 4);
         hw[nb] = ldf(prm.head_w, nb * 16 + n16);
       }
       head_epilogue<C::MW, C::NB>(
@@ -459,13 +511,14 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
 #pragma unroll
         for (int nb = 0; nb < C::NB; ++nb) {
           bsv[nb] = ld<f4>(gin(prm.bias) + chan4(nb));
-          scv[nb] = ld<f4>(osc_p + chan4(nb)) * up;
+          if constexpr (NP == 2) scv[nb] = ld<f4>(osc_p + chan4(nb));
         }
       }
-      // this lane's four channels of n-block nb: acc * sc + bs
+      // this lane's four channels of n-block nb: acc * sc + bs (triples are not scaled)
       auto value = [&](f4 v, int nb) __attribute__((always_inline)) {
         const f4 bs = PRE ? bsv[PRE ? nb : 0] : ld<f4>(gin(prm.bias) + chan4(nb));
-        const f4 sc = PRE ? scv[PRE ? nb : 0] : ld<f4>(osc_p + chan4(nb)) * up;
+        if constexpr (NP == 3) return v + bs;
+        const f4 sc = PRE ? scv[PRE ? nb : 0] : ld<f4>(osc_p + chan4(nb));
         f4 t;
 #pragma unroll
         for (int k = 0; k < 4; ++k) t[k] = fmaf(v[k], sc[k], bs[k]);
@@ -551,25 +604,33 @@ __global__ __launch_bounds__((CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB
 
 // ---------------------------------------------------------------- registry
 
-#define EMCNN_SPLITN(NAME, CIN, COUT, KS, POOL, KIND, TY, TX, NCW, NPW, CB, SS, LONE, RATE)               \
+#define EMCNN_SPLITN(NAME, CIN, COUT, KS, POOL, KIND, TY, TX, NCW, NPW, CB, SS, NP, LONE, RATE)           \
   VariantInfo{F32, CIN, COUT, KS, KIND >= SK_PHASE ? 1 : POOL, KIND == SK_HEAD, TY, TX,                    \
-              CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS>::MW,                                 \
-              CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS>::THREADS, CB, 8, 1,                  \
-              CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS>::NSL * SS, 0, 0,                     \
-              KIND >= SK_PHASE ? 1 : 0, CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS>::LDS,      \
-              reinterpret_cast<const void*>(&conv_split<CIN, COUT, KS, POOL, KIND, TY, TX, NCW, NPW, CB, SS>), \
-              NAME, 0, KIND == SK_GROUP, KIND >= SK_PHASE ? 2 : 1, TileCost{LONE, RATE}}
+              CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS, NP>::MW,                             \
+              CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS, NP>::THREADS, CB, 8, 1,              \
+              CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS, NP>::NSL * SS, 0, 0,                 \
+              KIND >= SK_PHASE ? 1 : 0, CfgSplit<CIN, COUT, KS, KIND, TY, TX, NCW, NPW, CB, SS, NP>::LDS,  \
+              reinterpret_cast<const void*>(&conv_split<CIN, COUT, KS, POOL, KIND, TY, TX, NCW, NPW, CB, SS, NP>), \
+              NAME, 0, KIND == SK_GROUP, KIND >= SK_PHASE ? 2 : 1, TileCost{LONE, RATE}, NP}
 #define EMCNN_SPLIT(CIN, COUT, KS, POOL, HEAD, TY, TX, NCW, NPW, CB, SS, LONE, RATE)                       \
   EMCNN_SPLITN("conv_split<" #CIN "," #COUT "," #KS "," #POOL "," #HEAD "," #TY "," #TX "," #NCW "," #NPW "," #CB \
                "," #SS ">",                                                                                 \
-               CIN, COUT, KS, POOL, (HEAD ? SK_HEAD : SK_RELU), TY, TX, NCW, NPW, CB, SS, LONE, RATE)
+               CIN, COUT, KS, POOL, (HEAD ? SK_HEAD : SK_RELU), TY, TX, NCW, NPW, CB, SS, 2, LONE, RATE)
 #define EMCNN_SPLIT_PHASE(CIN, COUT, KS, POOL, TY, TX, NCW, NPW, CB, SS, LONE, RATE)                        \
   EMCNN_SPLITN("conv_phase<F32S," #CIN "," #COUT "," #KS "," #POOL "," #TY "," #TX "," #NCW "," #NPW "," #CB "," #SS \
                ">",                                                                                         \
-               CIN, COUT, KS, POOL, SK_PHASE, TY, TX, NCW, NPW, CB, SS, LONE, RATE)
+               CIN, COUT, KS, POOL, SK_PHASE, TY, TX, NCW, NPW, CB, SS, 2, LONE, RATE)
 #define EMCNN_SPLIT_GROUP(CIN, COUT, KS, TY, NCW, NPW, CB, SS, LONE, RATE)                                  \
   EMCNN_SPLITN("conv_phase_group<F32S," #CIN "," #COUT "," #KS "," #TY "," #NCW "," #NPW "," #CB "," #SS ">", \
-               CIN, COUT, KS, true, SK_GROUP, TY, 16, NCW, NPW, CB, SS, LONE, RATE)
+               CIN, COUT, KS, true, SK_GROUP, TY, 16, NCW, NPW, CB, SS, 2, LONE, RATE)
+// the same over bf16 triples
+#define EMCNN_SPLIT3_PHASE(CIN, COUT, KS, POOL, TY, TX, NCW, NPW, CB, SS, LONE, RATE)                       \
+  EMCNN_SPLITN("conv_phase<F32S,3xbf16," #CIN "," #COUT "," #KS "," #POOL "," #TY "," #TX "," #NCW "," #NPW "," #CB \
+               "," #SS ">",                                                                                 \
+               CIN, COUT, KS, POOL, SK_PHASE, TY, TX, NCW, NPW, CB, SS, 3, LONE, RATE)
+#define EMCNN_SPLIT3_GROUP(CIN, COUT, KS, TY, NCW, NPW, CB, SS, LONE, RATE)                                 \
+  EMCNN_SPLITN("conv_phase_group<F32S,3xbf16," #CIN "," #COUT "," #KS "," #TY "," #NCW "," #NPW "," #CB "," #SS ">", \
+               CIN, COUT, KS, true, SK_GROUP, TY, 16, NCW, NPW, CB, SS, 3, LONE, RATE)
 
 // First entry per signature: the default; last two arguments its TileCost. All shapes of a signature contract in
 // the same order (16-channel stages), so their outputs are bitwise the same.
@@ -598,15 +659,21 @@ static const VariantInfo kSplit[] = {
     EMCNN_SPLIT_GROUP(32, 64, 4, 4, 8, 4, 16, 2, 13, 12.3),
     EMCNN_SPLIT_PHASE(32, 64, 4, true, 16, 32, 8, 4, 16, 2, 21.5, 20.6),
     EMCNN_SPLIT_PHASE(32, 64, 4, true, 8, 32, 8, 4, 16, 2, 13, 12),
-    // MaskExtend (4 x 800^2): twelve maps, no max filter; 32 -> 80 (0.58 ms; 4-row
-    // members 0.61), 40 -> 96 in 8-channel stages (0.81; 0.94), 48 -> 112 (1.02 with
-    // 8 consumer waves, 1.05 with 4 of twice the m-blocks), 56 -> 128 (1.32; 1.32).
-    // 8-row members of the two widest would need 112 and 128 accumulators and spill.
-    EMCNN_SPLIT_PHASE(12, 64, 4, false, 16, 32, 8, 4, 16, 2, 14, 14.5),
-    EMCNN_SPLIT_PHASE(12, 64, 4, false, 8, 32, 8, 4, 16, 2, 8, 7.4),
-    EMCNN_SPLIT_GROUP(32, 80, 4, 8, 8, 4, 16, 1, 28, 29.7), EMCNN_SPLIT_GROUP(32, 80, 4, 4, 8, 4, 16, 2, 15, 15.8),
-    EMCNN_SPLIT_GROUP(40, 96, 4, 8, 8, 4, 8, 2, 39, 39.9), EMCNN_SPLIT_GROUP(40, 96, 4, 4, 8, 4, 8, 2, 22, 23.5),
-    EMCNN_SPLIT_GROUP(48, 112, 4, 4, 8, 4, 16, 2, 0, 0), EMCNN_SPLIT_GROUP(56, 128, 4, 4, 8, 4, 8, 2, 0, 0),
+    // MaskExtend, on bf16 triples. ms on 2 x 512 x 600 and 4 x 800^2 maps (f16 pairs, for
+    // whose scales real-valued maps have no bound; the FP32 kernels):
+    //   12 -> 64, no max filter   0.10 and 0.41 (0.07 and 0.30; 0.14 and 0.62)
+    //   32 -> 80                  0.23 and 0.91 (0.18 and 0.58; 0.53 and 2.30), 4-row members 0.23 and 0.96
+    //   40 -> 96                  0.29 and 1.38 (0.21 and 0.81; 0.66 and 3.16), 4-row members 0.29 and 1.38
+    //   48 -> 112                 0.44 and 1.71 (0.30 and 1.02; 0.94 and 3.74), 6-row members 10 % slower
+    //   56 -> 128                 0.42 and 2.07 (0.24 and 1.32; 0.89 and 4.63), 6-row members 27 % slower
+    // In 8-channel stages: 16-channel ones leave room for one weight slice per barrier
+    // (32 -> 80 2 % slower, 48 -> 112 4 %). Taller members spill: 3 x 4 registers of
+    // weights and of each m-block's pixels beside the accumulators.
+    EMCNN_SPLIT3_PHASE(12, 64, 4, false, 24, 16, 8, 4, 16, 1, 15, 15.4),
+    EMCNN_SPLIT3_PHASE(12, 64, 4, false, 8, 32, 8, 4, 16, 1, 10.5, 10.9),
+    EMCNN_SPLIT3_GROUP(32, 80, 4, 6, 8, 4, 8, 2, 34, 35.3), EMCNN_SPLIT3_GROUP(32, 80, 4, 4, 8, 4, 8, 2, 24, 24.9),
+    EMCNN_SPLIT3_GROUP(40, 96, 4, 6, 8, 4, 8, 1, 50, 51.5), EMCNN_SPLIT3_GROUP(40, 96, 4, 4, 8, 4, 8, 2, 33.5, 34.7),
+    EMCNN_SPLIT3_GROUP(48, 112, 4, 4, 8, 4, 8, 2, 0, 0), EMCNN_SPLIT3_GROUP(56, 128, 4, 4, 8, 4, 8, 2, 0, 0),
 };
 
 int split_variant_count() { return (int)(sizeof(kSplit) / sizeof(kSplit[0])); }

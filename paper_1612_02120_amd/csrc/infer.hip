@@ -188,7 +188,6 @@ int launch_layer(Net* net, const ExecLayer& L, const JobSet& js, int grid, hipSt
     p.head_w = L.head_w;
     p.head_b = L.head_b;
     p.out_inv_scale = L.out_inv_scale;
-    p.range = net->range;
     if (conv_variant(L.variant)->fused) {
       const ExecLayer& L0 = net->layers[0];
       p.w1 = L0.wpack;
@@ -288,14 +287,10 @@ __global__ __launch_bounds__(256) void maps_top(const float* __restrict__ x, int
   if (threadIdx.x == 0) atomicMax(&r->top, max(max(red[0], red[1]), max(red[2], red[3])));
 }
 
-// The call's scales and gates from the maximum, which is cleared for the next call.
-__global__ void maps_scale(MapsRange* r) {
-  const uint32_t t = r->top;
-  int k = (int)(t >> 23) - 127 + ((t & 0x7fffffu) ? 1 : 0);  // least k with every |x| <= 2^k
-  k = max(k, 0);
-  const bool ok = k <= kMapsRangeMax;  // infinities and NaN have the largest exponent
-  r->down = ok ? ldexpf(1.0f, -k) : 1.0f;
-  r->up = ok ? ldexpf(1.0f, k) : 1.0f;
+// The call's gates from the maximum, which is cleared for the next call. Infinities
+// and NaN have the largest bits.
+__global__ void maps_gate(MapsRange* r) {
+  const bool ok = r->top <= __builtin_bit_cast(uint32_t, (float)(1 << kMapsRangeMax));
   r->ok = ok;
   r->bad = !ok;
   r->top = 0;
@@ -304,7 +299,7 @@ __global__ void maps_scale(MapsRange* r) {
 static int launch_range(Net* net, const float* maps, int64_t n, hipStream_t st) {
   const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((n / 4 + 1023) / 1024, net->num_cus * 8));
   hipLaunchKernelGGL(maps_top, dim3(grid), dim3(256), 0, st, maps, n, net->range);
-  hipLaunchKernelGGL(maps_scale, dim3(1), dim3(1), 0, st, net->range);
+  hipLaunchKernelGGL(maps_gate, dim3(1), dim3(1), 0, st, net->range);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? CNN_OK : hip_fail(e, "cnn_infer_maps: range of the maps");
 }
@@ -1090,7 +1085,7 @@ extern "C" int cnn_autotune(cnn_net* h, int64_t H, int64_t W, const char* cache_
       // only candidates with the default's accumulation order (K layout and channel block)
       if (!L.first && (conv_variant(c)->rr != conv_variant(def)->rr || conv_variant(c)->cb != conv_variant(def)->cb ||
                        conv_variant(c)->fused != conv_variant(def)->fused ||
-                       conv_variant(c)->split != conv_variant(def)->split))
+                       conv_variant(c)->parts != conv_variant(def)->parts))
         continue;
       select_variant(L, c);
       rc = run_one_layer(net, l, layer_in(l), bufs[nl + 1], d, st);  // warm-up, also the checked output
@@ -1263,7 +1258,7 @@ extern "C" int cnn_autotune_batch(cnn_net* h, const cnn_tile* tiles, int32_t n, 
         if (!L.first && (conv_variant(cand)->rr != conv_variant(defaults[l])->rr ||
                          conv_variant(cand)->cb != conv_variant(defaults[l])->cb ||
                          conv_variant(cand)->fused != conv_variant(defaults[l])->fused ||
-                         conv_variant(cand)->split != conv_variant(defaults[l])->split))
+                         conv_variant(cand)->parts != conv_variant(defaults[l])->parts))
           continue;
         std::vector<int> trial = best;
         trial[l] = cand;

@@ -146,7 +146,7 @@ static bool share_pack(ExecLayer& L, const VariantInfo* v) {
   for (size_t k = 0; k < L.wpacks.size(); ++k) {
     const VariantInfo* o = conv_variant(L.candidates[k]);
     if (o->split != v->split || o->prec != v->prec || o->cb != v->cb || o->chb != v->chb || o->u != v->u ||
-        o->ngs != v->ngs || o->rr != v->rr || o->rowq != v->rowq)
+        o->ngs != v->ngs || o->rr != v->rr || o->rowq != v->rowq || o->parts != v->parts)
       continue;
     L.wpacks.push_back(L.wpacks[k]);
     return true;
@@ -231,9 +231,11 @@ static int pack_conv(ExecLayer& L, int variant, const double* w, const double* b
 
 // ------------------------------------------------------------------ split FP32 convs
 
-// Range of every stored activation channel of a layer, over all images.
+// Range of every stored activation channel of a layer, over all images, and the
+// largest magnitude that any sum on the way there can reach.
 struct Bounds {
   std::vector<double> lo, hi;
+  double reach = 0;
 };
 
 // Bounds of a conv's stored output from its input's: interval arithmetic over
@@ -242,16 +244,22 @@ struct Bounds {
 // two covers.
 static Bounds conv_bounds(const cnn_layer& l, const double* w, const double* b, const Bounds& in) {
   Bounds o;
+  o.reach = in.reach;
   const size_t taps = (size_t)l.k * l.k;
   for (int co = 0; co < l.cout; ++co) {
-    double lo = b[co], hi = b[co];
+    double lo = b[co], hi = b[co], sum = std::fabs(b[co]);
     for (int ci = 0; ci < l.cin; ++ci) {
       const double* p = w + ((size_t)co * l.cin + ci) * taps;
       double pos = 0, neg = 0;
-      for (size_t t = 0; t < taps; ++t) (p[t] > 0 ? pos : neg) += p[t];
+      for (size_t t = 0; t < taps; ++t) {
+        pos += std::max(p[t], 0.0);
+        neg += std::min(p[t], 0.0);
+      }
       hi += pos * in.hi[ci] + neg * in.lo[ci];
       lo += pos * in.lo[ci] + neg * in.hi[ci];
+      sum += (pos - neg) * std::max(std::fabs(in.lo[ci]), std::fabs(in.hi[ci]));
     }
+    o.reach = std::max(o.reach, std::isfinite(sum) ? sum : HUGE_VAL);
     if (l.act == CNN_ACT_RELU) {
       lo = std::max(lo, 0.0);
       hi = std::max(hi, 0.0);
@@ -320,22 +328,40 @@ static uint16_t f16_code(float x, float& val) {
   return (uint16_t)(h | (sign >> 16));
 }
 
-// Scaled and split weights of one layer (split_scales' scales), for every split
-// candidate of the layer.
+// Nearest bf16 code of a finite x (ties to even) and, in val, its value.
+static uint16_t bf16_code(float x, float& val) {
+  uint32_t u;
+  std::memcpy(&u, &x, 4);
+  u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+  std::memcpy(&val, &u, 4);
+  return (uint16_t)(u >> 16);
+}
+
+// Triples (bf16, the exponents of FP32) need no scales: they hold any weight and
+// activation exactly, whatever the others are, as long as none is infinite and
+// the last part of one that matters is no subnormal. True where every sum stays
+// below 2^100 and every output channel's largest weight above 2^-100.
+static bool triples_ok(const cnn_layer& l, const double* w, const Bounds& out) {
+  if (!(out.reach <= std::ldexp(1.0, 100))) return false;
+  const size_t n = (size_t)l.cin * l.k * l.k;
+  for (int co = 0; co < l.cout; ++co) {
+    float m = 0;
+    for (size_t t = 0; t < n; ++t) m = std::max(m, std::fabs((float)w[co * n + t]));
+    if (m != 0 && m < std::ldexp(1.0f, -100)) return false;
+  }
+  return true;
+}
+
+// Split weights of one layer, for every split candidate of the layer.
 struct SplitWeights {
-  bool ok = false;
-  std::vector<uint16_t> hi, lo;       // [co][tap][ci]
-  std::vector<float> iscale, oscale;  // 2^iexp per input channel, 2^-rexp per output channel
+  std::vector<uint16_t> pair[2], triple[3];  // [co][tap][ci]; empty: no such candidate
+  std::vector<float> iscale, oscale;         // pairs: 2^iexp per input channel, 2^-rexp per output channel
 };
 
-static SplitWeights split_weights(const cnn_layer& l, const double* w, const Bounds& in) {
-  SplitWeights s;
-  std::vector<int> iexp, rexp;
-  s.ok = split_scales(l.cin, l.cout, l.k, w, in, iexp, rexp);
-  if (!s.ok) return s;
+static void split_pairs(const cnn_layer& l, const double* w, const std::vector<int>& iexp, const std::vector<int>& rexp,
+                        SplitWeights& s) {
   const int taps = l.k * l.k;
-  s.hi.resize((size_t)l.cout * taps * l.cin);
-  s.lo.resize(s.hi.size());
+  for (auto& p : s.pair) p.resize((size_t)l.cout * taps * l.cin);
   for (int ci = 0; ci < l.cin; ++ci) s.iscale.push_back(std::ldexp(1.0f, iexp[ci]));
   for (int co = 0; co < l.cout; ++co) {
     s.oscale.push_back(std::ldexp(1.0f, -rexp[co]));
@@ -346,51 +372,85 @@ static SplitWeights split_weights(const cnn_layer& l, const double* w, const Bou
         const float x = (float)((double)(float)w[((size_t)co * l.cin + ci) * taps + t] * sc);
         const size_t at = ((size_t)co * taps + t) * l.cin + ci;
         float hv, lv;
-        s.hi[at] = f16_code(x, hv);
-        s.lo[at] = f16_code(x - hv, lv);
+        s.pair[0][at] = f16_code(x, hv);
+        s.pair[1][at] = f16_code(x - hv, lv);
       }
     }
+  }
+}
+
+static void split_triples(const cnn_layer& l, const double* w, SplitWeights& s) {
+  const int taps = l.k * l.k;
+  for (auto& p : s.triple) p.resize((size_t)l.cout * taps * l.cin);
+  for (int co = 0; co < l.cout; ++co)
+    for (int ci = 0; ci < l.cin; ++ci)
+      for (int t = 0; t < taps; ++t) {
+        float x = (float)w[((size_t)co * l.cin + ci) * taps + t], v;
+        const size_t at = ((size_t)co * taps + t) * l.cin + ci;
+        for (auto& p : s.triple) {
+          p[at] = bf16_code(x, v);
+          x -= v;
+        }
+      }
+}
+
+// The split weights that the layer's candidates need; candidates whose operands
+// the layer's weights and bounds rule out are dropped. maps: the net reads
+// real-valued maps, whose range no scale of a pair can follow.
+static SplitWeights split_weights(ExecLayer& L, const cnn_layer& l, const double* w, const Bounds& in, const Bounds& out,
+                                  bool maps) {
+  SplitWeights s;
+  const auto any = [&](int parts) {
+    return std::any_of(L.candidates.begin(), L.candidates.end(), [&](int v) { return conv_variant(v)->parts == parts; });
+  };
+  const auto drop = [&](int parts) {
+    L.candidates.erase(std::remove_if(L.candidates.begin(), L.candidates.end(),
+                                      [&](int v) { return conv_variant(v)->parts == parts; }),
+                       L.candidates.end());
+  };
+  if (any(2)) {
+    std::vector<int> iexp, rexp;
+    if (!maps && split_scales(l.cin, l.cout, l.k, w, in, iexp, rexp)) split_pairs(l, w, iexp, rexp, s);
+    else drop(2);
+  }
+  if (any(3)) {
+    if (triples_ok(l, w, out)) split_triples(l, w, s);
+    else drop(3);
   }
   return s;
 }
 
-// Weights of a split conv: fragments [channel block][group-step][n-block][hi,
-// lo][lane][8 f16], lane (n16, g) holding channel split_chan of row n16 for the
-// 8 input channels of slot 4 s + g; then float iscale[cin, padded to whole blocks],
-// oscale[cout].
+// Weights of a split conv: fragments [channel block][group-step][n-block][part][lane][8
+// values], lane (n16, g) holding channel split_chan of row n16 for the 8 input channels
+// of slot 4 s + g; pairs: then float iscale[cin, padded to whole blocks], oscale[cout].
 static int pack_split(ExecLayer& L, int variant, const SplitWeights& sw, const double* b, const double* hw, double hb) {
   const VariantInfo* v = conv_variant(variant);
   const int cin = v->cin, cout = v->cout, ks = v->ks, cb = v->cb, ncb = (cin + cb - 1) / cb, nb = cout / 16;
+  const int np = v->parts;
+  const std::vector<uint16_t>* part = np == 2 ? sw.pair : sw.triple;
   if (share_pack(L, v)) return CNN_OK;
-  const size_t frags = (size_t)ncb * v->ngs * nb * 2 * 1024;
-  std::vector<uint8_t> pk(frags + (size_t)(ncb * cb + cout) * 4, 0);
+  const size_t frags = (size_t)ncb * v->ngs * nb * np * 1024;
+  std::vector<uint8_t> pk(frags + (np == 2 ? (size_t)(ncb * cb + cout) * 4 : 0), 0);
   for (int c0 = 0; c0 < ncb; ++c0)
     for (int s = 0; s < v->ngs; ++s)
       for (int g = 0; g < 4; ++g) {
         const KSlot k = k_slot(4 * s + g, ks, cb / 8, false);
         if (!k.live) continue;
+        const int ci = c0 * cb + k.cg * 8, live = std::min(8, cin - ci);  // channels past cin: zero weights
+        if (live <= 0) continue;
         for (int q = 0; q < nb; ++q)
           for (int r = 0; r < 16; ++r) {
             const int co = split_chan(q, r, nb, v->split == 2);
-            const int ci = c0 * cb + k.cg * 8, live = std::min(8, cin - ci);  // channels past cin: zero weights
-            if (live <= 0) continue;
             const size_t at = ((size_t)co * ks * ks + k.i * ks + k.j) * cin + ci;
-            uint8_t* dst = pk.data() + (((size_t)(c0 * v->ngs + s) * nb + q) * 2 * 64 + g * 16 + r) * 16;
-            std::memcpy(dst, &sw.hi[at], 2 * live);
-            std::memcpy(dst + 1024, &sw.lo[at], 2 * live);
+            uint8_t* dst = pk.data() + (((size_t)(c0 * v->ngs + s) * nb + q) * np * 64 + g * 16 + r) * 16;
+            for (int e = 0; e < np; ++e) std::memcpy(dst + e * 1024, &part[e][at], 2 * live);
           }
       }
-  std::memcpy(pk.data() + frags, sw.iscale.data(), (size_t)cin * 4);
-  std::memcpy(pk.data() + frags + (size_t)ncb * cb * 4, sw.oscale.data(), (size_t)cout * 4);
+  if (np == 2) {
+    std::memcpy(pk.data() + frags, sw.iscale.data(), (size_t)cin * 4);
+    std::memcpy(pk.data() + frags + (size_t)ncb * cb * 4, sw.oscale.data(), (size_t)cout * 4);
+  }
   return upload_conv(L, v, pk, b, {}, hw, hb, 0.0);
-}
-
-// Drop a layer's split candidates unless its scales exist (split_scales).
-static void keep_split(ExecLayer& L, bool ok) {
-  if (ok) return;
-  L.candidates.erase(std::remove_if(L.candidates.begin(), L.candidates.end(),
-                                    [](int v) { return conv_variant(v)->split != 0; }),
-                     L.candidates.end());
 }
 
 // First-layer weights as per-lane MFMA B fragments (see conv_first):
@@ -610,10 +670,13 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
   }
   const double* wp = weights;
   int sp = 1;  // spacing of the current layer's input
-  // ranges of the current layer's input channels: V / 255 lies in [0, 1]; real-valued
-  // maps are taken to lie in [-1, 1], and MapsRange covers what each call brings
+  // ranges of the current layer's input channels: V / 255 lies in [0, 1], and maps that
+  // the split kernels are given (MapsRange) in [-2^kMapsRangeMax, 2^kMapsRangeMax]
   Bounds act{{0.0}, {1.0}};
-  if (maps) act = Bounds{std::vector<double>(l0.cin, -1.0), std::vector<double>(l0.cin, 1.0)};
+  if (maps) {
+    const double top = std::ldexp(1.0, kMapsRangeMax);
+    act = Bounds{std::vector<double>(l0.cin, -top), std::vector<double>(l0.cin, top)};
+  }
   for (size_t c = 0; c < conv_at.size(); ++c) {
     const cnn_layer& l = Lr[conv_at[c]];
     const int64_t nwl = (int64_t)l.cout * l.cin * l.k * l.k;
@@ -625,9 +688,9 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
     E.cin = l.cin;
     E.spaced = 1;
     int rc = CNN_OK;
+    const Bounds in = act;
+    if (prec == CNN_PREC_FP32) act = conv_bounds(l, w, b, in);
     SplitWeights split;
-    if (prec == CNN_PREC_FP32) split = split_weights(l, w, act);
-    act = conv_bounds(l, w, b, act);
     if (c == 0 && maps) {
       // a spaced conv straight on the caller's NHWC float maps: no max filter, spacing 1
       E.cout = l.cout;
@@ -640,7 +703,7 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
       E.candidates.erase(std::remove_if(E.candidates.begin(), E.candidates.end(),
                                         [](int v) { return conv_variant(v)->groups != 0; }),
                          E.candidates.end());  // no max filter: no phase groups
-      keep_split(E, split.ok);
+      split = split_weights(E, l, w, in, act, maps);
       if (E.candidates.empty()) return unsupported("no kernel for a first conv " + std::to_string(l.cin) + " -> " +
                                                    std::to_string(l.cout));
       for (int v : E.candidates)
@@ -720,7 +783,7 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
           E.candidates.erase(std::remove_if(E.candidates.begin(), E.candidates.end(),
                                             [](int v) { return conv_variant(v)->groups != 0; }),
                              E.candidates.end());
-        keep_split(E, split.ok);
+        split = split_weights(E, l, w, in, act, maps);
         if (E.candidates.empty())
           return unsupported("no MFMA kernel for conv " + std::to_string(c) + " (" + std::to_string(l.cin) + " -> " +
                              std::to_string(l.cout) + ")");
@@ -940,9 +1003,9 @@ extern "C" int cnn_create(const double* weights, int64_t n_weights, const cnn_la
     const double* b = wp + nwl;
     wp += nwl + l.cout;
     if (i == nl - 1) break;  // head: fused into the previous conv
+    const Bounds in = act;
+    if (prec == CNN_PREC_FP32) act = conv_bounds(l, w, b, in);
     SplitWeights split;
-    if (prec == CNN_PREC_FP32) split = split_weights(l, w, act);
-    act = conv_bounds(l, w, b, act);
     ExecLayer E;
     E.cin = l.cin;
     E.cout = l.cout;
@@ -980,7 +1043,7 @@ extern "C" int cnn_create(const double* weights, int64_t n_weights, const cnn_la
         }
         E.candidates.swap(keep);
       }
-      keep_split(E, split.ok);
+      split = split_weights(E, l, w, in, act, false);
       if (E.candidates.empty()) {
         rc = fail(CNN_EUNSUPPORTED, "cnn_create: no MFMA kernel for conv " + std::to_string(i));
         break;
