@@ -238,27 +238,38 @@ struct Bounds {
   double reach = 0;
 };
 
-// Bounds of a conv's stored output from its input's: interval arithmetic over
-// the taps, then the activation (max filters and subsamples keep a channel's
-// range). Exact up to the rounding of FP32 sums, which split_scales' factor of
-// two covers.
+// Bounds of a conv's stored output from its input's: interval arithmetic over the
+// taps, then the activation (max filters and subsamples keep a channel's range).
+// They hold for the values that the kernels compute, not only for the exact ones:
+// from the FP32 weights, and widened by what a sum of n products may be rounded,
+// which is relative to the products' magnitudes. A bound that nearly cancels is
+// rounding and little else: 25 weights of 0.04 and a bias of -1 give 2e-16 exactly,
+// and 1.2e-7 in FP32 on a white image.
 static Bounds conv_bounds(const cnn_layer& l, const double* w, const double* b, const Bounds& in) {
   Bounds o;
   o.reach = in.reach;
   const size_t taps = (size_t)l.k * l.k;
+  // n roundings of a sum by at most 2^-23, a few for the operands (first-layer weights
+  // are divided by 255, pairs hold 22 bits), and as much again to spare
+  const double unit = std::ldexp((double)(taps * l.cin + 8), -22);
   for (int co = 0; co < l.cout; ++co) {
-    double lo = b[co], hi = b[co], sum = std::fabs(b[co]);
+    const double bias = (float)b[co];
+    double lo = bias, hi = bias, sum = std::fabs(bias);
     for (int ci = 0; ci < l.cin; ++ci) {
       const double* p = w + ((size_t)co * l.cin + ci) * taps;
       double pos = 0, neg = 0;
       for (size_t t = 0; t < taps; ++t) {
-        pos += std::max(p[t], 0.0);
-        neg += std::min(p[t], 0.0);
+        const double v = (float)p[t];
+        pos += std::max(v, 0.0);
+        neg += std::min(v, 0.0);
       }
       hi += pos * in.hi[ci] + neg * in.lo[ci];
       lo += pos * in.lo[ci] + neg * in.hi[ci];
       sum += (pos - neg) * std::max(std::fabs(in.lo[ci]), std::fabs(in.hi[ci]));
     }
+    hi += unit * sum;
+    lo -= unit * sum;
+    sum += unit * sum;
     o.reach = std::max(o.reach, std::isfinite(sum) ? sum : HUGE_VAL);
     if (l.act == CNN_ACT_RELU) {
       lo = std::max(lo, 0.0);
