@@ -120,12 +120,20 @@ typedef struct cnn_net cnn_net;
  * weights: host float64, for each conv in order W[cout][cin][k][k] (C order)
  *   followed by b[cout]; n_weights must equal that total. Copied, then packed
  *   and quantised once here:
- *     FP32: FP32 weights and activations, FP32 accumulation. A conv whose
- *           inputs the weights and biases of the layers before it bound (all
- *           but degenerate nets) takes each operand as a pair of f16 values,
- *           hi + lo, scaled by powers of two, and three products per pair: 22
- *           significant bits per operand, no further from the exact result
- *           than FP32 products (the first conv and the head stay in FP32);
+ *     FP32: FP32 weights and activations, FP32 accumulation. The body convs
+ *           run on 16-bit matrix units, each operand as a sum of 16-bit values:
+ *           nets on uint8 input as a pair of f16 values, scaled by powers of
+ *           two from bounds that the weights and biases of the layers before
+ *           give, and three products; a pair holds 22 bits or more, or, where
+ *           that is less, 2^-40 of the channel's bound (of the row's largest
+ *           weight). A conv whose bounds lie too far above its values (more than
+ *           2^10 times an estimate of them), whose rows hold most of their
+ *           filters too far below their largest weight, or whose bounds are not
+ *           finite takes FP32 products instead. Nets on real-valued maps hold
+ *           each operand exactly, as three bf16 values. Measured errors against
+ *           64 bits are no larger than with FP32 products; cnn_set_variant can
+ *           choose those for a layer (the first conv and the head always have
+ *           them);
  *     BF16: every conv but the 1x1 head takes bf16 weights and bf16 input
  *           activations (round to nearest even), FP32 accumulation;
  *     FP8:  the first conv as BF16; later convs except the head take e4m3fn

@@ -26,8 +26,9 @@
 // give by interval arithmetic, and each output channel's weights by their largest
 // magnitude. Values down to 2^-11 of a channel's bound keep all their bits; below,
 // the error is 2^-40 of the bound (f16 subnormals, which the MFMA does not flush).
-// Nets whose bounds or weights are not finite or leave the exponent range keep the
-// FP32 kernels, and nets on real-valued maps, which have no bound, take triples.
+// Convs whose bounds or weights leave an ordinary value fewer bits than FP32's own
+// rounding keep the FP32 kernels (split_scales), and nets on real-valued maps, which
+// have no bound, take triples.
 //
 // The kernel is warp-specialised as conv_ws: NCW consumer waves run the
 // implicit GEMM with both operands in LDS, NPW producer waves fill it. A stage

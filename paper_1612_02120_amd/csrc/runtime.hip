@@ -232,11 +232,17 @@ static int pack_conv(ExecLayer& L, int variant, const double* w, const double* b
 // ------------------------------------------------------------------ split FP32 convs
 
 // Range of every stored activation channel of a layer, over all images, and the
-// largest magnitude that any sum on the way there can reach.
+// largest magnitude that any sum on the way there can reach. usual: estimate of a
+// channel's magnitude on an ordinary image (rms of independent terms); terms: the
+// same of the sum of its products' magnitudes, which its FP32 rounding goes with.
+// Both are made from the smaller three quarters of the channels before: a few that
+// could be large may hardly ever be.
 struct Bounds {
-  std::vector<double> lo, hi;
+  std::vector<double> lo, hi, usual, terms;
   double reach = 0;
+  bool live(int c) const { return lo[c] != 0 || hi[c] != 0; }  // else always zero
 };
+constexpr double kUsualInput = 0.25;  // of V / 255: grey level 64
 
 // Bounds of a conv's stored output from its input's: interval arithmetic over the
 // taps, then the activation (max filters and subsamples keep a channel's range).
@@ -252,21 +258,35 @@ static Bounds conv_bounds(const cnn_layer& l, const double* w, const double* b, 
   // n roundings of a sum by at most 2^-23, a few for the operands (first-layer weights
   // are divided by 255, pairs hold 22 bits), and as much again to spare
   const double unit = std::ldexp((double)(taps * l.cin + 8), -22);
+  std::vector<double> sq(l.cin), mag(l.cin);  // shares of the filters in usual^2 and terms
+  const int most = l.cin - l.cin / 4;
   for (int co = 0; co < l.cout; ++co) {
     const double bias = (float)b[co];
-    double lo = bias, hi = bias, sum = std::fabs(bias);
+    double lo = bias, hi = bias, sum = std::fabs(bias), usual = bias * bias, terms = std::fabs(bias);
     for (int ci = 0; ci < l.cin; ++ci) {
       const double* p = w + ((size_t)co * l.cin + ci) * taps;
-      double pos = 0, neg = 0;
+      double pos = 0, neg = 0, s2 = 0;
       for (size_t t = 0; t < taps; ++t) {
         const double v = (float)p[t];
         pos += std::max(v, 0.0);
         neg += std::min(v, 0.0);
+        s2 += v * v;
       }
+      sq[ci] = s2 * in.usual[ci] * in.usual[ci];
+      mag[ci] = (pos - neg) * in.usual[ci];
       hi += pos * in.hi[ci] + neg * in.lo[ci];
       lo += pos * in.lo[ci] + neg * in.hi[ci];
       sum += (pos - neg) * std::max(std::fabs(in.lo[ci]), std::fabs(in.hi[ci]));
     }
+    if (most < l.cin) {
+      std::nth_element(sq.begin(), sq.begin() + most, sq.end());
+      std::nth_element(mag.begin(), mag.begin() + most, mag.end());
+    }
+    for (int k = 0; k < most; ++k) {
+      usual += sq[k];
+      terms += mag[k];
+    }
+    usual = std::sqrt(usual);
     hi += unit * sum;
     lo -= unit * sum;
     sum += unit * sum;
@@ -278,22 +298,35 @@ static Bounds conv_bounds(const cnn_layer& l, const double* w, const double* b, 
     if (l.act == CNN_ACT_MAXOUT && (co & 1)) {
       o.lo.back() = std::max(o.lo.back(), lo);
       o.hi.back() = std::max(o.hi.back(), hi);
+      o.usual.back() = std::max(o.usual.back(), usual);
+      o.terms.back() = std::max(o.terms.back(), terms);
     } else {
       o.lo.push_back(lo);
       o.hi.push_back(hi);
+      o.usual.push_back(usual);
+      o.terms.push_back(terms);
     }
   }
   return o;
 }
 
-// Power-of-two scales of a split conv (conv_split): iscale brings the bound of
-// each input channel to (2^14, 2^15], a factor of two below f16's largest
-// value, and rexp each output channel's largest weight (taken against the
-// scaled inputs) to the same range. Powers of two are exact, so the scales
-// change no product; a product's error is then relative to the largest value
-// its channel can take and its row's largest weight. False (keep the FP32
-// kernels) where a bound or weight is not finite or a scale leaves FP32's
-// normal exponents.
+// Power-of-two scales of a conv on f16 pairs (conv_split): iscale brings the bound of
+// each input channel to [2^14, 2^15), a factor of two below f16's largest value, and
+// rexp each output channel's largest weight (taken against the scaled inputs) to the
+// same range. Powers of two are exact, so the scales change no product. What a pair
+// cannot hold below its 22 to 24 bits is 2^-25 of a scaled value, 2^-40 of the bound
+// or of the row's largest weight, so the pairs are taken only where that is below
+// the rounding of FP32 itself, and the FP32 kernels elsewhere:
+// * an input channel's bound is at most 2^10 of its `terms`: 2^-40 of the bound is
+//   then 2^-6 of one FP32 rounding (2^-24 of the terms) of the sum that made the value,
+//   and no more than one on an image of grey level 1. (Bounds grow by 2^3 to 2^4 a layer
+//   over the values; with He-normal weights they are 2^2 of the terms after the first
+//   layer and 2^8 at FastMemb_ss's last such conv.)
+// * three quarters of a row's filters (those of its input channels) have a scaled tap
+//   of 2^3 or more: a pair holds them to 2^-28 of it (He-normal weights: 2^12). A
+//   channel that could reach far past the others, and scales the row by what it never
+//   shows, fails this.
+// Bounds or weights that are not finite, or scales past 2^100, fail too.
 static bool split_scales(int cin, int cout, int ks, const double* w, const Bounds& in, std::vector<int>& iexp,
                          std::vector<int>& rexp) {
   if ((int)in.lo.size() != cin) return false;
@@ -301,21 +334,30 @@ static bool split_scales(int cin, int cout, int ks, const double* w, const Bound
   iexp.assign(cin, 0);
   rexp.assign(cout, 0);
   for (int ci = 0; ci < cin; ++ci) {
-    const double m = std::max(std::fabs(in.lo[ci]), std::fabs(in.hi[ci]));
     if (!std::isfinite(in.lo[ci]) || !std::isfinite(in.hi[ci])) return false;
+    const double m = std::max(std::fabs(in.lo[ci]), std::fabs(in.hi[ci]));
+    if (!(m <= std::ldexp(in.terms[ci], 10))) return false;
     if (m > 0) iexp[ci] = 14 - std::ilogb(m);
     if (std::abs(iexp[ci]) > 100) return false;
   }
+  std::vector<double> tap;  // largest scaled tap of each filter of the row
   for (int co = 0; co < cout; ++co) {
-    double m = 0;
-    for (int ci = 0; ci < cin; ++ci)
+    tap.clear();
+    for (int ci = 0; ci < cin; ++ci) {
+      const double* p = w + ((size_t)co * cin + ci) * taps;
+      float m = 0;
       for (size_t t = 0; t < taps; ++t) {
-        const double a = std::fabs((double)(float)w[((size_t)co * cin + ci) * taps + t]);
-        if (!std::isfinite(a)) return false;
-        m = std::max(m, std::ldexp(a, -iexp[ci]));
+        const float a = std::fabs((float)p[t]);
+        m = a <= m ? m : a;  // a NaN stays until the next tap
+        if (!std::isfinite(m)) return false;
       }
-    if (m > 0) rexp[co] = 14 - std::ilogb(m);
+      if (m > 0 && in.live(ci)) tap.push_back(std::ldexp((double)m, -iexp[ci]));
+    }
+    if (tap.empty()) continue;
+    rexp[co] = 14 - std::ilogb(*std::max_element(tap.begin(), tap.end()));
     if (std::abs(rexp[co]) > 100) return false;
+    std::nth_element(tap.begin(), tap.begin() + tap.size() / 4, tap.end());
+    if (tap[tap.size() / 4] < std::ldexp(1.0, 3 - rexp[co])) return false;
   }
   return true;
 }
@@ -369,14 +411,16 @@ struct SplitWeights {
   std::vector<float> iscale, oscale;         // pairs: 2^iexp per input channel, 2^-rexp per output channel
 };
 
-static void split_pairs(const cnn_layer& l, const double* w, const std::vector<int>& iexp, const std::vector<int>& rexp,
-                        SplitWeights& s) {
+// Weights on a channel that is always zero stay out: no scale has been made for them.
+static void split_pairs(const cnn_layer& l, const double* w, const Bounds& in, const std::vector<int>& iexp,
+                        const std::vector<int>& rexp, SplitWeights& s) {
   const int taps = l.k * l.k;
   for (auto& p : s.pair) p.resize((size_t)l.cout * taps * l.cin);
   for (int ci = 0; ci < l.cin; ++ci) s.iscale.push_back(std::ldexp(1.0f, iexp[ci]));
   for (int co = 0; co < l.cout; ++co) {
     s.oscale.push_back(std::ldexp(1.0f, -rexp[co]));
     for (int ci = 0; ci < l.cin; ++ci) {
+      if (!in.live(ci)) continue;
       const double sc = std::ldexp(1.0, rexp[co] - iexp[ci]);
       for (int t = 0; t < taps; ++t) {
         // exact: a power of two times an FP32 value (what underflows FP32 here is below 2^-100 of its row)
@@ -421,7 +465,7 @@ static SplitWeights split_weights(ExecLayer& L, const cnn_layer& l, const double
   };
   if (any(2)) {
     std::vector<int> iexp, rexp;
-    if (!maps && split_scales(l.cin, l.cout, l.k, w, in, iexp, rexp)) split_pairs(l, w, iexp, rexp, s);
+    if (!maps && split_scales(l.cin, l.cout, l.k, w, in, iexp, rexp)) split_pairs(l, w, in, iexp, rexp, s);
     else drop(2);
   }
   if (any(3)) {
@@ -683,10 +727,11 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
   int sp = 1;  // spacing of the current layer's input
   // ranges of the current layer's input channels: V / 255 lies in [0, 1], and maps that
   // the split kernels are given (MapsRange) in [-2^kMapsRangeMax, 2^kMapsRangeMax]
-  Bounds act{{0.0}, {1.0}};
+  Bounds act{{0.0}, {1.0}, {kUsualInput}, {kUsualInput}};
   if (maps) {
     const double top = std::ldexp(1.0, kMapsRangeMax);
-    act = Bounds{std::vector<double>(l0.cin, -top), std::vector<double>(l0.cin, top)};
+    const std::vector<double> lo(l0.cin, -top), hi(l0.cin, top);
+    act = Bounds{lo, hi, hi, hi};
   }
   for (size_t c = 0; c < conv_at.size(); ++c) {
     const cnn_layer& l = Lr[conv_at[c]];
@@ -989,7 +1034,7 @@ extern "C" int cnn_create(const double* weights, int64_t n_weights, const cnn_la
   int pending_pool = 0;
   int conv_i = 0;
   int rc = CNN_OK;
-  Bounds act{{0.0}, {1.0}};  // ranges of the current layer's input channels (V / 255)
+  Bounds act{{0.0}, {1.0}, {kUsualInput}, {kUsualInput}};  // of the current layer's input channels (V / 255)
   // next FP8 input scale of the conv following layer i
   auto next_conv_scale = [&](int i) -> double {
     for (int k = i + 1; k < nl; ++k)

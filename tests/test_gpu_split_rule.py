@@ -1,0 +1,78 @@
+"""The rule that keeps a layer on the FP32 kernels where its weights and bounds
+leave an f16 pair too few bits for its ordinary channels (conv_split): a hidden
+channel that could reach far past the others and hardly ever does. Bar: rms error
+against 64 bits within 1.25 of the FP32 kernels', plus one output rounding (2^-24)."""
+import numpy as np
+import pytest
+
+import oracle
+from synth import em_volume
+from synth.nets import NET_B, NET_FM, NET_FMSS, calibrated_params, he_normal_params
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def emcnn():
+    import paper_1612_02120_amd as m
+    assert torch.cuda.is_available()
+    return m
+
+
+def _is_split(name):
+    return name.startswith("conv_split<") or "<F32S," in name
+
+
+def _rms(emcnn, h, vol, ref):
+    got = emcnn.cnn_infer(h, torch.from_numpy(vol).cuda()).cpu().numpy().astype(np.float64)
+    return float(np.sqrt(np.mean((got - ref) ** 2)))
+
+
+def _no_larger(emcnn, p, net, vol):
+    ref = oracle.forward(vol, net, p)
+    h = emcnn.cnn_create(p, net, "fp32")
+    got = _rms(emcnn, h, vol, ref)
+    for layer in range(1, 6):
+        fp32 = [n for n in emcnn.cnn_variant_names(h, layer) if not _is_split(n)]
+        if fp32:
+            emcnn.cnn_set_variant(h, layer, fp32[0])
+    assert got <= 1.25 * _rms(emcnn, h, vol, ref) + 2.0 ** -24
+
+
+def _rare_channel(p, reach):
+    """Channel 0 of net B's first conv: zero unless the window is a sharp checkerboard, then up to `reach`."""
+    s = np.where(np.arange(25) % 2 == 0, 1.0, -1.0)
+    a = reach / (13 * 0.01)
+    p[:25] = a * s
+    p[48 * 25] = -a * 13 * 0.99
+    return p
+
+
+@pytest.mark.parametrize("reach", [1e2, 1e4, 1e6, 1e8, 1e9, 1e12])
+def test_a_large_channel_that_never_fires(emcnn, reach):
+    _no_larger(emcnn, _rare_channel(calibrated_params("B"), reach), NET_B, em_volume(6, 1, 90, 100))
+
+
+@pytest.mark.parametrize("net", [NET_B, NET_FM], ids=["B", "FM"])
+@pytest.mark.parametrize("rows", [1, 20, 47])
+def test_filters_far_below_their_rows(emcnn, net, rows):
+    # input channels of the second conv whose filters are 2^-20 of the others' (bounds alike)
+    p = he_normal_params(net, 71)
+    first, cin = (48 * 26, 48) if net is NET_B else (64 * 17, 32)
+    k2, cout = (25, 48) if net is NET_B else (16, 64)
+    w = p[first:first + cout * cin * k2].reshape(cout, cin, k2)
+    w[:, :min(rows, cin - 1)] *= 2.0 ** -20
+    _no_larger(emcnn, p, net, em_volume(7, 1, 100, 90))
+
+
+@pytest.mark.parametrize("net", [NET_B, NET_FM, NET_FMSS], ids=["B", "FM", "FMSS"])
+def test_images_of_the_darkest_grey_levels(emcnn, net):
+    # levels 0 and 1: activations a hundredth of what their scales allow for
+    _no_larger(emcnn, he_normal_params(net, 72), net, em_volume(8, 1, 130, 140) // 150)
+
+
+def test_ordinary_nets_keep_the_split_kernels(emcnn):
+    for net, p in ((NET_B, calibrated_params("B")), (NET_FM, calibrated_params("FM"))):
+        h = emcnn.cnn_create(p, net, "fp32")
+        assert all(_is_split(emcnn.cnn_variant_names(h, layer)[0]) for layer in (1, 2))
