@@ -809,7 +809,8 @@ __global__ __launch_bounds__(512) void st_wgrad(WgradArgs a) {
     const float* px = one ? ones : o.x[xpl];
     const int n = min(WQ, w.nq - k * WQ);
     const int* od = odd[k & 1];
-    if (od[0] | od[1] | od[2] | od[3]) {
+    // (c0 and c1 are of the stage before, or of the chunk's start)
+    if (od[0] | od[1] | od[2] | od[3] || __any(!isfinite(c0) || !isfinite(c1))) {
       // an h1 of this stage is not finite (0 times it is NaN): only positions, one by one
       for (int q = 0; q < n; ++q) {
         const float x = px[q], d = pd[q];
