@@ -962,6 +962,14 @@ static int candidate_name_index(const ExecLayer& L, const std::string& name) {
   return -1;
 }
 
+// Candidates a and b contract in the same order (K layout, channel block, operand
+// parts): the autotuner changes no bit, so it takes no other, from a cache neither.
+static bool same_order(const ExecLayer& L, int a, int b) {
+  if (L.first) return true;
+  const VariantInfo *x = conv_variant(a), *y = conv_variant(b);
+  return x->rr == y->rr && x->cb == y->cb && x->fused == y->fused && x->parts == y->parts;
+}
+
 // One launch of layer l over a single H x W slice region (a fused layer 1
 // reads the uint8 input, passed as `in`, with layer 0's geometry).
 static int run_one_layer(Net* net, int l, const void* in, void* out, const Dims& d, hipStream_t st) {
@@ -1006,7 +1014,10 @@ extern "C" int cnn_autotune(cnn_net* h, int64_t H, int64_t W, const char* cache_
       lines.push_back(line);
       for (int l = 0; l < nl; ++l) {
         const std::string pre = layer_sig(net, net->layers[l]) + "|" + shape + "|";
-        if (line.rfind(pre, 0) == 0) chosen[l] = candidate_name_index(net->layers[l], line.substr(pre.size()));
+        if (line.rfind(pre, 0) != 0) continue;
+        // (the file may be older than the kernels that are now the default)
+        const int c = candidate_name_index(net->layers[l], line.substr(pre.size()));
+        chosen[l] = c >= 0 && same_order(net->layers[l], c, net->layers[l].variant) ? c : -1;
       }
     }
   }
@@ -1082,11 +1093,7 @@ extern "C" int cnn_autotune(cnn_net* h, int64_t H, int64_t W, const char* cache_
     int best = def;
     float best_ms = 1e30f;
     for (int c : L.candidates) {
-      // only candidates with the default's accumulation order (K layout and channel block)
-      if (!L.first && (conv_variant(c)->rr != conv_variant(def)->rr || conv_variant(c)->cb != conv_variant(def)->cb ||
-                       conv_variant(c)->fused != conv_variant(def)->fused ||
-                       conv_variant(c)->parts != conv_variant(def)->parts))
-        continue;
+      if (!same_order(L, c, def)) continue;
       select_variant(L, c);
       rc = run_one_layer(net, l, layer_in(l), bufs[nl + 1], d, st);  // warm-up, also the checked output
       if (rc) break;
@@ -1254,12 +1261,7 @@ extern "C" int cnn_autotune_batch(cnn_net* h, const cnn_tile* tiles, int32_t n, 
       const ExecLayer& L = net->layers[l];
       for (int cand : L.candidates) {
         if (cand == best[l]) continue;
-        // only candidates with the default's accumulation order
-        if (!L.first && (conv_variant(cand)->rr != conv_variant(defaults[l])->rr ||
-                         conv_variant(cand)->cb != conv_variant(defaults[l])->cb ||
-                         conv_variant(cand)->fused != conv_variant(defaults[l])->fused ||
-                         conv_variant(cand)->parts != conv_variant(defaults[l])->parts))
-          continue;
+        if (!same_order(L, cand, defaults[l])) continue;
         std::vector<int> trial = best;
         trial[l] = cand;
         float ms = 0.f;
