@@ -65,6 +65,7 @@ int ensure_ws(Net* net, size_t need) {
   need = (need + (1 << 20) - 1) & ~(size_t)((1 << 20) - 1);
   if ((e = hipMalloc(&net->ws, need)) != hipSuccess) {
     net->ws = nullptr;
+    (void)hipGetLastError();  // reported here, not by the caller's next use of the runtime
     return fail(CNN_ENOMEM, std::string("workspace hipMalloc(") + std::to_string(need) + "): " + hipGetErrorString(e));
   }
   net->ws_bytes = need;

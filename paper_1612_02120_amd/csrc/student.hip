@@ -1376,7 +1376,8 @@ extern "C" int student_infer_with_fallback(cnn_student* h, cnn_net* th, const ui
   const int ty = (Ho + tile - 1) / tile, tx = (Wo + tile - 1) / tile;
   const int64_t ntile = Z * ty * tx;
   if (ntile > (1 << 24)) return fail(CNN_EINVAL, "fallback: too many tiles");
-  // workspace: teacher samples, window table, flags (grown before anything is enqueued)
+  // workspace: teacher samples, window table, flags (this and the teacher's are grown
+  // before anything is enqueued, so that a call that fails for memory writes nothing)
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t nwin = (size_t)ntile * n_samples * 5;
   const size_t sz_samp = al((size_t)ntile * n_samples * 256 * 4), sz_win = al(nwin * 4), sz_flag = al((size_t)ntile * 4);
@@ -1407,10 +1408,7 @@ extern "C" int student_infer_with_fallback(cnn_student* h, cnn_net* th, const ui
   float* samples = reinterpret_cast<float*>(s->fb);
   int32_t* win_dev = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(s->fb) + sz_samp);
   int32_t* flags = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(s->fb) + sz_samp + sz_win);
-  // 1) student everywhere, in the teacher's output frame (it runs while the teacher's passes are planned)
-  rc = student_launch(s, vol, Z, H, W, prob, Wo, (int64_t)Ho * Wo, Ho, Wo, crop, st);
-  if (rc) return rc;
-  // 2) seeded sample windows per tile (positions do not depend on the data)
+  // 1) seeded sample windows per tile (positions do not depend on the data)
   std::vector<Region> sample_regs, rerun_regs;
   for (int64_t z = 0; z < Z; ++z)
     for (int a = 0; a < ty; ++a)
@@ -1468,6 +1466,9 @@ extern "C" int student_infer_with_fallback(cnn_student* h, cnn_net* th, const ui
   rc = plan_regions(net, rerun_regs, 0, l2, used2, ws2, true);
   if (rc) return rc;
   rc = ensure_ws(net, std::max(ws1, ws2));
+  if (rc) return rc;
+  // 2) student everywhere, in the teacher's output frame (it runs while the teacher's passes are planned)
+  rc = student_launch(s, vol, Z, H, W, prob, Wo, (int64_t)Ho * Wo, Ho, Wo, crop, st);
   if (rc) return rc;
   const void* ws_before = net->ws;
   rc = plan_regions(net, sample_regs, 0, l1, used1, ws1);
