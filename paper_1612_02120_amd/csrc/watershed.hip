@@ -153,7 +153,7 @@ __global__ __launch_bounds__(512) void ws_tile(const float* __restrict__ p, Vol3
   __shared__ __attribute__((aligned(16))) int par[TX * TY * TZ];  // >= 0: a voxel of the tile; else ~ one outside it
   // consecutive tiles (along z, then x, then y: the largest shared faces first) on the
   // same XCD (workgroup b on XCD b % 8), whose L2 serves the rows that neighbours share
-  const unsigned tile = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const unsigned tile = blockIdx.y * gridDim.x + (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   if (tile >= ntiles) return;
   const int z0 = (int)(tile % ntz) * TZ, x0 = (int)(tile / ntz % ntx) * TX, y0 = (int)(tile / (ntz * ntx)) * TY;
   const int HW = g.H * g.W, lane = threadIdx.x & 63, l32 = lane & 31;
@@ -444,9 +444,11 @@ template <bool VEC, int TZ, int TY>
 static hipError_t ws_run(const float* p, const Vol3& g, float t, int32_t* labels, int32_t* work, hipStream_t st) {
   const int64_t ntz = (g.Z + TZ - 1) / TZ, ntx = (g.W + TX - 1) / TX, nty = (g.H + TY - 1) / TY, nt = ntz * ntx * nty;
   const int64_t groups = ((int64_t)g.Z * g.H + 3) / 4;  // of four rows
-  // grids in multiples of 8, one share per XCD; ws_border runs persistent waves, which keep their queues filled
-  hipLaunchKernelGGL((ws_tile<VEC, TZ, TY>), dim3((unsigned)((nt + 7) / 8 * 8)), dim3(512), 0, st, p, g, t, work,
-                     (unsigned)ntz, (unsigned)ntx, (unsigned)nt);
+  // grids in multiples of 8, one share per XCD; ws_border runs persistent waves, which keep their queues filled.
+  // Thin volumes have more tiles than a row of the grid may hold threads for (2^32): then in several rows
+  const int64_t gx = std::min<int64_t>((nt + 7) / 8 * 8, 1 << 20);
+  hipLaunchKernelGGL((ws_tile<VEC, TZ, TY>), dim3((unsigned)gx, (unsigned)((nt + gx - 1) / gx)), dim3(512), 0, st, p, g, t,
+                     work, (unsigned)ntz, (unsigned)ntx, (unsigned)nt);
   hipLaunchKernelGGL((ws_border<VEC, TZ, TY>), dim3((unsigned)std::min<int64_t>((groups + 7) / 8 * 8, 2048)), dim3(256), 0,
                      st, p, g, t, work);
   hipLaunchKernelGGL(ws_label<VEC>, dim3((unsigned)((g.N + 1023) / 1024)), dim3(256), 0, st, g, work, labels);
