@@ -1,5 +1,9 @@
-"""Volumes with very many tiles: a few voxels a slice, tens of millions of slices."""
+"""Thin volumes: very many tiles, a few voxels a slice over tens of millions of slices;
+and sides of one voxel, which are laid out as if they came first."""
+import numpy as np
 import pytest
+
+import oracle
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -15,3 +19,29 @@ def test_more_tiles_than_one_row_of_a_grid(Z):
     lab = emcnn.watershed_3d(p, 0.2)
     want = ((z // 5) * 20 + 1).to(torch.int32)[:, None, None].expand(Z, 2, 2)
     assert torch.equal(lab, want)
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 7), (1, 9, 1), (11, 1, 1), (5, 1, 300), (5, 300, 1), (1, 130, 1), (300, 1, 2),
+                                   (2, 1, 1 << 20), (1 << 20, 2, 1), ((1 << 20) + 5, 1, 1)])
+def test_sides_of_one_voxel(shape):
+    import paper_1612_02120_amd as emcnn
+    rng = np.random.default_rng(shape[0] + shape[1])
+    p = (np.floor(rng.uniform(0, 1, shape) * 6) / 6 + 0.1).astype(np.float32)
+    p[rng.uniform(0, 1, shape) < 0.5] = 0.05
+    lab = emcnn.watershed_3d(torch.from_numpy(p).cuda(), 0.08)
+    assert np.array_equal(lab.cpu().numpy(), oracle.watershed(p, 0.08))
+
+
+@pytest.mark.parametrize("shape", [(4, 512, 512), (4, 512, 513), (5, 419, 503), (1, 1024, 1024), (1, 1023, 1026)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_volumes_around_the_switch_of_tiles(shape, offset):
+    # 2 x 8 rows a tile up to 2^20 voxels, 4 x 8 beyond; aligned and unaligned
+    import paper_1612_02120_amd as emcnn
+    rng = np.random.default_rng(shape[2])
+    p = np.floor(rng.uniform(0, 1, shape) * 6) / 6
+    p = np.where(rng.uniform(0, 1, shape) < 0.5, 0.05, p + 0.1).astype(np.float32)
+    flat = torch.empty(p.size + offset, dtype=torch.float32, device="cuda")
+    view = flat[offset:].view(p.shape)
+    view.copy_(torch.from_numpy(p))
+    lab = emcnn.watershed_3d(view, 0.08)
+    assert np.array_equal(lab.cpu().numpy(), oracle.watershed(p, 0.08))
