@@ -26,6 +26,14 @@
 
 namespace emcnn {
 
+// n < 2^31 workgroups as a grid: a launch holds at most 2^32 threads along x, so in
+// rows of at most 2^20, the last of which may have some to spare (grid_block() >= n).
+static dim3 grid_rows(int64_t n) {
+  const int64_t x = std::min<int64_t>(n, 1 << 20);
+  return dim3((unsigned)x, (unsigned)((n + x - 1) / x));
+}
+__device__ __forceinline__ unsigned grid_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+
 constexpr int S_C = 8;  // student channels
 constexpr int S_NP = 801;
 constexpr int OFF_W1 = 0, OFF_B1 = 200, OFF_W2 = 208, OFF_B2 = 784, OFF_WH = 792, OFF_BH = 800;
@@ -172,8 +180,9 @@ __global__ __launch_bounds__(256, 4) void student_strip(const uint8_t* in, int64
   __shared__ __attribute__((aligned(16))) unsigned char lds_all[4 * SLDS];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int strip = blockIdx.x * 4 + wave;
-  if (strip >= nstrips) return;
+  const unsigned at = grid_block() * 4 + wave;
+  if (at >= (unsigned)nstrips) return;
+  const int strip = (int)at;
   unsigned char* const xr = lds_all + wave * SLDS;
   unsigned char* const hr = xr + SX;
   const int g = lane >> 4, n16 = lane & 15;
@@ -400,7 +409,7 @@ __global__ __launch_bounds__(FT) void st_forward(const uint8_t* __restrict__ pat
                                                   float* __restrict__ h1, float* __restrict__ h2,
                                                   float* __restrict__ dz, float* __restrict__ dh2,
                                                   float* __restrict__ dh1, double* __restrict__ loss_part,
-                                                  double invN, int bf16) {
+                                                  double invN, int bf16, int nblocks) {
   constexpr int XR = FY + 8, XC = FX + 8;  // input tile, from (y0 - 2, x0 - 2)
   constexpr int HR = FY + 4, HC = FX + 4;  // h1, from (y0 - 2, x0 - 2)
   constexpr int DR = FY + 2, DC = FX + 2;  // h2 and dh2, from (y0 - 2, x0 - 2)
@@ -413,8 +422,10 @@ __global__ __launch_bounds__(FT) void st_forward(const uint8_t* __restrict__ pat
   const int tid = threadIdx.x;
   const int P1 = P - 4, P2 = P - 6;
   const int tiles = tiles_y * tiles_x;
-  const int64_t b = blockIdx.x / tiles;
-  const int rt = (int)(blockIdx.x % tiles);
+  const unsigned block = grid_block();
+  if (block >= (unsigned)nblocks) return;
+  const int64_t b = block / (unsigned)tiles;
+  const int rt = (int)(block % (unsigned)tiles);
   const int y0 = (rt / tiles_x) * FY, x0 = (rt % tiles_x) * FX;
   const uint8_t* src = patches + b * P * P;
   // every load of the block's inputs in flight before the first is used: input
@@ -601,7 +612,7 @@ __global__ __launch_bounds__(FT) void st_forward(const uint8_t* __restrict__ pat
     if (tid < s) red[tid] += red[tid + s];
     __syncthreads();
   }
-  if (tid == 0) loss_part[blockIdx.x] = red[0];
+  if (tid == 0) loss_part[block] = red[0];
 }
 
 // Partial weight gradients over a chunk of 2048 positions, in FP32: element
@@ -1133,8 +1144,8 @@ static int grad_impl(Student* s, const uint8_t* patches, const float* teacher, i
   double* lp = reinterpret_cast<double*>(w);
   const int bf = s->prec == CNN_PREC_BF16;
   const double invN = 1.0 / (double)n2;
-  hipLaunchKernelGGL(st_forward, dim3(nloss), dim3(FT), 0, st, patches, P, tiles_y, tiles_x, s->ww, teacher, h1, h2, dz,
-                     dh2, dh1, lp, invN, bf);
+  hipLaunchKernelGGL(st_forward, grid_rows(nloss), dim3(FT), 0, st, patches, P, tiles_y, tiles_x, s->ww, teacher, h1, h2,
+                     dz, dh2, dh1, lp, invN, bf, nloss);
   WgradArgs wa;
   wa.dh1 = dh1;
   wa.h1 = h1;
@@ -1321,7 +1332,7 @@ static int student_launch(Student* s, const uint8_t* vol, int64_t Z, int64_t H, 
     while (rows > 8 && Z * nsx * ((Ho + rows - 1) / rows) < 8192) rows /= 2;
     const int64_t nsy = (Ho + rows - 1) / rows, n = Z * nsx * nsy;
     if (n > 2147483647ll - 4) return fail(CNN_EUNSUPPORTED, "student: volume too large");
-    hipLaunchKernelGGL(student_strip, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, vol, W, H * W, out, out_rs, out_zs,
+    hipLaunchKernelGGL(student_strip, grid_rows((n + 3) / 4), dim3(256), 0, st, vol, W, H * W, out, out_rs, out_zs,
                        Ho, Wo, crop, s->ww, rows, (int)nsy, (int)nsx, (int)n);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "student_strip");
     return CNN_OK;
