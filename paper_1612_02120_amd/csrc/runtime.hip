@@ -167,15 +167,13 @@ static int pack_conv(ExecLayer& L, int variant, const double* w, const double* b
   const int nsteps = v->rr ? ks * ngs : ngs;
   const size_t bytes = (size_t)ncb * nsteps * nb * 64 * u * 16;
   std::vector<uint8_t> pk(bytes, 0);
-  // quantised weights, [co][ci][i][j]
-  const size_t nw = (size_t)cout * cin * ks * ks;
+  // quantised weights, [co][ci][i][j] (FP32: rounded where they are packed)
+  const size_t nw = v->prec == F32 ? 0 : (size_t)cout * cin * ks * ks;
   std::vector<double> wq(nw);
   std::vector<float> osc(cout, 1.0f);
-  if (v->prec == F32) {
-    for (size_t i = 0; i < nw; ++i) wq[i] = (float)w[i];
-  } else if (v->prec == BF16) {
+  if (v->prec == BF16) {
     for (size_t i = 0; i < nw; ++i) wq[i] = bf16_rne((float)w[i]);
-  } else {
+  } else if (v->prec == FP8) {
     const size_t per = (size_t)cin * ks * ks;
     for (int co = 0; co < cout; ++co) {
       double mx = 0.0;
@@ -185,6 +183,7 @@ static int pack_conv(ExecLayer& L, int variant, const double* w, const double* b
       osc[co] = (float)(in_scale * sw);
     }
   }
+  const double* from = v->prec == F32 ? w : wq.data();
   for (int c0 = 0; c0 < ncb; ++c0)
     for (int s = 0; s < nsteps; ++s)
       for (int n_b = 0; n_b < nb; ++n_b)
@@ -210,7 +209,7 @@ static int pack_conv(ExecLayer& L, int variant, const double* w, const double* b
             uint8_t* dst = pk.data() + ((((size_t)(c0 * nsteps + s) * nb + n_b) * u + uu) * 64 + lane) * 16;
             for (int t = 0; t < chb; ++t) {
               const int ci = c0 * cb + cg * chb + t;
-              const double val = wq[(((size_t)co * cin + ci) * ks + i) * ks + j];
+              const double val = from[(((size_t)co * cin + ci) * ks + i) * ks + j];
               if (v->prec == F32) {
                 float f = (float)val;
                 std::memcpy(dst + t * esz, &f, 4);
@@ -231,15 +230,13 @@ static int pack_conv(ExecLayer& L, int variant, const double* w, const double* b
 
 // ------------------------------------------------------------------ split FP32 convs
 
-// Range of every stored activation channel of a layer, over all images, and the
-// largest magnitude that any sum on the way there can reach. usual: estimate of a
-// channel's magnitude on an ordinary image (rms of independent terms); terms: the
-// same of the sum of its products' magnitudes, which its FP32 rounding goes with.
+// Range of every stored activation channel of a layer, over all images. usual:
+// estimate of a channel's magnitude on an ordinary image (rms of independent terms);
+// terms: the same of the sum of its products' magnitudes, which its FP32 rounding goes with.
 // Both are made from the smaller three quarters of the channels before: a few that
 // could be large may hardly ever be.
 struct Bounds {
   std::vector<double> lo, hi, usual, terms;
-  double reach = 0;
   bool live(int c) const { return lo[c] != 0 || hi[c] != 0; }  // else always zero
 };
 constexpr double kUsualInput = 0.25;  // of V / 255: grey level 64
@@ -253,7 +250,6 @@ constexpr double kUsualInput = 0.25;  // of V / 255: grey level 64
 // and 1.2e-7 in FP32 on a white image.
 static Bounds conv_bounds(const cnn_layer& l, const double* w, const double* b, const Bounds& in) {
   Bounds o;
-  o.reach = in.reach;
   const size_t taps = (size_t)l.k * l.k;
   // n roundings of a sum by at most 2^-23, a few for the operands (first-layer weights
   // are divided by 255, pairs hold 22 bits), and as much again to spare
@@ -289,8 +285,6 @@ static Bounds conv_bounds(const cnn_layer& l, const double* w, const double* b, 
     usual = std::sqrt(usual);
     hi += unit * sum;
     lo -= unit * sum;
-    sum += unit * sum;
-    o.reach = std::max(o.reach, std::isfinite(sum) ? sum : HUGE_VAL);
     if (l.act == CNN_ACT_RELU) {
       lo = std::max(lo, 0.0);
       hi = std::max(hi, 0.0);
@@ -362,99 +356,79 @@ static bool split_scales(int cin, int cout, int ks, const double* w, const Bound
   return true;
 }
 
-// Nearest f16 code of x (ties to even, |x| below 2^16) and, in val, its value.
-static uint16_t f16_code(float x, float& val) {
+static uint32_t bits_of(float x) {
   uint32_t u;
   std::memcpy(&u, &x, 4);
-  const uint32_t sign = u & 0x80000000u, m = u & 0x7fffffffu;
-  uint32_t h;
-  if (m >= 0x38800000u) {  // 2^-14 and above: drop 13 mantissa bits, rounding
-    h = (m + 0xfffu + ((m >> 13) & 1u)) >> 13;
-    const uint32_t back = (h << 13) | sign;
-    std::memcpy(&val, &back, 4);
-    h -= 112u << 10;
-  } else {  // subnormal: a multiple of 2^-24
-    const float a = std::fabs(x);
-    h = (uint32_t)std::nearbyint(a * 16777216.0f);
-    val = std::copysign((float)h * (1.0f / 16777216.0f), x);
-  }
-  return (uint16_t)(h | (sign >> 16));
+  return u;
+}
+static float float_of(uint32_t u) {
+  float x;
+  std::memcpy(&x, &u, 4);
+  return x;
 }
 
-// Nearest bf16 code of a finite x (ties to even) and, in val, its value.
-static uint16_t bf16_code(float x, float& val) {
-  uint32_t u;
-  std::memcpy(&u, &x, 4);
+// Nearest f16 code of x (ties to even, |x| below 2^16); x becomes what it leaves.
+static uint16_t f16_part(float& x) {
+  const uint32_t u = bits_of(x), sign = u & 0x80000000u, m = u & 0x7fffffffu;
+  // 2^-14 and above: 13 mantissa bits dropped, rounding; below, multiples of 2^-24, the
+  // unit of 0.5
+  const uint32_t normal = (m + 0xfffu + ((m >> 13) & 1u)) >> 13;
+  const float sub = float_of(m) + 0.5f;
+  const bool big = m >= 0x38800000u;
+  x -= float_of((big ? normal << 13 : bits_of(sub - 0.5f)) | sign);
+  return (uint16_t)((big ? normal - (112u << 10) : bits_of(sub) - bits_of(0.5f)) | (sign >> 16));
+}
+
+// Nearest bf16 code of a finite x (ties to even); x becomes what it leaves.
+static uint16_t bf16_part(float& x) {
+  uint32_t u = bits_of(x);
   u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
-  std::memcpy(&val, &u, 4);
+  x -= float_of(u);
   return (uint16_t)(u >> 16);
 }
 
 // Triples (bf16, the exponents of FP32) need no scales: they hold any weight and
 // activation exactly, whatever the others are, as long as none is infinite and
 // the last part of one that matters is no subnormal. True where every sum stays
-// below 2^100 and every output channel's largest weight above 2^-100.
-static bool triples_ok(const cnn_layer& l, const double* w, const Bounds& out) {
-  if (!(out.reach <= std::ldexp(1.0, 100))) return false;
+// below 2^100 and every output channel's largest weight above 2^-100. reach: bound of
+// every magnitude in the layer's input, then of those in its sums and output (from the
+// largest weight alone: conv_bounds costs three times as long).
+static bool triples_ok(const cnn_layer& l, const double* w, const double* b, double& reach) {
   const size_t n = (size_t)l.cin * l.k * l.k;
+  double top = 0, least = HUGE_VAL, bias = 0;
+  bool finite = true;
   for (int co = 0; co < l.cout; ++co) {
-    float m = 0;
-    for (size_t t = 0; t < n; ++t) m = std::max(m, std::fabs((float)w[co * n + t]));
-    if (m != 0 && m < std::ldexp(1.0f, -100)) return false;
+    double m[4] = {0, 0, 0, 0};  // four maxima at once
+    for (size_t t = 0; t < n; ++t) {
+      const double a = std::fabs(w[co * n + t]);
+      m[t & 3] = std::max(m[t & 3], a);
+      finite &= a < HUGE_VAL;
+    }
+    const double row = std::max(std::max(m[0], m[1]), std::max(m[2], m[3]));
+    top = std::max(top, row);
+    if (row != 0) least = std::min(least, row);
+    bias = std::max(bias, std::fabs(b[co]));
+    finite &= std::isfinite(b[co]);
   }
-  return true;
+  reach = finite ? 1.01 * (bias + (double)n * top * reach) : HUGE_VAL;
+  return reach <= std::ldexp(1.0, 100) && least >= std::ldexp(1.0, -100);
 }
 
-// Split weights of one layer, for every split candidate of the layer.
-struct SplitWeights {
-  std::vector<uint16_t> pair[2], triple[3];  // [co][tap][ci]; empty: no such candidate
-  std::vector<float> iscale, oscale;         // pairs: 2^iexp per input channel, 2^-rexp per output channel
+// Scales of a layer's pairs: 2^iexp per input channel (in_scale its inverse for the
+// weights, 0 for a channel that is always zero: no scale has been made for its weights),
+// 2^rexp per output channel and its inverse.
+struct SplitScales {
+  std::vector<float> iscale, oscale;
+  std::vector<double> in_scale, out_scale;
 };
 
-// Weights on a channel that is always zero stay out: no scale has been made for them.
-static void split_pairs(const cnn_layer& l, const double* w, const Bounds& in, const std::vector<int>& iexp,
-                        const std::vector<int>& rexp, SplitWeights& s) {
-  const int taps = l.k * l.k;
-  for (auto& p : s.pair) p.resize((size_t)l.cout * taps * l.cin);
-  for (int ci = 0; ci < l.cin; ++ci) s.iscale.push_back(std::ldexp(1.0f, iexp[ci]));
-  for (int co = 0; co < l.cout; ++co) {
-    s.oscale.push_back(std::ldexp(1.0f, -rexp[co]));
-    for (int ci = 0; ci < l.cin; ++ci) {
-      if (!in.live(ci)) continue;
-      const double sc = std::ldexp(1.0, rexp[co] - iexp[ci]);
-      for (int t = 0; t < taps; ++t) {
-        // exact: a power of two times an FP32 value (what underflows FP32 here is below 2^-100 of its row)
-        const float x = (float)((double)(float)w[((size_t)co * l.cin + ci) * taps + t] * sc);
-        const size_t at = ((size_t)co * taps + t) * l.cin + ci;
-        float hv, lv;
-        s.pair[0][at] = f16_code(x, hv);
-        s.pair[1][at] = f16_code(x - hv, lv);
-      }
-    }
-  }
-}
-
-static void split_triples(const cnn_layer& l, const double* w, SplitWeights& s) {
-  const int taps = l.k * l.k;
-  for (auto& p : s.triple) p.resize((size_t)l.cout * taps * l.cin);
-  for (int co = 0; co < l.cout; ++co)
-    for (int ci = 0; ci < l.cin; ++ci)
-      for (int t = 0; t < taps; ++t) {
-        float x = (float)w[((size_t)co * l.cin + ci) * taps + t], v;
-        const size_t at = ((size_t)co * taps + t) * l.cin + ci;
-        for (auto& p : s.triple) {
-          p[at] = bf16_code(x, v);
-          x -= v;
-        }
-      }
-}
-
-// The split weights that the layer's candidates need; candidates whose operands
-// the layer's weights and bounds rule out are dropped. maps: the net reads
-// real-valued maps, whose range no scale of a pair can follow.
-static SplitWeights split_weights(ExecLayer& L, const cnn_layer& l, const double* w, const Bounds& in, const Bounds& out,
-                                  bool maps) {
-  SplitWeights s;
+// Drops the layer's candidates whose operands its weights and bounds rule out, and
+// makes the scales of those that need some. in: bounds of a net on uint8 input; nullptr:
+// the net reads real-valued maps, whose range no scale of a pair can follow. reach: see
+// triples_ok.
+static SplitScales split_candidates(ExecLayer& L, const cnn_layer& l, const double* w, const double* b, const Bounds* in,
+                                    double& reach) {
+  SplitScales s;
   const auto any = [&](int parts) {
     return std::any_of(L.candidates.begin(), L.candidates.end(), [&](int v) { return conv_variant(v)->parts == parts; });
   };
@@ -465,47 +439,80 @@ static SplitWeights split_weights(ExecLayer& L, const cnn_layer& l, const double
   };
   if (any(2)) {
     std::vector<int> iexp, rexp;
-    if (!maps && split_scales(l.cin, l.cout, l.k, w, in, iexp, rexp)) split_pairs(l, w, in, iexp, rexp, s);
-    else drop(2);
+    if (in && split_scales(l.cin, l.cout, l.k, w, *in, iexp, rexp)) {
+      for (int ci = 0; ci < l.cin; ++ci) {
+        s.iscale.push_back(std::ldexp(1.0f, iexp[ci]));
+        s.in_scale.push_back(in->live(ci) ? std::ldexp(1.0, -iexp[ci]) : 0.0);
+      }
+      for (int co = 0; co < l.cout; ++co) {
+        s.oscale.push_back(std::ldexp(1.0f, -rexp[co]));
+        s.out_scale.push_back(std::ldexp(1.0, rexp[co]));
+      }
+    } else {
+      drop(2);
+    }
   }
-  if (any(3)) {
-    if (triples_ok(l, w, out)) split_triples(l, w, s);
-    else drop(3);
+  if (in && any(3)) {
+    reach = 0;
+    for (int ci = 0; ci < l.cin; ++ci)
+      reach = in->lo[ci] <= in->hi[ci] ? std::max(reach, std::max(-in->lo[ci], in->hi[ci])) : HUGE_VAL;
   }
+  if ((!in || any(3)) && !triples_ok(l, w, b, reach)) drop(3);
   return s;
 }
 
 // Weights of a split conv: fragments [channel block][group-step][n-block][part][lane][8
 // values], lane (n16, g) holding channel split_chan of row n16 for the 8 input channels
 // of slot 4 s + g; pairs: then float iscale[cin, padded to whole blocks], oscale[cout].
-static int pack_split(ExecLayer& L, int variant, const SplitWeights& sw, const double* b, const double* hw, double hb) {
-  const VariantInfo* v = conv_variant(variant);
-  const int cin = v->cin, cout = v->cout, ks = v->ks, cb = v->cb, ncb = (cin + cb - 1) / cb, nb = cout / 16;
-  const int np = v->parts;
-  const std::vector<uint16_t>* part = np == 2 ? sw.pair : sw.triple;
-  if (share_pack(L, v)) return CNN_OK;
-  const size_t frags = (size_t)ncb * v->ngs * nb * np * 1024;
-  std::vector<uint8_t> pk(frags + (np == 2 ? (size_t)(ncb * cb + cout) * 4 : 0), 0);
-  for (int c0 = 0; c0 < ncb; ++c0)
-    for (int s = 0; s < v->ngs; ++s)
-      for (int g = 0; g < 4; ++g) {
-        const KSlot k = k_slot(4 * s + g, ks, cb / 8, false);
-        if (!k.live) continue;
-        const int ci = c0 * cb + k.cg * 8, live = std::min(8, cin - ci);  // channels past cin: zero weights
-        if (live <= 0) continue;
-        for (int q = 0; q < nb; ++q)
-          for (int r = 0; r < 16; ++r) {
-            const int co = split_chan(q, r, nb, v->split == 2);
-            const size_t at = ((size_t)co * ks * ks + k.i * ks + k.j) * cin + ci;
-            uint8_t* dst = pk.data() + (((size_t)(c0 * v->ngs + s) * nb + q) * np * 64 + g * 16 + r) * 16;
-            for (int e = 0; e < np; ++e) std::memcpy(dst + e * 1024, &part[e][at], 2 * live);
-          }
-      }
-  if (np == 2) {
-    std::memcpy(pk.data() + frags, sw.iscale.data(), (size_t)cin * 4);
-    std::memcpy(pk.data() + frags + (size_t)ncb * cb * 4, sw.oscale.data(), (size_t)cout * 4);
+// NP parts. Weights are read once and in order, eight filters at a time (with arrays of
+// all parts between, and bounds taken in a pass of their own for triples, creating
+// MaskExtend's net took 3.9 ms; 1.05 this way).
+template <int NP>
+static std::vector<uint8_t> split_fragments(const VariantInfo* v, const double* w, const SplitScales& sc) {
+  const int cin = v->cin, cout = v->cout, taps = v->ks * v->ks, cb = v->cb, ncb = (cin + cb - 1) / cb, nb = cout / 16;
+  const int nchb = cb / 8;
+  const size_t frags = (size_t)ncb * v->ngs * nb * NP * 1024;
+  std::vector<uint8_t> pk(frags + (NP == 2 ? (size_t)(ncb * cb + cout) * 4 : 0), 0);
+  std::vector<int> slot(taps * nchb, -1);  // of each tap and chunk
+  for (int c = 0; c < 4 * v->ngs; ++c) {
+    const KSlot k = k_slot(c, v->ks, nchb, false);
+    if (k.live) slot[(k.i * v->ks + k.j) * nchb + k.cg] = c;
   }
-  return upload_conv(L, v, pk, b, {}, hw, hb, 0.0);
+  for (int q = 0; q < nb; ++q)
+    for (int r = 0; r < 16; ++r) {
+      const int co = split_chan(q, r, nb, v->split == 2);
+      for (int c0 = 0; c0 < cin; c0 += 8) {
+        const int live = std::min(8, cin - c0);  // channels past cin: zero weights
+        const double* p = w + ((size_t)co * cin + c0) * taps;
+        uint8_t* block = pk.data() + ((size_t)(c0 / cb) * v->ngs * nb + q) * NP * 1024 + r * 16;
+        for (int t = 0; t < taps; ++t) {
+          float x[8];
+          uint16_t part[NP][8];
+          for (int e = 0; e < 8; ++e) {
+            const double a = e < live ? (double)(float)p[e * taps + t] : 0.0;
+            // exact: a power of two times an FP32 value (what underflows FP32 here is below 2^-100 of its row)
+            x[e] = NP == 2 && e < live ? (float)(a * sc.in_scale[c0 + e] * sc.out_scale[co]) : (float)a;
+          }
+          for (int k = 0; k < NP; ++k)
+            for (int e = 0; e < 8; ++e) part[k][e] = NP == 2 ? f16_part(x[e]) : bf16_part(x[e]);
+          const int c = slot[t * nchb + c0 % cb / 8];
+          uint8_t* dst = block + (size_t)(c / 4) * nb * NP * 1024 + (c % 4) * 256;
+          for (int k = 0; k < NP; ++k) std::memcpy(dst + k * 1024, part[k], 16);
+        }
+      }
+    }
+  if (NP == 2) {
+    std::memcpy(pk.data() + frags, sc.iscale.data(), (size_t)cin * 4);
+    std::memcpy(pk.data() + frags + (size_t)ncb * cb * 4, sc.oscale.data(), (size_t)cout * 4);
+  }
+  return pk;
+}
+
+static int pack_split(ExecLayer& L, int variant, const double* w, const SplitScales& sc, const double* b, const double* hw,
+                      double hb) {
+  const VariantInfo* v = conv_variant(variant);
+  if (share_pack(L, v)) return CNN_OK;
+  return upload_conv(L, v, v->parts == 2 ? split_fragments<2>(v, w, sc) : split_fragments<3>(v, w, sc), b, {}, hw, hb, 0.0);
 }
 
 // First-layer weights as per-lane MFMA B fragments (see conv_first):
@@ -725,14 +732,10 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
   }
   const double* wp = weights;
   int sp = 1;  // spacing of the current layer's input
-  // ranges of the current layer's input channels: V / 255 lies in [0, 1], and maps that
-  // the split kernels are given (MapsRange) in [-2^kMapsRangeMax, 2^kMapsRangeMax]
+  // of the current layer's input: V / 255 lies in [0, 1], and maps that the split kernels
+  // are given (MapsRange) in [-2^kMapsRangeMax, 2^kMapsRangeMax]
   Bounds act{{0.0}, {1.0}, {kUsualInput}, {kUsualInput}};
-  if (maps) {
-    const double top = std::ldexp(1.0, kMapsRangeMax);
-    const std::vector<double> lo(l0.cin, -top), hi(l0.cin, top);
-    act = Bounds{lo, hi, hi, hi};
-  }
+  double reach = std::ldexp(1.0, kMapsRangeMax);
   for (size_t c = 0; c < conv_at.size(); ++c) {
     const cnn_layer& l = Lr[conv_at[c]];
     const int64_t nwl = (int64_t)l.cout * l.cin * l.k * l.k;
@@ -745,8 +748,8 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
     E.spaced = 1;
     int rc = CNN_OK;
     const Bounds in = act;
-    if (prec == CNN_PREC_FP32) act = conv_bounds(l, w, b, in);
-    SplitWeights split;
+    if (prec == CNN_PREC_FP32 && !maps) act = conv_bounds(l, w, b, in);
+    SplitScales split;
     if (c == 0 && maps) {
       // a spaced conv straight on the caller's NHWC float maps: no max filter, spacing 1
       E.cout = l.cout;
@@ -759,12 +762,12 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
       E.candidates.erase(std::remove_if(E.candidates.begin(), E.candidates.end(),
                                         [](int v) { return conv_variant(v)->groups != 0; }),
                          E.candidates.end());  // no max filter: no phase groups
-      split = split_weights(E, l, w, in, act, maps);
+      split = split_candidates(E, l, w, b, maps ? nullptr : &in, reach);
       if (E.candidates.empty()) return unsupported("no kernel for a first conv " + std::to_string(l.cin) + " -> " +
                                                    std::to_string(l.cout));
       for (int v : E.candidates)
         if (rc == CNN_OK)
-          rc = conv_variant(v)->split ? pack_split(E, v, split, b, nullptr, 0.0)
+          rc = conv_variant(v)->split ? pack_split(E, v, w, split, b, nullptr, 0.0)
                                       : pack_conv(E, v, w, b, nullptr, 0.0, 1.0, 0.0);
     } else if (c == 0) {
       E.first = 1;
@@ -839,13 +842,13 @@ static int build_strided(Net* net, const double* weights, const cnn_layer* Lr, i
           E.candidates.erase(std::remove_if(E.candidates.begin(), E.candidates.end(),
                                             [](int v) { return conv_variant(v)->groups != 0; }),
                              E.candidates.end());
-        split = split_weights(E, l, w, in, act, maps);
+        split = split_candidates(E, l, w, b, maps ? nullptr : &in, reach);
         if (E.candidates.empty())
           return unsupported("no MFMA kernel for conv " + std::to_string(c) + " (" + std::to_string(l.cin) + " -> " +
                              std::to_string(l.cout) + ")");
         for (int v : E.candidates)
           if (rc == CNN_OK)
-            rc = conv_variant(v)->split ? pack_split(E, v, split, b, nullptr, 0.0)
+            rc = conv_variant(v)->split ? pack_split(E, v, w, split, b, nullptr, 0.0)
                                         : pack_conv(E, v, w, b, nullptr, 0.0, 1.0, 0.0);
       }
     }
@@ -1061,7 +1064,7 @@ extern "C" int cnn_create(const double* weights, int64_t n_weights, const cnn_la
     if (i == nl - 1) break;  // head: fused into the previous conv
     const Bounds in = act;
     if (prec == CNN_PREC_FP32) act = conv_bounds(l, w, b, in);
-    SplitWeights split;
+    SplitScales split;
     ExecLayer E;
     E.cin = l.cin;
     E.cout = l.cout;
@@ -1099,7 +1102,8 @@ extern "C" int cnn_create(const double* weights, int64_t n_weights, const cnn_la
         }
         E.candidates.swap(keep);
       }
-      split = split_weights(E, l, w, in, act, false);
+      double reach = 0;
+      split = split_candidates(E, l, w, b, &in, reach);
       if (E.candidates.empty()) {
         rc = fail(CNN_EUNSUPPORTED, "cnn_create: no MFMA kernel for conv " + std::to_string(i));
         break;
@@ -1118,7 +1122,7 @@ extern "C" int cnn_create(const double* weights, int64_t n_weights, const cnn_la
       }
       for (int c : E.candidates) {
         if (rc == CNN_OK)
-          rc = conv_variant(c)->split ? pack_split(E, c, split, b, hw, hb)
+          rc = conv_variant(c)->split ? pack_split(E, c, w, split, b, hw, hb)
                                       : pack_conv(E, c, w, b, hw, hb, in_scale, fuse_head ? 0.0 : nxt);
       }
       if (rc == CNN_OK) select_variant(E, E.variant);
