@@ -32,8 +32,10 @@ sys.path.insert(0, ROOT)
 METRIC = "membrane-prob voxels/sec at 1 MI355X and % MFMA peak, plain FP32 vs BF16/FP8/student"
 PEAK_TFLOPS = {"fp32": 157.3, "bf16": 2500.0, "fp8": 5000.0}
 # What the convs of each form can reach: the FP32 ones take three f16 products per
-# FP32 product (operands as f16 hi + lo pairs), so a third of the dense f16 rate
+# FP32 product (operands as f16 hi + lo pairs), so a third of the dense 16-bit rate,
+# and those on real-valued maps six bf16 ones (operands as bf16 triples)
 CONV_TFLOPS = dict(PEAK_TFLOPS, fp32=PEAK_TFLOPS["bf16"] / 3)
+MAPS_TFLOPS = PEAK_TFLOPS["bf16"] / 6
 HBM_GBS = 8000.0
 # algorithmic work of net B per output voxel: 2 x (1200 + 57600 + 20736 + 48) MAC
 NET_B_FLOP_PER_VOXEL = 159168
@@ -285,7 +287,7 @@ def maskextend_form(emcnn, torch, dev, stream, args):
                        % (Z, Z),
            "voxels_per_s": nv / dt, "ms_per_pass": dt * 1e3,
            "path_tflops": nv * MASKEXTEND_FLOP_PER_VOXEL / dt / 1e12,
-           "path_mfma_frac": nv * MASKEXTEND_FLOP_PER_VOXEL / dt / 1e12 / CONV_TFLOPS["fp32"],
+           "path_mfma_frac": nv * MASKEXTEND_FLOP_PER_VOXEL / dt / 1e12 / MAPS_TFLOPS,
            "layer_ms": [m / reps for m in ms[:6]], "tiles": emcnn.cnn_describe(h)}
     log("maskextend", json.dumps(res))
     del maps, out, h

@@ -130,10 +130,10 @@ typedef struct cnn_net cnn_net;
  *           2^10 times an estimate of them), whose rows hold most of their
  *           filters too far below their largest weight, or whose bounds are not
  *           finite takes FP32 products instead. Nets on real-valued maps hold
- *           each operand exactly, as three bf16 values. Measured errors against
- *           64 bits are no larger than with FP32 products; cnn_set_variant can
- *           choose those for a layer (the first conv and the head always have
- *           them);
+ *           each operand exactly, as three bf16 values, and take six products.
+ *           Measured errors against 64 bits are level with those of FP32
+ *           products or below; cnn_set_variant can choose FP32 products for a
+ *           layer (the first conv on uint8 and the head always have them);
  *     BF16: every conv but the 1x1 head takes bf16 weights and bf16 input
  *           activations (round to nearest even), FP32 accumulation;
  *     FP8:  the first conv as BF16; later convs except the head take e4m3fn
@@ -262,7 +262,8 @@ int cnn_set_workspace_limit(cnn_net* net, int64_t bytes);
  * only; graph replays are not timed). cnn_profile_read waits for the events,
  * writes the summed milliseconds and launch count per executed layer (first
  * layer, body convs; the head is fused into the last body conv) and clears
- * the record. */
+ * the record. A body conv on real-valued maps counts both forms that
+ * cnn_infer_maps enqueues. */
 int cnn_profile(cnn_net* net, int32_t enable);
 int cnn_profile_read(cnn_net* net, double* ms_per_layer, int32_t* launches_per_layer,
                      int32_t max_layers);
