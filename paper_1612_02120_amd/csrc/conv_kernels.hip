@@ -10,7 +10,7 @@
 //                 uint8 volume (1/255 is folded into its weights on the host).
 //   conv_mfma   - every later FP32 conv as an implicit GEMM on FP32 MFMA (the
 //                 default where conv_split.hip has no kernel for the layer, or
-//                 its activations have no usable bound): M = output
+//                 its bounds and weights allow none): M = output
 //                 pixels (16 consecutive pixels of a row per m-block), N = output
 //                 channels (16 per n-block), K = (tap, input channel).
 //                 The input tile plus halo is staged in LDS, the preceding 2x2

@@ -437,7 +437,9 @@ __global__ __launch_bounds__(256) void ws_label(Vol3 g, int32_t* a, int32_t* out
 
 // Voxels up to which tiles of 2 x 8 rows are taken: a step of a wave less, twice the
 // workgroups (us with 2 x 8 against 4 x 8 rows: 25.6 against 30.7 on 2^19 voxels, 32 against
-// 35 on 2^20, 48-50 against 46 on 1.2 M, 62 against 60 on 2^22).
+// 35 on 2^20, 48-50 against 46 on 1.2 M, 62 against 60 on 2^22). Single slices take them
+// too, though they leave three quarters of a tile empty: 100 us on 1100^2, 342 on 4096^2
+// (134 and 860 with rows as waves and all links in memory).
 constexpr int64_t kSmall = 1 << 20;
 
 template <bool VEC, int TZ, int TY>
