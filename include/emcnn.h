@@ -127,8 +127,9 @@ typedef struct cnn_net cnn_net;
  *           give, and three products; a pair holds 22 bits or more, or, where
  *           that is less, 2^-40 of the channel's bound (of the row's largest
  *           weight). A conv whose bounds lie too far above its values (more than
- *           2^10 times an estimate of them), whose rows hold most of their
- *           filters too far below their largest weight, or whose bounds are not
+ *           2^11 times an estimate of them), whose rows hold more than half of
+ *           their filters (the taps on one input channel, scaled by its bound)
+ *           below about 2^-11 of their largest weight, or whose bounds are not
  *           finite takes FP32 products instead. Nets on real-valued maps hold
  *           each operand exactly, as three bf16 values, and take six products.
  *           Measured errors against 64 bits are level with those of FP32

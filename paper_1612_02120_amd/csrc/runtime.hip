@@ -232,12 +232,15 @@ static int pack_conv(ExecLayer& L, int variant, const double* w, const double* b
 
 // Range of every stored activation channel of a layer, over all images. usual:
 // estimate of a channel's magnitude on an ordinary image (rms of independent terms);
-// terms: the same of the sum of its products' magnitudes, which its FP32 rounding goes with.
-// Both are made from the smaller three quarters of the channels before: a few that
-// could be large may hardly ever be.
+// terms: the same of the sum of its products' magnitudes, which its FP32 rounding goes
+// with. Both are kept low, as channels that could be large may hardly ever be: they take
+// the median of the channels before for all of them; a ReLU channel whose bias lies
+// more than that sum's size below zero is not counted on (usual 0); and a max-out pair
+// whose biases lie further apart has the smaller member's.
 struct Bounds {
   std::vector<double> lo, hi, usual, terms;
   bool live(int c) const { return lo[c] != 0 || hi[c] != 0; }  // else always zero
+  bool counts(int c) const { return usual[c] > 0; }
 };
 constexpr double kUsualInput = 0.25;  // of V / 255: grey level 64
 
@@ -254,13 +257,16 @@ static Bounds conv_bounds(const cnn_layer& l, const double* w, const double* b, 
   // n roundings of a sum by at most 2^-23, a few for the operands (first-layer weights
   // are divided by 255, pairs hold 22 bits), and as much again to spare
   const double unit = std::ldexp((double)(taps * l.cin + 8), -22);
-  std::vector<double> sq(l.cin), mag(l.cin);  // shares of the filters in usual^2 and terms
-  const int most = l.cin - l.cin / 4;
+  std::vector<double> sq, mag;  // shares of the filters in usual^2 and terms, on channels counted on
+  double bias0 = 0, size0 = 0;  // of a max-out pair's first member
   for (int co = 0; co < l.cout; ++co) {
     const double bias = (float)b[co];
-    double lo = bias, hi = bias, sum = std::fabs(bias), usual = bias * bias, terms = std::fabs(bias);
+    double lo = bias, hi = bias, sum = std::fabs(bias), size = 0, terms = std::fabs(bias);
+    sq.clear();
+    mag.clear();
     for (int ci = 0; ci < l.cin; ++ci) {
       const double* p = w + ((size_t)co * l.cin + ci) * taps;
+      const double u = in.usual[ci];
       double pos = 0, neg = 0, s2 = 0;
       for (size_t t = 0; t < taps; ++t) {
         const double v = (float)p[t];
@@ -268,33 +274,38 @@ static Bounds conv_bounds(const cnn_layer& l, const double* w, const double* b, 
         neg += std::min(v, 0.0);
         s2 += v * v;
       }
-      sq[ci] = s2 * in.usual[ci] * in.usual[ci];
-      mag[ci] = (pos - neg) * in.usual[ci];
+      if (in.counts(ci) && s2 > 0) {
+        sq.push_back(s2 * u * u);
+        mag.push_back((pos - neg) * u);
+      }
       hi += pos * in.hi[ci] + neg * in.lo[ci];
       lo += pos * in.lo[ci] + neg * in.hi[ci];
       sum += (pos - neg) * std::max(std::fabs(in.lo[ci]), std::fabs(in.hi[ci]));
     }
-    if (most < l.cin) {
-      std::nth_element(sq.begin(), sq.begin() + most, sq.end());
-      std::nth_element(mag.begin(), mag.begin() + most, mag.end());
+    if (!sq.empty()) {
+      const size_t n = sq.size(), m = (n - 1) / 2;
+      std::nth_element(sq.begin(), sq.begin() + m, sq.end());
+      std::nth_element(mag.begin(), mag.begin() + m, mag.end());
+      size = std::sqrt(n * sq[m]);
+      terms += n * mag[m];
     }
-    for (int k = 0; k < most; ++k) {
-      usual += sq[k];
-      terms += mag[k];
-    }
-    usual = std::sqrt(usual);
+    double usual = std::hypot(bias, size);
     hi += unit * sum;
     lo -= unit * sum;
     if (l.act == CNN_ACT_RELU) {
       lo = std::max(lo, 0.0);
       hi = std::max(hi, 0.0);
+      if (-bias > size) usual = 0;
     }
     if (l.act == CNN_ACT_MAXOUT && (co & 1)) {
       o.lo.back() = std::max(o.lo.back(), lo);
       o.hi.back() = std::max(o.hi.back(), hi);
-      o.usual.back() = std::max(o.usual.back(), usual);
-      o.terms.back() = std::max(o.terms.back(), terms);
+      const bool both = std::fabs(bias - bias0) <= std::max(size, size0);
+      o.usual.back() = both ? std::max(o.usual.back(), usual) : std::min(o.usual.back(), usual);
+      o.terms.back() = both ? std::max(o.terms.back(), terms) : std::min(o.terms.back(), terms);
     } else {
+      bias0 = bias;
+      size0 = size;
       o.lo.push_back(lo);
       o.hi.push_back(hi);
       o.usual.push_back(usual);
@@ -311,15 +322,16 @@ static Bounds conv_bounds(const cnn_layer& l, const double* w, const double* b, 
 // cannot hold below its 22 to 24 bits is 2^-25 of a scaled value, 2^-40 of the bound
 // or of the row's largest weight, so the pairs are taken only where that is below
 // the rounding of FP32 itself, and the FP32 kernels elsewhere:
-// * an input channel's bound is at most 2^10 of its `terms`: 2^-40 of the bound is
-//   then 2^-6 of one FP32 rounding (2^-24 of the terms) of the sum that made the value,
-//   and no more than one on an image of grey level 1. (Bounds grow by 2^3 to 2^4 a layer
-//   over the values; with He-normal weights they are 2^2 of the terms after the first
-//   layer and 2^8 at FastMemb_ss's last such conv.)
-// * three quarters of a row's filters (those of its input channels) have a scaled tap
-//   of 2^3 or more: a pair holds them to 2^-28 of it (He-normal weights: 2^12). A
+// * an input channel's bound is at most 2^11 of its `terms`: 2^-40 of the bound is
+//   then 2^-5 of one FP32 rounding (2^-24 of the terms) of the sum that made the value,
+//   and two on an image of grey level 1. (Bounds grow by 2^3 to 2^5 a layer over the
+//   values; with He-normal weights they are 2^2 of the terms after the first layer and
+//   2^8 at FastMemb_ss's last such conv.)
+// * half of a row's filters (the taps on one input channel) that are not zero and whose
+//   channel is counted on have a scaled tap of 2^3 or more: a pair holds those to 2^-28
+//   of it, and smaller ones to 2^-28 of what those give (He-normal weights: 2^12). A
 //   channel that could reach far past the others, and scales the row by what it never
-//   shows, fails this.
+//   shows, fails this. Rows on no such channel: every filter.
 // Bounds or weights that are not finite, or scales past 2^100, fail too.
 static bool split_scales(int cin, int cout, int ks, const double* w, const Bounds& in, std::vector<int>& iexp,
                          std::vector<int>& rexp) {
@@ -330,12 +342,13 @@ static bool split_scales(int cin, int cout, int ks, const double* w, const Bound
   for (int ci = 0; ci < cin; ++ci) {
     if (!std::isfinite(in.lo[ci]) || !std::isfinite(in.hi[ci])) return false;
     const double m = std::max(std::fabs(in.lo[ci]), std::fabs(in.hi[ci]));
-    if (!(m <= std::ldexp(in.terms[ci], 10))) return false;
+    if (!(m <= std::ldexp(in.terms[ci], 11))) return false;
     if (m > 0) iexp[ci] = 14 - std::ilogb(m);
     if (std::abs(iexp[ci]) > 100) return false;
   }
-  std::vector<double> tap;  // largest scaled tap of each filter of the row
+  std::vector<double> tap;
   for (int co = 0; co < cout; ++co) {
+    double largest = 0, least = HUGE_VAL;  // of the filters' largest scaled taps
     tap.clear();
     for (int ci = 0; ci < cin; ++ci) {
       const double* p = w + ((size_t)co * cin + ci) * taps;
@@ -345,13 +358,21 @@ static bool split_scales(int cin, int cout, int ks, const double* w, const Bound
         m = a <= m ? m : a;  // a NaN stays until the next tap
         if (!std::isfinite(m)) return false;
       }
-      if (m > 0 && in.live(ci)) tap.push_back(std::ldexp((double)m, -iexp[ci]));
+      if (m == 0 || !in.live(ci)) continue;
+      const double scaled = std::ldexp((double)m, -iexp[ci]);
+      largest = std::max(largest, scaled);
+      least = std::min(least, scaled);
+      if (in.counts(ci)) tap.push_back(scaled);
     }
-    if (tap.empty()) continue;
-    rexp[co] = 14 - std::ilogb(*std::max_element(tap.begin(), tap.end()));
+    if (largest == 0) continue;
+    rexp[co] = 14 - std::ilogb(largest);
     if (std::abs(rexp[co]) > 100) return false;
-    std::nth_element(tap.begin(), tap.begin() + tap.size() / 4, tap.end());
-    if (tap[tap.size() / 4] < std::ldexp(1.0, 3 - rexp[co])) return false;
+    if (!tap.empty()) {
+      const size_t m = (tap.size() - 1) / 2;
+      std::nth_element(tap.begin(), tap.begin() + m, tap.end());
+      least = tap[m];
+    }
+    if (least < std::ldexp(1.0, 3 - rexp[co])) return false;
   }
   return true;
 }
